@@ -70,6 +70,8 @@ __global__ void k_init_ws(Status* st, double* mom, int64_t nmom, uint32_t* cnt, 
     st->far_flag = 0;
     st->far_decision = 0;
     st->win_blocks = st->glob_blocks = 0;
+    st->split_count[0] = st->split_count[1] = 0;
+    st->diag_ticket = 0;
   }
 }
 
@@ -116,6 +118,8 @@ Layout workspace_layout(const hvpic_params* p) {
   off += align256(p->ndim == 3 ? sizeof(int32_t) * (size_t)(ceil_div(cap, kChunk3) + 1 +
                                                            3 * (int64_t)p->ny * p->nz + 1)
                                : 0);
+  L.split_list = off;
+  off += align256(sizeof(int32_t) * 2 * (size_t)ceil_div(cap, 1024));
   L.total = off;
   return L;
 }
@@ -166,6 +170,7 @@ int hvpic_init(const hvpic_params* params, void* hip_stream, void* workspace, hv
   c->fscratch = (float*)(c->ws + L.fscratch);
   c->mom_acc = (double*)(c->ws + L.mom_acc);
   c->open_rows = params->open_x ? (int32_t*)(c->ws + L.open_rows) : nullptr;
+  c->split_list = (int32_t*)(c->ws + L.split_list);
   c->chunk_order = params->ndim == 3 ? (int32_t*)(c->ws + L.chunk_order) : nullptr;
   hipLaunchKernelGGL(k_init_ws, dim3(256), dim3(256), 0, c->stream, c->status, c->mom_acc,
                      4ll * c->ncell, c->sort_cnt,

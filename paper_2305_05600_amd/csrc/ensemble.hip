@@ -176,6 +176,15 @@ bool tuning_ok(const hvpic_tuning* t) {
   return true;
 }
 
+// Run r's push chunk (0..2): the tuned choice, but no longer than the plain
+// push takes (one that fits the LDS windows at the run's particles per cell).
+int push_choice(const hvpic_ensemble* e, int r) {
+  const int most = ens_plain_ppt(e->runs[r].store[0].n, e->runs[r].ctx->ncell);
+  int g = e->tune.push_chunk[e->pclass[r]];
+  while (g > 0 && kPpt[g] > most) --g;
+  return g;
+}
+
 // The item lists and both parities' tables for the current tuning, uploaded
 // with synchronous copies (never inside a capture).
 int build(hvpic_ensemble* e) {
@@ -188,7 +197,7 @@ int build(hvpic_ensemble* e) {
   for (int g = 0; g < 3; ++g) {
     e->push_off[g] = (int)push.size();
     for (int r = 0; r < R; ++r) {
-      if (e->tune.push_chunk[e->pclass[r]] != g) continue;
+      if (push_choice(e, r) != g) continue;
       const int nb = (int)ceil_div(e->runs[r].store[0].n, ens_chunk(kPpt[g]));
       for (int b = 0; b < nb; ++b) push.push_back(Item{r, b, nb});
     }
@@ -230,7 +239,7 @@ int build(hvpic_ensemble* e) {
     for (int r = 0; r < R; ++r) {
       hvpic_run& U = e->runs[r];
       hvpic_ctx* c = U.ctx;
-      const int g = e->tune.push_chunk[e->pclass[r]];
+      const int g = push_choice(e, r);
       const int shape = e->tune.field_tile[e->gclass[r]];
       ens_push_record(c, &U.store[a], U.perm, &U.store[b], U.cell_start[a], U.E, U.B,
                       U.push_diag != nullptr, pt.data() + e->push_rec * r);

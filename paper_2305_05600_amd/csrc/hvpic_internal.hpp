@@ -47,6 +47,13 @@ struct Status {
   // test (read by the kernels of the fallback and of the acceptance)
   uint32_t no_accept;
   uint32_t no_pad;
+  // chunks that the push left to its second kernel, and the blocks of that
+  // kernel that have ended (both zero between pushes)
+  uint32_t split_count[2];
+  // blocks of the running field kernel that have left their diagnostic
+  // partials (zero between launches)
+  uint32_t diag_ticket;
+  uint32_t diag_pad;
 };
 
 // One count per block of a particle kernel: whether it used the LDS windows.
@@ -188,6 +195,8 @@ struct hvpic_ctx {
   // 3D: the order in which the push takes its chunks [chunks + 1] and its
   // per-row workspace, or null
   int32_t* chunk_order;
+  // the push's chunks that do not fit one LDS window: {chunk, slot} [chunks]
+  int32_t* split_list;
   // the last injection: the store it appended to, its size before, count
   const int32_t* inj_cell;
   int64_t inj_n0, inj_k;
@@ -278,7 +287,9 @@ size_t ens_field_diag_record(hvpic_ctx* c, double* out, int shape, void* dst);
 int ens_launch_field(hipStream_t s, int shape, int K, int has_lin, int fin, const void* tab,
                      const Item* items, int nitems, int grid);
 int ens_launch_field_diag(hipStream_t s, const void* tab, int nruns);
-// particles per chunk of the 2D push for ppt particles per lane
+// particles per lane of the plain 2D push for n particles on ncell cells, and
+// particles per chunk for ppt particles per lane
+int ens_plain_ppt(int64_t n, int64_t ncell);
 constexpr int ens_chunk(int ppt) { return 256 * ppt; }
 // Per-block partial slots the field diagnostics need (the larger of the
 // output kernel's blocks and the 2D subcycle's tiles); kFieldPartStride
@@ -311,7 +322,7 @@ int launch_init_workspace(hvpic_ctx* c);
 // Workspace layout (bytes from the start; each region 256-byte aligned).
 struct Layout {
   size_t status, push_part, field_part, sort_cnt, sort_blk, rkey0, rkey1, rval0, rval1, rhist,
-      fscratch, mom_acc, open_rows, chunk_order, total;
+      fscratch, mom_acc, open_rows, chunk_order, split_list, total;
 };
 Layout workspace_layout(const hvpic_params* p);
 

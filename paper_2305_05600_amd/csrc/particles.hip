@@ -40,15 +40,12 @@
 namespace hvpic {
 namespace {
 
-// Particles per lane and per block, and the largest deposit-window width
-// (cells per band).  A 3D chunk spans more bands, so it is kept shorter.
-template <int NDIM>
-struct Chunk {
-  static constexpr int PPT = NDIM == 2 ? 12 : 4;
-  static constexpr int N = kBlock * PPT;
-  static constexpr int WMAX = NDIM == 2 ? 64 : 24;
-};
-static_assert(Chunk<3>::N == kChunk3, "workspace sizing of the 3D chunk order");
+// Particles per lane (a block's chunk is kBlock times that) and the largest
+// deposit-window width (cells per band) of the particle kernels.  A 3D chunk
+// spans more bands, so it is kept shorter.
+constexpr int kPpt3 = 4;
+constexpr int kWin2 = 64;
+static_assert(kBlock * kPpt3 == kChunk3, "workspace sizing of the 3D chunk order");
 
 struct Geo {
   int nx, ny, nz, ncell, nxny;
@@ -88,6 +85,8 @@ struct PushArgs {
   float* wo;
   bool off32;               // every source byte offset fits 32 bits (n < 2^30)
   const int32_t* order;     // position -> chunk (a permutation of the chunks), or null
+  int2* split_list;         // (chunk, slot) of the chunks left to k_push_split
+  uint32_t* split_count;    // their number, and the count of its blocks that ended
 };
 
 struct DepArgs {
@@ -227,11 +226,33 @@ struct Stencil {
   static constexpr int T = SHAPE == HVPIC_SHAPE_NGP ? 1 : (NDIM == 2 ? 5 : 7);
 };
 
-template <int NDIM>
-__device__ __forceinline__ bool window_ok(int c0, int c1, const Geo& g, int& W) {
-  W = c1 - c0 + 5;
-  return c0 >= 0 && c1 < g.ncell && c1 >= c0 && W <= Chunk<NDIM>::WMAX && g.nx >= 4 &&
-         (NDIM == 2 || g.ny >= 4);
+// The cells [first, last] of a block's chunk, taken through the LDS windows
+// in `passes` equal parts of at most WM - 4 cells each (a window has two more
+// columns at either end): one where the chunk fits, more where the density
+// is below what its length was chosen for; none (0) for an unsorted chunk, a
+// grid smaller than a stencil, or one so sparse that kMaxPasses windows do
+// not cover it.  A pass handles the particles whose cell lies in its part.
+constexpr int kMaxPasses = 16;
+struct Span {
+  int first, last, passes, part;
+  // cells [c0, c1] of pass t
+  __device__ __forceinline__ int begin(int t) const { return first + t * part; }
+  __device__ __forceinline__ int end(int t) const { return min(first + (t + 1) * part - 1, last); }
+};
+template <int NDIM, int WM>
+__device__ __forceinline__ Span chunk_span(int first, int last, const Geo& g) {
+  Span S{first, last, 0, 0};
+  if (first < 0 || last >= g.ncell || last < first || g.nx < 4 || (NDIM == 3 && g.ny < 4)) return S;
+  const int cells = last - first + 1;
+  if (cells <= WM - 4) {
+    S.passes = 1;
+    S.part = cells;
+  } else if (cells <= kMaxPasses * (WM - 4)) {
+    const int t = (cells + WM - 5) / (WM - 4);
+    S.part = (int)((uint32_t)(cells + t - 1) / (uint32_t)t);
+    S.passes = (int)((uint32_t)(cells + S.part - 1) / (uint32_t)S.part);
+  }
+  return S;
 }
 
 // Linear cell of deposit-window column `off` in band (by, bz): the window
@@ -419,9 +440,9 @@ __device__ __forceinline__ void dep_weights(float x, float y, float z, float* wt
 // cell (a particle's deposit cell) takes bands -1..1 only, so that its
 // stencil stays inside; the rare deposit cell further out (a diagonal
 // mid-point at a wrapped x or y edge) goes to the global accumulators.
-template <int NDIM>
+template <int NDIM, int WM>
 struct DWin {
-  static constexpr int SW = Chunk<NDIM>::WMAX;  // slots per band
+  static constexpr int SW = WM;                 // slots per band
   static constexpr int BZ = 5 * SW;             // slots per z band row (3D)
   static constexpr int NB = NDIM == 2 ? 5 : 25;
   static constexpr int LEN = NB * SW * 4;       // doubles
@@ -429,6 +450,7 @@ struct DWin {
 
 // The block's deposit window in LDS: the FP64 sums, and per slot the wrap
 // bits (as in stencil_slots) of that slot's cell.
+template <int WM>
 struct WinLds {
   double* acc;
   const uint8_t* wrap;
@@ -436,9 +458,9 @@ struct WinLds {
 
 // Window slots of the stencil cells of the cell at slot `key`; wrap bit 0/1:
 // its +x/-x neighbour wraps around the x boundary, bit 2/3 the same for y (3D).
-template <int NDIM, int SHAPE>
+template <int NDIM, int SHAPE, int WM>
 __device__ __forceinline__ void stencil_slots(int key, int wrap, int* s) {
-  constexpr int SW = DWin<NDIM>::SW, BZ = DWin<NDIM>::BZ;
+  constexpr int SW = DWin<NDIM, WM>::SW, BZ = DWin<NDIM, WM>::BZ;
   s[0] = key;
   if (SHAPE == HVPIC_SHAPE_QS) {
     s[1] = key + 1 - ((wrap & 1) ? SW : 0);
@@ -466,7 +488,7 @@ __device__ __forceinline__ int wrap_bits(int i, int j, const Geo& g) {
 // Window slot of the cell (mx, my, mz) away from the cell of window column
 // `rel` with indices (i, j), as a home cell; -1 when its band offset is
 // beyond -1..1 (the particle then deposits to the global accumulators).
-template <int NDIM>
+template <int NDIM, int WM>
 __device__ __forceinline__ int window_slot(int rel, int i, int j, int mx, int my, int mz,
                                            const Geo& g) {
   const int t1 = i + mx;
@@ -480,7 +502,7 @@ __device__ __forceinline__ int window_slot(int rel, int i, int j, int mx, int my
   }
   if (by < -1 || by > 1 || bz < -1 || bz > 1) return -1;
   const int band = NDIM == 3 ? (by + 2) + 5 * (bz + 2) : by + 2;
-  return band * DWin<NDIM>::SW + rel + mx + 2;
+  return band * DWin<NDIM, WM>::SW + rel + mx + 2;
 }
 
 // Deposit straight into the FP64 global accumulators (particles outside the
@@ -549,8 +571,8 @@ struct Queue {
 };
 
 // Adds every queued deposit to the window, lane e taking entry e.
-template <int NDIM, int SHAPE>
-__device__ __forceinline__ void queue_drain(Queue<NDIM>& Q, const WinLds& wl) {
+template <int NDIM, int SHAPE, int WM>
+__device__ __forceinline__ void queue_drain(Queue<NDIM>& Q, const WinLds<WM>& wl) {
   constexpr int T = Stencil<NDIM, SHAPE>::T;
   constexpr int QC = Queue<NDIM>::QCAP, o = NDIM == 3 ? 4 : 3;
   if (Q.count == 0) return;
@@ -566,7 +588,7 @@ __device__ __forceinline__ void queue_drain(Queue<NDIM>& Q, const WinLds& wl) {
     float wt[T];
     dep_weights<NDIM, SHAPE>(x, y, z, wt);
     int s[T];
-    stencil_slots<NDIM, SHAPE>(key, wl.wrap[key], s);
+    stencil_slots<NDIM, SHAPE, WM>(key, wl.wrap[key], s);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       const float nq = q * wt[t];
@@ -581,8 +603,8 @@ __device__ __forceinline__ void queue_drain(Queue<NDIM>& Q, const WinLds& wl) {
 }
 
 // Queues this lane's deposit when `exc`; every lane of the wavefront calls it.
-template <int NDIM, int SHAPE>
-__device__ __forceinline__ void queue_push(Queue<NDIM>& Q, const WinLds& wl, bool exc, int key,
+template <int NDIM, int SHAPE, int WM>
+__device__ __forceinline__ void queue_push(Queue<NDIM>& Q, const WinLds<WM>& wl, bool exc, int key,
                                            float x, float y, float z, float q, float vx,
                                            float vy, float vz) {
   constexpr int QC = Queue<NDIM>::QCAP, o = NDIM == 3 ? 4 : 3;
@@ -624,9 +646,9 @@ __device__ __forceinline__ void home_clear(Home<NDIM, SHAPE>& H) {
 // Deposit of one particle: into the home sums when its deposit cell is the
 // home cell, else into the queue (in the window) or the global accumulators.
 // Every lane of the wavefront calls it.
-template <int NDIM, int SHAPE>
+template <int NDIM, int SHAPE, int WM>
 __device__ __forceinline__ void deposit_particle(Home<NDIM, SHAPE>& H, Queue<NDIM>& Q,
-                                                 const WinLds& wl, bool live, bool inwin, int rel,
+                                                 const WinLds<WM>& wl, bool live, bool inwin, int rel,
                                                  int i, int j, int k, int mx, int my, int mz,
                                                  float x, float y, float z, float q, float vx,
                                                  float vy, float vz, const Geo& g,
@@ -634,7 +656,7 @@ __device__ __forceinline__ void deposit_particle(Home<NDIM, SHAPE>& H, Queue<NDI
   constexpr int T = Stencil<NDIM, SHAPE>::T;
   const bool near = live && inwin && mx >= -1 && mx <= 1 && my >= -1 && my <= 1 &&
                     mz >= -1 && mz <= 1;
-  const int key = near ? window_slot<NDIM>(rel, i, j, mx, my, mz, g) : -1;
+  const int key = near ? window_slot<NDIM, WM>(rel, i, j, mx, my, mz, g) : -1;
   const bool use_win = key >= 0;
   if (use_win && H.key < 0) H.key = key;
   const bool stay = use_win && key == H.key;
@@ -705,8 +727,8 @@ __device__ __forceinline__ void scan_level(float (&acc)[T][4], float m) {
 // alone adds it to the window: a few active lanes per cell in each FP64 LDS
 // atomic.  A level adds the neighbour's partial sum times 0 or 1, a DPP move
 // and one FMA.  Every lane of the wavefront calls it.
-template <int NDIM, int SHAPE>
-__device__ __forceinline__ void home_flush(Home<NDIM, SHAPE>& H, const WinLds& wl) {
+template <int NDIM, int SHAPE, int WM>
+__device__ __forceinline__ void home_flush(Home<NDIM, SHAPE>& H, const WinLds<WM>& wl) {
   constexpr int T = Stencil<NDIM, SHAPE>::T;
   const int r = threadIdx.x & 15;
   const int h = H.key;
@@ -734,7 +756,7 @@ __device__ __forceinline__ void home_flush(Home<NDIM, SHAPE>& H, const WinLds& w
   scan_level<8, T>(H.acc, m8);
   if (h >= 0 && last) {
     int s[T];
-    stencil_slots<NDIM, SHAPE>(h, wl.wrap[h], s);
+    stencil_slots<NDIM, SHAPE, WM>(h, wl.wrap[h], s);
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -746,9 +768,9 @@ __device__ __forceinline__ void home_flush(Home<NDIM, SHAPE>& H, const WinLds& w
 // Clears the deposit window (every slot of every band, so that the loops
 // divide by the compile-time band width only) and fills the wrap bits of the
 // cells of columns [0, W) (column 0 = cell c0 - 2).
-template <int NDIM>
+template <int NDIM, int WM>
 __device__ void dwin_init(double* win, uint8_t* wrap, int W, int c0, const Geo& g) {
-  constexpr int SW = DWin<NDIM>::SW, NB = DWin<NDIM>::NB;
+  constexpr int SW = DWin<NDIM, WM>::SW, NB = DWin<NDIM, WM>::NB;
   double2* w2 = reinterpret_cast<double2*>(win);
   for (int s = threadIdx.x; s < NB * SW * 2; s += kBlock) w2[s] = make_double2(0.0, 0.0);
   for (int s = threadIdx.x; s < NB * SW; s += kBlock) {
@@ -763,10 +785,10 @@ __device__ void dwin_init(double* win, uint8_t* wrap, int W, int c0, const Geo& 
 
 // Adds columns [0, W) of the block's deposit window (column 0 = cell c0 - 2)
 // to the FP64 global accumulators.
-template <int NDIM>
+template <int NDIM, int WM>
 __device__ void dwin_flush(const double* win, int W, int c0, const Geo& g,
                            double* __restrict__ acc) {
-  constexpr int SW = DWin<NDIM>::SW, NB = DWin<NDIM>::NB;
+  constexpr int SW = DWin<NDIM, WM>::SW, NB = DWin<NDIM, WM>::NB;
   for (int s = threadIdx.x; s < NB * SW * 4; s += kBlock) {
     const int band = s / (SW * 4), rest = s - band * (SW * 4);
     const int off = rest >> 2;
@@ -799,9 +821,11 @@ __device__ __forceinline__ void load4e(const T* __restrict__ p, int64_t i, int64
   for (int q = 0; q < 4; ++q) v[q] = i + q < end ? p[i + q] : T(0);
 }
 
+// Stores a lane's four values: one 16-byte access when `full`, else those of
+// the bits of `keep` below end.
 template <typename T>
 __device__ __forceinline__ void store4(T* __restrict__ p, int64_t i, int64_t end, bool full,
-                                       const T v[4]) {
+                                       uint32_t keep, const T v[4]) {
   if (full) {
     using V = typename std::conditional<std::is_same<T, int>::value, int4, float4>::type;
     V u;
@@ -813,7 +837,7 @@ __device__ __forceinline__ void store4(T* __restrict__ p, int64_t i, int64_t end
   } else {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (i + q < end) p[i + q] = v[q];
+      if (i + q < end && ((keep >> q) & 1u)) p[i + q] = v[q];
   }
 }
 
@@ -1083,7 +1107,10 @@ __device__ __forceinline__ void count_move(int d, bool inwin, int rel, int a, in
 template <int NDIM>
 __device__ __forceinline__ void count_flush(int& chome, uint32_t& nstay, uint32_t* s_cnt) {
   const int h = chome;
-  const bool same = h == dpp_i<0xB1>(h) && h == dpp_i<0x4E>(h) && h == dpp_i<0x1B>(h);
+  // every lane reads all three of its quad (an && would leave lanes that
+  // already differ inactive, and a read from an inactive lane gives 0)
+  const int h1 = dpp_i<0xB1>(h), h2 = dpp_i<0x4E>(h), h3 = dpp_i<0x1B>(h);
+  const bool same = (h == h1) & (h == h2) & (h == h3);
   uint32_t n = nstay;
   if (same) {
     n += (uint32_t)dpp_i<0xB1>((int)n);
@@ -1160,43 +1187,46 @@ __device__ void move_general(const PushArgs& A, float x, float y, float z, float
 
 // ---------------------------------------------------------------- kernels --
 
-// Fused gather + Boris push + move (+ mid-point deposit when DEP).
+// LDS of a block of the push.
+template <int NDIM, int SHAPE, bool DEP, int WM>
+struct PushLds {
+  float4 gw[WM * Rec<NDIM, SHAPE>::NF4];
+  double win[DEP ? DWin<NDIM, WM>::LEN : 2];
+  uint8_t wrap[DEP ? DWin<NDIM, WM>::NB * WM : 1];
+  float q[DEP ? kBlock / 64 * Queue<NDIM>::QCAP * Queue<NDIM>::QW : 1];
+  uint32_t cnt[WM * Moves<NDIM>::ND];
+  int32_t cs[WM + 1];
+};
+
+// What a chunk that does not fit one window does: kNever takes the global
+// path, kDefer leaves it in the list of k_push_split, which is the kPasses
+// form and takes several passes.  That form is a kernel of its own: the few
+// values that it carries along cost the common path registers when it is
+// inlined (2D QS 18 spilled; Harris step 337 to 341 us, full 3D push and sort
+// 6555 to 6677 us), and a call from the kernel costs more (345 and 6717 us).
+enum class Split { kNever, kDefer, kPasses };
+
+// Fused gather + Boris push + move (+ mid-point deposit when DEP) of the chunk
+// [base, end) of PPT*kBlock consecutive particles, whose cells run from first
+// to last.
 // At most 128 VGPRs, so that four wavefronts per SIMD keep enough loads in
 // flight (a 3D block's 35.8 KB of LDS allows four blocks per CU as well).
 // PM: 0 reads and writes the store in place; 1 and 2 read it through the
 // gather map A.perm (1: all byte offsets of the source arrays fit 32 bits).
-// The push of one chunk of PPT*kBlock consecutive particles of the store
-// (chunk `chunk` of the nb chunks of that store).  slot, a bijection of the
-// launch's blocks onto [0, nb) that does not depend on the data, picks the
-// block's share of the cell_start check and its diagnostic slot, so that
-// the check covers every entry even where a chunk order built from a bad
-// cell_start repeats a chunk.
-template <int NDIM, int SHAPE, bool DEP, int PM, int PPT>
-__device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slot, int nb) {
-  constexpr int NF4 = Rec<NDIM, SHAPE>::NF4;
-  constexpr int CN = kBlock * PPT;  // particles per chunk
-  __shared__ float4 gw[Chunk<NDIM>::WMAX * NF4];
-  __shared__ __attribute__((aligned(16))) double win[DEP ? DWin<NDIM>::LEN : 2];
-  __shared__ uint8_t s_wrap[DEP ? DWin<NDIM>::NB * DWin<NDIM>::SW : 1];
-  __shared__ float s_q[DEP ? kBlock / 64 * Queue<NDIM>::QCAP * Queue<NDIM>::QW : 1];
-  __shared__ uint32_t s_cnt[Chunk<NDIM>::WMAX * Moves<NDIM>::ND];
-  __shared__ int32_t s_cs[Chunk<NDIM>::WMAX + 1];
-  __shared__ int s_c[2];
+// slot picks the block's diagnostic slot (see push_chunk).
+template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM, Split MODE>
+__device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int64_t end,
+                                            int first, int last, int slot, int nb,
+                                            PushLds<NDIM, SHAPE, DEP, WM>& L) {
+  constexpr bool SPLIT = MODE == Split::kPasses;
   const Geo& g = A.g;
-  const int64_t base = (int64_t)chunk * CN;
-  const int64_t end = min(base + (int64_t)CN, A.n);
-  if (threadIdx.x == 0) {
-    if (PM != 0) {
-      // (entries outside [0, n) are flagged where the particles are loaded)
-      const uint32_t e0 = (uint32_t)A.perm[base], e1 = (uint32_t)A.perm[end - 1];
-      s_c[0] = A.icell[e0 < (uint32_t)A.nsrc ? e0 : 0];
-      s_c[1] = A.icell[e1 < (uint32_t)A.nsrc ? e1 : 0];
-    } else {
-      s_c[0] = A.cell[base];
-      s_c[1] = A.cell[end - 1];
-    }
-  }
-  __syncthreads();
+  float4* gw = L.gw;
+  double* win = L.win;
+  uint8_t* s_wrap = L.wrap;
+  float* s_q = L.q;
+  uint32_t* s_cnt = L.cnt;
+  int32_t* s_cs = L.cs;
+  const bool cnt_on = A.cs != nullptr;  // count the moves for the sort
   const bool want_diag = A.diag_part != nullptr;
   const bool wq = DEP || want_diag || PM != 0;  // the weights are needed
   // Wavefront wv owns particles [base + wv*64*PPT, +64*PPT); in each group
@@ -1208,25 +1238,27 @@ __device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slo
   // a step of the wavefront is all in range, or it takes element-wise accesses
   auto step_full = [&](int h) { return A.vec && wb + h * 64 + 256 <= end; };
   Group<NDIM> cur;
-  if (PM != 0)
-    load_group_perm<NDIM, PM>(A, lb, end, step_full(0), cur);
-  else
-    load_group<NDIM>(A, lb, end, step_full(0), wq, cur);
-  const int c0 = s_c[0], span = s_c[1] - s_c[0];
-  int W = 0;
-  const bool wok = window_ok<NDIM>(c0, s_c[1], g, W);
-  count_path(A.st, wok);
-  const bool cnt_on = A.cs != nullptr;  // count the moves for the sort
-  if (wok) {
-    gwin_fill<NDIM, SHAPE>(reinterpret_cast<float*>(gw), span + 1, c0, g, A.E, A.B);
-    if (DEP) dwin_init<NDIM>(win, s_wrap, W, c0, g);
-    if (cnt_on) moves_window_init<NDIM>(A.cs, c0, span, s_cs, s_cnt);
+  auto load_step = [&](int h) {
+    if (PM != 0)
+      load_group_perm<NDIM, PM>(A, lb + h * 64, end, step_full(h), cur);
+    else
+      load_group<NDIM>(A, lb + h * 64, end, step_full(h), wq, cur);
+  };
+
+  load_step(0);
+  const Span S = chunk_span<NDIM, WM>(first, last, g);
+  if (MODE == Split::kDefer && S.passes > 1) {
+    if (threadIdx.x == 0) {
+      const uint32_t at = atomicAdd(A.split_count, 1u);
+      if (at < (uint32_t)nb) A.split_list[at] = make_int2((int)(base / (kBlock * PPT)), slot);
+    }
+    if (cnt_on) check_cell_start(A.cs, g.ncell, A.n, A.st, slot, nb);
+    return;
   }
-  if (cnt_on) check_cell_start(A.cs, g.ncell, A.n, A.st, slot, nb);
-  __syncthreads();
+  const bool wok = SPLIT || S.passes == 1;
 
   float dK = 0.f, dP0 = 0.f, dP1 = 0.f, dP2 = 0.f;
-  const WinLds wl{win, s_wrap};
+  const WinLds<WM> wl{win, s_wrap};
   Home<NDIM, SHAPE> H;
   home_clear(H);
   Queue<NDIM> Q;
@@ -1234,28 +1266,52 @@ __device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slo
   Q.count = 0;
   int chome = -1;      // window column of the lane's home cell for move counts
   uint32_t nstay = 0;  // home-cell particles that stay in their cell
+  uint32_t done = 0;   // the lane's particles that an earlier pass has pushed
+  int pass = 0;
+#pragma unroll 1
+  do {
+  const int c0 = SPLIT ? S.begin(pass) : first;
+  const int span = (SPLIT ? S.end(pass) : last) - c0, W = span + 5;
+  if (SPLIT && pass > 0) load_step(0);
+  if (wok) {
+    gwin_fill<NDIM, SHAPE>(reinterpret_cast<float*>(gw), span + 1, c0, g, A.E, A.B);
+    if (DEP) dwin_init<NDIM, WM>(win, s_wrap, W, c0, g);
+    if (cnt_on) moves_window_init<NDIM>(A.cs, c0, span, s_cs, s_cnt);
+  }
+  if (pass == 0) {  // behind the loads of the first step
+    count_path(A.st, wok);
+    if (cnt_on && !SPLIT) check_cell_start(A.cs, g.ncell, A.n, A.st, slot, nb);
+  }
+  __syncthreads();
 #pragma unroll 1
   for (int h = 0; h < PPT; h += 4) {
     const int64_t b4 = lb + h * 64;
-    const bool full = step_full(h);
+    const bool full = step_full(h) && !SPLIT;
     int* ca = cur.ca;
     float *px = cur.px, *py = cur.py, *pz = cur.pz, *ux = cur.ux, *uy = cur.uy, *uz = cur.uz;
     const float* pw = cur.pw;
+    uint32_t keep = 0xFu;  // the lane's particles that this pass takes
+    if (SPLIT && PM == 0 && pass > 0) {
+      // in place, those that an earlier pass pushed hold their new cells: the
+      // chunk's first cell stands for "not in this pass" instead
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if ((done >> (h + q)) & 1u) ca[q] = S.first;
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      // Every lane runs the common path; a lane past the end or with a bad
-      // cell computes on finite stand-in values and has no effect.  Rare
-      // cases (outside the windows, far or non-finite moves, flags) take
-      // wavefront-uniform branches.
+      // Every lane runs the common path; a lane past the end, with a bad
+      // cell or of another pass computes on finite stand-in values and has no
+      // effect.  Rare cases (outside the windows, far or non-finite moves,
+      // flags) take wavefront-uniform branches.
       const int a = ca[q];
       const float x = px[q], y = py[q], z = NDIM == 3 ? pz[q] : 0.f;
       const float vx = ux[q], vy = uy[q], vz = uz[q];
       const bool inrange = b4 + q < end;
       const bool badcell = inrange && (unsigned)a >= (unsigned)g.ncell;
-      const bool live = inrange && !badcell;
-      const float wgt = wq && live ? pw[q] : 0.f;
+      bool live = inrange && !badcell;
       if (__ballot(badcell) != 0) {
-        if (badcell) raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
+        if (badcell && pass == 0) raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
       }
       const int rel = a - c0;
       const bool inwin = wok && rel >= 0 && rel <= span;
@@ -1267,14 +1323,21 @@ __device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slo
       // arithmetic of this rare path does not move the loaded cells into
       // aligned register pairs on the common path)
       int ag = 0;
-      const bool outwin = live && !inwin;
+      bool outwin = live && !inwin;
       if (__ballot(outwin) != 0) {
+        if (SPLIT && outwin && (pass > 0 || (a >= S.first && a <= S.last))) {
+          // another pass takes it (the first also takes what lies outside
+          // the chunk's cells altogether)
+          live = outwin = false;
+          keep &= ~(1u << q);
+        }
         if (outwin) {
           decompose(a, g, i, j, k);
           ag = i + g.nx * (j + g.ny * k);
           gather_eb<NDIM, SHAPE>(A.E, A.B, ag, i, j, k, x, y, z, g, Ep, Bp);
         }
       }
+      const float wgt = wq && live ? pw[q] : 0.f;
       // Boris: half kick, rotation, half kick.
       const float hh = A.a;
       const float vmx = fmaf(hh, Ep[0], vx), vmy = fmaf(hh, Ep[1], vy), vmz = fmaf(hh, Ep[2], vz);
@@ -1348,39 +1411,74 @@ __device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slo
         deposit_particle<NDIM, SHAPE>(H, Q, wl, live, inwin, rel, i, j, k, mx, my, mz, xm, ym,
                                       zm, A.qV * wgt, nvx, nvy, nvz, g, A.acc);
     }
-    store4(A.cell, b4, end, full, ca);
-    store4(A.ox, b4, end, full, px);
-    store4(A.oy, b4, end, full, py);
-    if (NDIM == 3) store4(A.oz, b4, end, full, pz);
-    store4(A.ux, b4, end, full, ux);
-    store4(A.uy, b4, end, full, uy);
-    store4(A.uz, b4, end, full, uz);
-    if (PM != 0) store4(A.wo, b4, end, full, pw);
+    store4(A.cell, b4, end, full, keep, ca);
+    store4(A.ox, b4, end, full, keep, px);
+    store4(A.oy, b4, end, full, keep, py);
+    if (NDIM == 3) store4(A.oz, b4, end, full, keep, pz);
+    store4(A.ux, b4, end, full, keep, ux);
+    store4(A.uy, b4, end, full, keep, uy);
+    store4(A.uz, b4, end, full, keep, uz);
+    if (PM != 0) store4(A.wo, b4, end, full, keep, pw);
+    if (SPLIT && PM == 0) done |= keep << h;
     // the next step's particles arrive during the flushes below
-    if (h + 4 < PPT) {
-      if (PM != 0)
-        load_group_perm<NDIM, PM>(A, b4 + 256, end, step_full(h + 4), cur);
-      else
-        load_group<NDIM>(A, b4 + 256, end, step_full(h + 4), wq, cur);
-    }
+    if (h + 4 < PPT) load_step(h + 4);
     if (DEP) home_flush(H, wl);
     if (cnt_on) count_flush<NDIM>(chome, nstay, s_cnt);
   }
   if (DEP) queue_drain<NDIM, SHAPE>(Q, wl);
+  if (wok && (DEP || cnt_on)) {
+    __syncthreads();
+    if (DEP) dwin_flush<NDIM, WM>(win, W, c0, g, A.acc);
+    if (cnt_on) moves_window_flush<NDIM>(s_cnt, c0, span, A.cnt);
+  }
+  // the next pass fills the windows again and reads what this one stored
+  if (SPLIT) __syncthreads();
+  } while (SPLIT && ++pass < S.passes);
   if (want_diag) {
     const double hm = 0.5 * A.ms;
     double v[4] = {hm * dK, hm * dP0, hm * dP1, hm * dP2};
     block_partial<4>(v, A.diag_part, slot);
   }
-  if (wok && (DEP || cnt_on)) {
-    __syncthreads();
-    if (DEP) dwin_flush<NDIM>(win, W, c0, g, A.acc);
-    if (cnt_on) moves_window_flush<NDIM>(s_cnt, c0, span, A.cnt);
-  }
 }
 
-template <int NDIM, int SHAPE, bool DEP, int PM>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
+// The push of chunk `chunk` of the nb chunks of PPT*kBlock consecutive
+// particles of the store.  slot, a bijection of the launch's blocks onto
+// [0, nb) that does not depend on the data, picks the block's share of the
+// cell_start check and its diagnostic slot, so that the check covers every
+// entry even where a chunk order built from a bad cell_start repeats a chunk.
+template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM, Split MODE>
+__device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slot, int nb) {
+  constexpr int CN = kBlock * PPT;  // particles per chunk
+  __shared__ __attribute__((aligned(16))) PushLds<NDIM, SHAPE, DEP, WM> lds;
+  __shared__ int s_c[2];
+  const int64_t base = (int64_t)chunk * CN;
+  const int64_t end = min(base + (int64_t)CN, A.n);
+  if (threadIdx.x == 0) {
+    if (PM != 0) {
+      // (entries outside [0, n) are flagged where the particles are loaded)
+      const uint32_t e0 = (uint32_t)A.perm[base], e1 = (uint32_t)A.perm[end - 1];
+      s_c[0] = A.icell[e0 < (uint32_t)A.nsrc ? e0 : 0];
+      s_c[1] = A.icell[e1 < (uint32_t)A.nsrc ? e1 : 0];
+    } else {
+      s_c[0] = A.cell[base];
+      s_c[1] = A.cell[end - 1];
+    }
+  }
+  __syncthreads();
+  push_passes<NDIM, SHAPE, DEP, PM, PPT, WM, MODE>(
+      A, base, end, __builtin_amdgcn_readfirstlane(s_c[0]),
+      __builtin_amdgcn_readfirstlane(s_c[1]), slot, nb, lds);
+}
+
+// Wavefronts per SIMD of the push: four unless a wider 3D window's LDS (53 KB
+// at 40 cells, 80 KB at 64) leaves room for fewer blocks.
+template <int NDIM, int WM>
+constexpr int push_waves() {
+  return NDIM == 2 || WM <= 24 ? 4 : (WM <= 40 ? 3 : 2);
+}
+
+template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(push_waves<NDIM, WM>())))
 void k_gather_push(PushArgs A) {
   const int slot = xcd_chunk(blockIdx.x, gridDim.x);
   int chunk = slot;
@@ -1388,7 +1486,26 @@ void k_gather_push(PushArgs A) {
     const int o = A.order[slot];
     if ((unsigned)o < gridDim.x) chunk = o;
   }
-  push_chunk<NDIM, SHAPE, DEP, PM, Chunk<NDIM>::PPT>(A, chunk, slot, gridDim.x);
+  push_chunk<NDIM, SHAPE, DEP, PM, PPT, WM, Split::kDefer>(A, chunk, slot, gridDim.x);
+}
+
+// The chunks that k_gather_push left in the list (nb chunks in all), a
+// persistent launch.  The last block to end empties the list for the next
+// push.
+template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM>
+__global__ __launch_bounds__(kBlock) void k_push_split(PushArgs A, int nb) {
+  const uint32_t m = min(*A.split_count, (uint32_t)nb);
+  if (m == 0) return;  // the same for every block: the list is empty and stays so
+  for (uint32_t i = blockIdx.x; i < m; i += gridDim.x) {
+    const int2 e = A.split_list[i];
+    push_chunk<NDIM, SHAPE, DEP, PM, PPT, WM, Split::kPasses>(A, e.x, e.y, nb);
+    __syncthreads();  // the next chunk reuses the LDS
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && atomicAdd(A.split_count + 1, 1u) == gridDim.x - 1) {
+    A.split_count[0] = 0;
+    A.split_count[1] = 0;
+  }
 }
 
 // The order in which the 3D push takes its chunks.  The store is sorted by
@@ -1493,28 +1610,26 @@ __global__ void k_order_write(int R, int nchunks, OrderWs W) {
 }
 
 // Stand-alone deposit at x - half_dt_back v (no push); same lane runs.
-template <int NDIM, int SHAPE>
+template <int NDIM, int SHAPE, int PPT, int WM>
 __global__ __launch_bounds__(kBlock) void k_deposit(DepArgs A) {
-  constexpr int PPT = Chunk<NDIM>::PPT;
-  __shared__ __attribute__((aligned(16))) double win[DWin<NDIM>::LEN];
-  __shared__ uint8_t s_wrap[DWin<NDIM>::NB * DWin<NDIM>::SW];
+  constexpr int CN = kBlock * PPT;  // particles per chunk
+  __shared__ __attribute__((aligned(16))) double win[DWin<NDIM, WM>::LEN];
+  __shared__ uint8_t s_wrap[DWin<NDIM, WM>::NB * WM];
   __shared__ float s_q[kBlock / 64 * Queue<NDIM>::QCAP * Queue<NDIM>::QW];
   __shared__ int s_c[2];
   const Geo& g = A.g;
-  const int64_t base = (int64_t)xcd_chunk(blockIdx.x, gridDim.x) * Chunk<NDIM>::N;
-  const int64_t end = min(base + (int64_t)Chunk<NDIM>::N, A.n);
+  const int64_t base = (int64_t)xcd_chunk(blockIdx.x, gridDim.x) * CN;
+  const int64_t end = min(base + (int64_t)CN, A.n);
   if (threadIdx.x == 0) {
     s_c[0] = A.cell[base];
     s_c[1] = A.cell[end - 1];
   }
   __syncthreads();
-  const int c0 = s_c[0], span = s_c[1] - s_c[0];
-  int W = 0;
-  const bool wok = window_ok<NDIM>(c0, s_c[1], g, W);
+  const Span S = chunk_span<NDIM, WM>(__builtin_amdgcn_readfirstlane(s_c[0]),
+                                      __builtin_amdgcn_readfirstlane(s_c[1]), g);
+  const bool wok = S.passes > 0;
   count_path(A.st, wok);
-  if (wok) dwin_init<NDIM>(win, s_wrap, W, c0, g);
-  __syncthreads();
-  const WinLds wl{win, s_wrap};
+  const WinLds<WM> wl{win, s_wrap};
   Home<NDIM, SHAPE> H;
   home_clear(H);
   Queue<NDIM> Q;
@@ -1522,6 +1637,12 @@ __global__ __launch_bounds__(kBlock) void k_deposit(DepArgs A) {
   Q.count = 0;
   const int64_t wb = base + (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 * PPT;
   const int64_t lb = wb + 4 * (threadIdx.x & 63);
+  int pass = 0;
+#pragma unroll 1
+  do {
+  const int c0 = S.begin(pass), span = S.end(pass) - c0, W = span + 5;
+  if (wok) dwin_init<NDIM, WM>(win, s_wrap, W, c0, g);
+  __syncthreads();
 #pragma unroll 1
   for (int h = 0; h < PPT; h += 4) {
     const int64_t b4 = lb + h * 64;
@@ -1537,10 +1658,14 @@ __global__ __launch_bounds__(kBlock) void k_deposit(DepArgs A) {
       int a = ca[q];
       bool live = b4 + q < end;
       if (live && (unsigned)a >= (unsigned)g.ncell) {
-        raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
+        if (pass == 0) raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
         live = false;
       }
       if (!live) a = 0;
+      const int rel = a - c0;
+      const bool inwin = wok && rel >= 0 && rel <= span;
+      // another pass takes it (see push_chunk)
+      if (S.passes > 1 && !inwin && (pass > 0 || (a >= S.first && a <= S.last))) live = false;
       int i = 0, j = 0, k = 0, mx = 0, my = 0, mz = 0;
       float x = px[q], y = py[q], z = NDIM == 3 ? pz[q] : 0.f;
       if (live) {
@@ -1555,8 +1680,6 @@ __global__ __launch_bounds__(kBlock) void k_deposit(DepArgs A) {
           mx = my = mz = 0;
         }
       }
-      const int rel = a - c0;
-      const bool inwin = wok && rel >= 0 && rel <= span;
       deposit_particle<NDIM, SHAPE>(H, Q, wl, live, inwin, rel, i, j, k, mx, my, mz, x, y, z,
                                     A.qV * pw[q], ux[q], uy[q], uz[q], g, A.acc);
     }
@@ -1565,8 +1688,10 @@ __global__ __launch_bounds__(kBlock) void k_deposit(DepArgs A) {
   queue_drain<NDIM, SHAPE>(Q, wl);
   if (wok) {
     __syncthreads();
-    dwin_flush<NDIM>(win, W, c0, g, A.acc);
+    dwin_flush<NDIM, WM>(win, W, c0, g, A.acc);
+    if (pass + 1 < S.passes) __syncthreads();  // the next pass fills the window again
   }
+  } while (++pass < S.passes);
 }
 
 __global__ void k_zero(float* __restrict__ a, int64_t na, float* __restrict__ b, int64_t nb) {
@@ -1649,22 +1774,78 @@ Geo make_geo(const hvpic_ctx* c) {
   return g;
 }
 
-template <int NDIM, int SHAPE, int PM>
-void push_dispatch_pm(bool dep, dim3 grid, hipStream_t s, const PushArgs& A) {
-  if (dep)
-    hipLaunchKernelGGL((k_gather_push<NDIM, SHAPE, true, PM>), grid, dim3(kBlock), 0, s, A);
-  else
-    hipLaunchKernelGGL((k_gather_push<NDIM, SHAPE, false, PM>), grid, dim3(kBlock), 0, s, A);
+// Chunk and window of a store of n particles.  A block works through its LDS
+// windows only if the cells of its chunk fit them; otherwise every particle
+// takes global gathers and up to 28 FP64 global atomics, which took 30 times
+// as long (413 x 257 cells of 36 ions: 3295 us in chunks of 3072, 75 us in
+// chunks of 1024).  So the chunk (2D: 3072, 2048 or 1024 ions) or the window
+// (3D: 24, 40 or 64 cells wide for 1024 ions) follows the ions per cell; the
+// limits lie where the chunk of a uniform store fills its window (2D 3072 /
+// 60 and 2048 / 60 cells, 3D 1024 / 20 and 1024 / 36), with a tenth to spare.
+// What is locally sparser goes to k_push_split.
+struct Plan {
+  int ppt, win;
+  int64_t chunk() const { return (int64_t)kBlock * ppt; }
+};
+template <int NDIM>
+Plan particle_plan(int64_t n, int64_t ncell) {
+  const double ppc = (double)n / (double)ncell;
+  if (NDIM == 3) return Plan{kPpt3, ppc >= 56.0 ? 24 : (ppc >= 31.0 ? 40 : 64)};
+  return Plan{ppc >= 60.0 ? 12 : (ppc >= 40.0 ? 8 : 4), kWin2};
 }
 
-template <int NDIM, int SHAPE>
-void push_dispatch(bool dep, dim3 grid, hipStream_t s, const PushArgs& A) {
-  if (!A.perm)
-    push_dispatch_pm<NDIM, SHAPE, 0>(dep, grid, s, A);
-  else if (A.off32)
-    push_dispatch_pm<NDIM, SHAPE, 1>(dep, grid, s, A);
+// Calls f(ppt, win) with the plan's values as compile-time constants.
+template <int NDIM, class F>
+void with_plan(const Plan& P, F f) {
+  using std::integral_constant;
+  if constexpr (NDIM == 2) {
+    const integral_constant<int, kWin2> w;
+    if (P.ppt == 4)
+      f(integral_constant<int, 4>{}, w);
+    else if (P.ppt == 8)
+      f(integral_constant<int, 8>{}, w);
+    else
+      f(integral_constant<int, 12>{}, w);
+  } else {
+    const integral_constant<int, kPpt3> p;
+    if (P.win == 24)
+      f(p, integral_constant<int, 24>{});
+    else if (P.win == 40)
+      f(p, integral_constant<int, 40>{});
+    else
+      f(p, integral_constant<int, 64>{});
+  }
+}
+
+template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM>
+void launch_push_kernels(hipStream_t s, const PushArgs& A) {
+  const int nb = (int)ceil_div(A.n, kBlock * PPT);
+  hipLaunchKernelGGL((k_gather_push<NDIM, SHAPE, DEP, PM, PPT, WM>), dim3(nb), dim3(kBlock), 0, s,
+                     A);
+  hipLaunchKernelGGL((k_push_split<NDIM, SHAPE, DEP, PM, PPT, WM>), dim3(std::min(nb, 256)),
+                     dim3(kBlock), 0, s, A, nb);
+}
+
+template <int NDIM, int SHAPE, bool DEP>
+void push_dispatch(const Plan& P, hipStream_t s, const PushArgs& A) {
+  with_plan<NDIM>(P, [&](auto ppt, auto win) {
+    if (!A.perm)
+      launch_push_kernels<NDIM, SHAPE, DEP, 0, ppt.value, win.value>(s, A);
+    else if (A.off32)
+      launch_push_kernels<NDIM, SHAPE, DEP, 1, ppt.value, win.value>(s, A);
+    else
+      launch_push_kernels<NDIM, SHAPE, DEP, 2, ppt.value, win.value>(s, A);
+  });
+}
+
+template <int NDIM>
+void push_dispatch(int shape, bool dep, const Plan& P, hipStream_t s, const PushArgs& A) {
+  if (shape == HVPIC_SHAPE_QS)
+    dep ? push_dispatch<NDIM, HVPIC_SHAPE_QS, true>(P, s, A)
+        : push_dispatch<NDIM, HVPIC_SHAPE_QS, false>(P, s, A);
   else
-    push_dispatch_pm<NDIM, SHAPE, 2>(dep, grid, s, A);
+    dep ? push_dispatch<NDIM, HVPIC_SHAPE_NGP, true>(P, s, A)
+        : push_dispatch<NDIM, HVPIC_SHAPE_NGP, false>(P, s, A);
 }
 
 int zero2(hvpic_ctx* c, float* a, int64_t na, float* b, int64_t nb) {
@@ -1745,6 +1926,8 @@ PushArgs push_args(hvpic_ctx* c, const hvpic_particles* in, const int32_t* perm,
   A.iw = in->w;
   A.wo = p->w;
   A.order = nullptr;
+  A.split_list = reinterpret_cast<int2*>(c->split_list);
+  A.split_count = c->status->split_count;
   return A;
 }
 
@@ -1762,13 +1945,14 @@ int launch_push(hvpic_ctx* c, const hvpic_particles* in, const int32_t* perm,
   }
   PushArgs A = push_args(c, in, perm, p, cell_start, E, B, diag_out);
   if (cell_start != nullptr && !c->cnt_clean) zero_counts(c);
-  const bool qs = c->p.shape == HVPIC_SHAPE_QS;
-  int nblocks = 0;
+  const Plan plan = c->p.ndim == 2 ? particle_plan<2>(p->n, c->ncell)
+                                   : particle_plan<3>(p->n, c->ncell);
+  const int nblocks = (int)ceil_div(p->n, plan.chunk());
   if (c->p.ndim == 3 && cell_start != nullptr && c->chunk_order &&
       (int64_t)c->p.ny * c->p.nz <= 65536) {
     // the chunk order (kernels of their own, outside the push's timing)
     const int R = c->p.ny * c->p.nz;
-    const int nch = (int)ceil_div(p->n, Chunk<3>::N);
+    const int nch = nblocks;
     OrderWs W;
     W.order = c->chunk_order;
     W.F = W.order + ceil_div(std::max<int64_t>(c->p.np_capacity, 1), kChunk3) + 1;
@@ -1784,15 +1968,10 @@ int launch_push(hvpic_ctx* c, const hvpic_particles* in, const int32_t* perm,
     A.order = W.order;
   }
   timing_begin(c, HVPIC_KERNEL_GATHER_PUSH);
-  if (c->p.ndim == 2) {
-    nblocks = (int)ceil_div(p->n, Chunk<2>::N);
-    if (qs) push_dispatch<2, HVPIC_SHAPE_QS>(dep, dim3(nblocks), c->stream, A);
-    else push_dispatch<2, HVPIC_SHAPE_NGP>(dep, dim3(nblocks), c->stream, A);
-  } else {
-    nblocks = (int)ceil_div(p->n, Chunk<3>::N);
-    if (qs) push_dispatch<3, HVPIC_SHAPE_QS>(dep, dim3(nblocks), c->stream, A);
-    else push_dispatch<3, HVPIC_SHAPE_NGP>(dep, dim3(nblocks), c->stream, A);
-  }
+  if (c->p.ndim == 2)
+    push_dispatch<2>(c->p.shape, dep, plan, c->stream, A);
+  else
+    push_dispatch<3>(c->p.shape, dep, plan, c->stream, A);
   timing_end(c, HVPIC_KERNEL_GATHER_PUSH);
   if (cell_start != nullptr) {
     c->cnt_clean = false;
@@ -1833,6 +2012,24 @@ int launch_gather_push_select(hvpic_ctx* c, const hvpic_particles* in, int64_t n
   return launch_push(c, in, perm, out, cell_start, E, B, n_mid, J_mid, diag_out);
 }
 
+namespace {
+
+template <int NDIM>
+void deposit_dispatch(hvpic_ctx* c, const DepArgs& A) {
+  const Plan P = particle_plan<NDIM>(A.n, c->ncell);
+  const dim3 grid((unsigned)ceil_div(A.n, P.chunk()));
+  with_plan<NDIM>(P, [&](auto ppt, auto win) {
+    if (c->p.shape == HVPIC_SHAPE_QS)
+      hipLaunchKernelGGL((k_deposit<NDIM, HVPIC_SHAPE_QS, ppt.value, win.value>), grid,
+                         dim3(kBlock), 0, c->stream, A);
+    else
+      hipLaunchKernelGGL((k_deposit<NDIM, HVPIC_SHAPE_NGP, ppt.value, win.value>), grid,
+                         dim3(kBlock), 0, c->stream, A);
+  });
+}
+
+}  // namespace
+
 int launch_deposit(hvpic_ctx* c, const hvpic_particles* p, const int32_t* cell_start,
                    float half_dt_back, float* n, float* J) {
   (void)cell_start;
@@ -1859,17 +2056,11 @@ int launch_deposit(hvpic_ctx* c, const hvpic_particles* p, const int32_t* cell_s
   A.qV = c->qV;
   A.st = c->status;
   A.vec = particles_aligned16(p);
-  const bool qs = c->p.shape == HVPIC_SHAPE_QS;
   timing_begin(c, HVPIC_KERNEL_DEPOSIT);
-  if (c->p.ndim == 2) {
-    const dim3 grid((unsigned)ceil_div(p->n, Chunk<2>::N));
-    if (qs) hipLaunchKernelGGL((k_deposit<2, HVPIC_SHAPE_QS>), grid, dim3(kBlock), 0, c->stream, A);
-    else hipLaunchKernelGGL((k_deposit<2, HVPIC_SHAPE_NGP>), grid, dim3(kBlock), 0, c->stream, A);
-  } else {
-    const dim3 grid((unsigned)ceil_div(p->n, Chunk<3>::N));
-    if (qs) hipLaunchKernelGGL((k_deposit<3, HVPIC_SHAPE_QS>), grid, dim3(kBlock), 0, c->stream, A);
-    else hipLaunchKernelGGL((k_deposit<3, HVPIC_SHAPE_NGP>), grid, dim3(kBlock), 0, c->stream, A);
-  }
+  if (c->p.ndim == 2)
+    deposit_dispatch<2>(c, A);
+  else
+    deposit_dispatch<3>(c, A);
   timing_end(c, HVPIC_KERNEL_DEPOSIT);
   moments_out(c, n, J);
   return hipGetLastError() == hipSuccess ? HVPIC_OK : HVPIC_EHIP;
@@ -1890,7 +2081,7 @@ void k_gather_push_batch(const PushArgs* __restrict__ tab, const Item* __restric
   for_items(nitems, [&](int it) {
     const Item item = items[it];
     const PushArgs A = tab[item.run];
-    push_chunk<2, SHAPE, true, 1, PPT>(A, item.idx, item.idx, item.nb);
+    push_chunk<2, SHAPE, true, 1, PPT, kWin2, Split::kNever>(A, item.idx, item.idx, item.nb);
     __syncthreads();  // the next item reuses the LDS
   });
 }
@@ -1942,6 +2133,8 @@ size_t ens_moments_record(hvpic_ctx* c, float* n, float* J, int nparts, double* 
 }
 
 int ens_moment_blocks(const hvpic_ctx* c) { return moment_blocks(c); }
+
+int ens_plain_ppt(int64_t n, int64_t ncell) { return particle_plan<2>(n, ncell).ppt; }
 
 int ens_launch_push(hipStream_t s, int shape, int ppt, const void* tab, const Item* items,
                     int nitems, int grid) {

@@ -1,0 +1,110 @@
+"""The particle kernels' chunk and window plans on uneven densities, against
+the FP64 oracle.
+
+A block takes its chunk of a sorted store through LDS windows over the chunk's
+cells, in several passes where a sparse region's chunk spans more cells than
+one window holds.  Boxes whose rows alternate between dense and sparse are
+pushed in place and through a map, with and without the fused deposit, at the
+average densities that select each plan (2D: 3072, 2048 and 1024 ions per
+block; 3D: windows of 24, 40 and 64 cells), and one box so sparse that a
+chunk needs more passes than a block makes.
+
+Tolerances: cells, sort order and cell_start bit-exact; velocities FP32
+rounding; moments 1e-5 relative L2."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2305_05600_amd import workloads as W
+from tests.helpers import announce, compare_particles, drop_push_straddlers, rel_l2
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def H():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2305_05600_amd import hvpic
+
+    hvpic.lib()
+    return hvpic
+
+
+def _cfg(ndim, shape):
+    dims = dict(nx=61, ny=24, nz=1, dz=1.0) if ndim == 2 else dict(nx=19, ny=10, nz=6, dz=0.7)
+    return W.Config(name="win", ndim=ndim, dx=0.5, dy=0.4, dt=0.05, nsub=3, shape=shape, te=0.2,
+                    eta=1e-3, **dims)
+
+
+def dev(a, dtype=None):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=dtype)).cuda()
+
+
+def _uneven(cfg, seed, ppc, thin):
+    """A sorted box of ppc ions per cell on average whose rows come in bands
+    of three dense ones and three with `thin` times the dense density."""
+    _, parts, B = W.random_box(seed, cfg, 2.0 * ppc / (1.0 + thin), vmax_cells=0.9)
+    rng = np.random.Generator(np.random.PCG64(seed + 1))
+    row = parts["cell"] // cfg.nx
+    keep = ((row // 3) % 2 == 0) | (rng.uniform(size=row.size) < thin)
+    parts = {k: np.ascontiguousarray(v[keep]) for k, v in parts.items()}
+    E = W.random_field(seed + 2, cfg, 0.3)
+    parts = drop_push_straddlers(cfg, parts, E, B, back=0.5 * cfg.dt)
+    perm, cs = O.sort(cfg, parts["cell"])
+    return {k: np.ascontiguousarray(v[perm]) for k, v in parts.items()}, E, B, cs
+
+
+PLANS = [(2, 90.0, 0.1), (2, 60.0, 0.1), (2, 30.0, 0.2), (2, 3.0, 0.05), (3, 70.0, 0.1),
+         (3, 45.0, 0.1), (3, 24.0, 0.2), (3, 5.0, 0.05)]
+
+
+@pytest.mark.parametrize("shape", [W.SHAPE_QS, W.SHAPE_NGP])
+@pytest.mark.parametrize("ndim,ppc,thin", PLANS)
+@pytest.mark.parametrize("mapped", [False, True])
+def test_uneven_density(H, ndim, ppc, thin, shape, mapped):
+    announce("uneven_density", ndim, ppc, thin, shape, mapped)
+    cfg = _cfg(ndim, shape)
+    parts, E, B, cs0 = _uneven(cfg, 900 + int(ppc), ppc, thin)
+    n = parts["cell"].size
+    ctx = H.Context(cfg, n)
+    cs_prev, cs = dev(cs0, np.int32), torch.zeros(cfg.ncell + 1, dtype=torch.int32, device="cuda")
+    n_mid = torch.full((cfg.ncell,), 7.0, device="cuda")
+    J_mid = torch.full((3, cfg.ncell), 7.0, device="cuda")
+    diag = torch.zeros(4, dtype=torch.float64, device="cuda")
+    ref = {k: v.copy() for k, v in O.particles64(parts).items()}
+    rd, st = O.push(cfg, ref, E, B)
+    rn, rJ = O.deposit(cfg, ref, 0.5 * cfg.dt)
+    rperm, rcs = O.sort(cfg, ref["cell"])
+    q = H.Particles(ndim, n)
+    if mapped:
+        # the store shuffled within itself, the map restoring its order
+        rng = np.random.Generator(np.random.PCG64(77))
+        order = rng.permutation(n)
+        inv = np.empty(n, np.int64)
+        inv[order] = np.arange(n)
+        p = H.Particles.from_numpy({k: np.ascontiguousarray(v[order]) for k, v in parts.items()}, ndim)
+        H.hvpic_gather_push_perm(ctx.ctx, p, dev(inv, np.int32), q, cs_prev, dev(E), dev(B), n_mid,
+                                 J_mid, diag)
+        pushed, perm = q, torch.zeros(n, dtype=torch.int32, device="cuda")
+        H.hvpic_sort_perm(ctx.ctx, q, cs_prev, perm, cs)
+        torch.cuda.synchronize()
+        assert np.array_equal(perm.cpu().numpy(), rperm)
+    else:
+        p = H.Particles.from_numpy(parts, ndim)
+        H.hvpic_gather_push(ctx.ctx, p, cs_prev, dev(E), dev(B), n_mid, J_mid, diag)
+        pushed = p
+        H.hvpic_sort(ctx.ctx, p, q, cs_prev, cs)
+    flags, counts = H.hvpic_sync_status(ctx.ctx)
+    assert flags == 0 and counts[0] == st.moved_gt1 == 0
+    compare_particles(cfg, pushed.to_numpy(), ref, band=0.0)
+    assert np.array_equal(cs.cpu().numpy(), rcs)
+    assert rel_l2(n_mid.cpu().numpy(), rn) < 1e-5
+    assert rel_l2(J_mid.cpu().numpy(), rJ) < 1e-5
+    assert np.allclose(diag.cpu().numpy(), rd, rtol=1e-5, atol=1e-6 * abs(rd[0]))
+    # the stand-alone deposit of the pushed store in its old order
+    H.hvpic_deposit(ctx.ctx, pushed, None, 0.5 * cfg.dt, n_mid, J_mid)
+    torch.cuda.synchronize()
+    assert rel_l2(n_mid.cpu().numpy(), rn) < 1e-5
+    assert rel_l2(J_mid.cpu().numpy(), rJ) < 1e-5

@@ -172,9 +172,9 @@ struct SubLds {
   static_assert(3 * PA::N + 3 * PS::N >= PB::N, "pressure plane overlays E and B*");
 };
 
-// FP64 sums of the five diagnostic values over a tile block (fixed order),
-// thread 0 writes them to out[0..4].
-__device__ void tile_partial(double* v, double* out) {
+// FP64 sums of the five diagnostic values over a tile block (fixed order), in
+// v of thread 0.
+__device__ void tile_partial(double* v) {
   __shared__ double s_red[kSubBlock / 64][kDiagNV];
 #pragma unroll
   for (int k = 0; k < kDiagNV; ++k)
@@ -187,7 +187,7 @@ __device__ void tile_partial(double* v, double* out) {
     for (int k = 0; k < kDiagNV; ++k) {
       double t = 0.0;
       for (int w = 0; w < kSubBlock / 64; ++w) t += s_red[w][k];
-      out[k] = t;
+      v[k] = t;
     }
 }
 
@@ -204,6 +204,7 @@ struct SubFinal {
   double* part;
   Status* st;
   const uint32_t* skip;  // non-null: the launch does nothing when *skip is set
+  DiagArgs diag;         // out non-null: the last block also finishes the diagnostics
 };
 
 template <int TX, int TY, int K, bool HAS_LIN, bool FINAL>
@@ -488,8 +489,14 @@ __device__ __forceinline__ void field_sub2d_body(
       atomicOr(&F.st->flags, (uint32_t)HVPIC_FLAG_FLOOR_HIT);
       atomicAdd(&F.st->floor_hits, (unsigned long long)__builtin_popcountll(m));
     }
-    if (F.part)
-      tile_partial(v, F.part + kFieldPartStride * (int64_t)slot);
+    if (F.part) {
+      tile_partial(v);
+      if (F.diag.out) {
+        if (threadIdx.x < 64) field_diag_last(F.diag, v, slot, &F.st->diag_ticket);
+      } else if (threadIdx.x == 0) {
+        for (int k = 0; k < kDiagNV; ++k) F.part[kFieldPartStride * (int64_t)slot + k] = v[k];
+      }
+    }
   }
 }
 
@@ -656,6 +663,8 @@ int field_impl(hvpic_ctx* c, float* B, const float* n_half, const float* J_half,
   float* Yl = c->fscratch + 16ll * nc;
   const Eos eos = make_eos(c);
   const float eta = (float)c->p.eta;
+  const double V = c->p.dx * c->p.dy * c->p.dz;
+  const double we_scale = eos.iso ? V * c->p.te : V * c->p.n0 * c->p.te / (c->p.gamma_e - 1.0);
   const float* fh = B;        // final B = fh + fl
   const float* fl = nullptr;
   bool fused_final = false;   // the last 2D tile launch wrote E, B and the partials
@@ -684,6 +693,9 @@ int field_impl(hvpic_ctx* c, float* B, const float* n_half, const float* J_half,
       F.Bfin = B;
       F.part = diag_out ? c->field_part : nullptr;
       F.st = c->status;
+      if (diag_out && (int64_t)tiles.x * tiles.y <= kDiagTicketBlocks)
+        F.diag = DiagArgs{c->field_part, (int)(tiles.x * tiles.y), diag_out, 0.5 * V,
+                          1.0 / (double)nc, we_scale};
       const SubFinal none{};
       for (int m = 0; m < c->p.nsub;) {
         const bool two = c->p.nsub - m >= 2;
@@ -739,11 +751,9 @@ int field_impl(hvpic_ctx* c, float* B, const float* n_half, const float* J_half,
   }
   // E^{n+1} from the extrapolated moments (mode 0) or E from the given ones
   // (mode 1), the final B, the floor count of n_half and the diagnostics
-  const double V = c->p.dx * c->p.dy * c->p.dz;
-  const double we_scale = eos.iso ? V * c->p.te : V * c->p.n0 * c->p.te / (c->p.gamma_e - 1.0);
   if (fused_final) {
-    if (diag_out) {
-      const dim3 tiles((unsigned)ceil_div(c->p.nx, kTX), (unsigned)ceil_div(c->p.ny, kTY));
+    const dim3 tiles((unsigned)ceil_div(c->p.nx, kTX), (unsigned)ceil_div(c->p.ny, kTY));
+    if (diag_out && (int64_t)tiles.x * tiles.y > kDiagTicketBlocks) {
       hipLaunchKernelGGL(k_field_diag_final, dim3(1), dim3(1024), 0, s,
                          (const double*)c->field_part, (int)(tiles.x * tiles.y), diag_out,
                          0.5 * V, 1.0 / (double)nc, we_scale);

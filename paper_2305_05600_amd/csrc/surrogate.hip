@@ -6,16 +6,17 @@
 // 7 -> 32 -> 32 -> 32 -> 3 channels with tanh between them map the
 // normalised (B^n, n^{n+1/2}, J_i^{n+1/2}) to the normalised increment
 // B^{n+1} - B^n.  Inference and training run here: BF16 operands on the
-// matrix cores (v_mfma_f32_16x16x16_bf16) with FP32 accumulation, FP32 master
+// matrix cores (v_mfma_f32_16x16x32_bf16) with FP32 accumulation, FP32 master
 // weights and Adam.
 //
 // Layout: activations are pixel-major with the channels contiguous ([pixel]
-// [channel], BF16), so that one lane's 4 consecutive channels are one 8-byte
+// [channel], BF16), so that one lane's 8 consecutive channels are one 16-byte
 // load; a layer is an implicit GEMM (out channels) x (pixels) with K = 9 taps
 // x in channels, the taps wrapping around each image.  Channel counts are
 // padded to 16 (7 inputs, 3 outputs) with zero weights.  The weight gradient
-// stages 64-pixel segments in LDS channel-major, so its operands are also
-// 8-byte reads; blocks leave partial sums that one pass adds in a fixed order.
+// has its K along the pixels: it stages pixel-major tiles in LDS and reads its
+// operands through the transposing LDS load; blocks leave partial sums that
+// one pass adds in a fixed order.
 #include <string.h>
 
 #include <algorithm>
@@ -27,6 +28,9 @@ namespace {
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+// 16-byte global accesses at 8-byte aligned addresses
+typedef uint32_t u4a8 __attribute__((ext_vector_type(4), aligned(8)));
 
 constexpr int kNL = 4;
 constexpr int kCin[kNL] = {7, 32, 32, 32}, kCout[kNL] = {32, 32, 32, 3};
@@ -62,83 +66,138 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// pixel q of the same image as p, shifted by (dy, dx) with periodic wrap
-__device__ __forceinline__ int64_t shifted(int64_t img0, int y, int x, int dy, int dx, int nx,
-                                          int ny) {
-  int yy = y + dy, xx = x + dx;
-  yy = yy < 0 ? yy + ny : (yy >= ny ? yy - ny : yy);
-  xx = xx < 0 ? xx + nx : (xx >= nx ? xx - nx : xx);
-  return img0 + (int64_t)yy * nx + xx;
+// tanh in FP32: the odd Taylor series below 0.35 (next term 2.4e-7 of x),
+// else 1 - 2 / (1 + exp(2|x|)) with the sign of x, by the hardware's exp2 and
+// reciprocal (1 ulp each): within 3e-7 of the value.  The math library's took
+// twice the time of the layer's matrix instructions.
+__device__ __forceinline__ float tanh_f32(float x) {
+  const float a = fabsf(x), s = x * x;
+  const float e = __builtin_amdgcn_exp2f(2.88539008f * a);
+  const float big = copysignf(1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + e), x);
+  float p = fmaf(s, 62.0f / 2835.0f, -17.0f / 315.0f);
+  p = fmaf(s, p, 2.0f / 15.0f);
+  p = fmaf(s, p, -1.0f / 3.0f);
+  return a < 0.35f ? fmaf(x * s, p, x) : big;
 }
 
 // One periodic 3x3 layer over N = nimg*ny*nx pixels.  W: bf16
 // [COUTP][9][CINP].  MODE 0: out bf16 = tanh(acc + bias); 1: out f32 = acc +
 // bias; 2: out bf16 = acc * (1 - h^2) with h from H [N][COUTP] (the
-// backward-data product of a tanh layer, no bias).  A wavefront takes 16
-// consecutive pixels; lane (ln, lq) = (lane % 16, lane / 16) holds the
-// channels 4lq..4lq+3 of pixel ln for the B operand and of output row ln for
-// the A operand, and receives out channels 4lq..4lq+3 of pixel ln.
+// backward-data product of a tanh layer, no bias).
+//
+// A wavefront takes tiles of 16 consecutive pixels; lane (ln, lq) = (lane %
+// 16, lane / 16) holds, of each group of 32 k, the k 8 lq .. 8 lq + 7 of pixel
+// ln for the B operand and of output row ln for the A operand, and receives
+// out channels 4lq..4lq+3 of pixel ln.  A group is one tap's 32 channels, or
+// two taps' 16 (the tenth tap is zero).  What bounds it: the activations
+// cross HBM once (a 32-channel layer of a million pixels moves 134 MB), and
+// each is read nine times from L1 and L2.  The weights stay in registers (72
+// of them at 32 x 32 channels) over all tiles of the wavefront: read from LDS
+// for every tile they took one LDS access per matrix instruction.  The next
+// tile's nine loads go out before the current tile's products.
+// 32 -> 32 at 1,048,576 pixels: 125 to 49 us (2.7 TB/s of HBM); at 131,072 29 to
+// 12 us.
 template <int CINP, int COUTP, int MODE>
-__global__ __launch_bounds__(256) void k_conv3x3(const uint16_t* __restrict__ X,
-                                                 const uint16_t* __restrict__ W,
-                                                 const float* __restrict__ bias,
-                                                 const uint16_t* __restrict__ Hact,
-                                                 void* __restrict__ out, int64_t N, int nx,
-                                                 int ny) {
-  constexpr int MT = COUTP / 16, KB = CINP / 16, NW = COUTP * 9 * CINP;
-  __shared__ uint16_t sw[NW];
-  for (int i = threadIdx.x; i < NW / 4; i += 256)
-    reinterpret_cast<uint2*>(sw)[i] = reinterpret_cast<const uint2*>(W)[i];
-  __syncthreads();
+__global__ __launch_bounds__(256, 2) void k_conv3x3(const uint16_t* __restrict__ X,
+                                                    const uint16_t* __restrict__ W,
+                                                    const float* __restrict__ bias,
+                                                    const uint16_t* __restrict__ Hact,
+                                                    void* __restrict__ out, uint32_t N, int nx,
+                                                    int ny, FastDiv fP, FastDiv fnx) {
+  constexpr int MT = COUTP / 16, TPG = 32 / CINP, NG = (9 + TPG - 1) / TPG;  // taps per group, groups
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int ln = lane & 15, lq = lane >> 4;
-  const int64_t P = (int64_t)nx * ny;
-  const int64_t ntiles = (N + 15) / 16;
-  for (int64_t tile = (int64_t)blockIdx.x * 4 + wid; tile < ntiles;
-       tile += (int64_t)gridDim.x * 4) {
-    const int64_t p = tile * 16 + ln;
+  const int sub = lq * 8 / CINP, ch = lq * 8 % CINP;  // the lane's tap in a group, and channels
+  v8b w[NG][MT];
+#pragma unroll
+  for (int q = 0; q < NG; ++q) {
+    const int t = q * TPG + sub;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      u4a8 v = {0u, 0u, 0u, 0u};
+      if (t < 9) v = *reinterpret_cast<const u4a8*>(W + ((mt * 16 + ln) * 9 + t) * CINP + ch);
+      w[q][mt] = __builtin_bit_cast(v8b, v);
+    }
+  }
+  float bs[MT][4];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bs[mt][i] = MODE == 2 ? 0.0f : bias[mt * 16 + lq * 4 + i];
+  const uint32_t ntiles = (uint32_t)(((uint64_t)N + 15) / 16);
+  // block b's tiles are contiguous (neighbouring rows share its L1), and an
+  // XCD's blocks take a contiguous eighth of them (they share its L2)
+  const uint32_t nb = gridDim.x, per8 = nb / 8, rem8 = nb % 8, xcd = blockIdx.x % 8;
+  const uint32_t blk = xcd * per8 + min(xcd, rem8) + blockIdx.x / 8;
+  const uint32_t t1 = (uint32_t)((uint64_t)(blk + 1) * ntiles / nb);
+  uint32_t tile = (uint32_t)((uint64_t)blk * ntiles / nb) + (uint32_t)wid;
+  auto load = [&](uint32_t tl, u4a8* v) {
+    // a lane past the end reads the last pixel (never stored)
+    const uint32_t p = min(tl * 16 + (uint32_t)ln, N - 1);
+    const uint32_t img = fdiv(p, fP), r = p - img * fP.d;
+    const int y = (int)fdiv(r, fnx), x = (int)(r - (uint32_t)y * fnx.d);
+    const int yy[3] = {(y == 0 ? ny : y) - 1, y, y == ny - 1 ? 0 : y + 1};
+    const int xx[3] = {(x == 0 ? nx : x) - 1, x, x == nx - 1 ? 0 : x + 1};
+    const uint16_t* base = X + (int64_t)img * fP.d * CINP + ch;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      int yt, xt;
+      if (TPG == 1) {
+        yt = yy[q / 3];
+        xt = xx[q % 3];
+      } else {  // two taps a group: the lane's own (the tenth tap reads the last one's pixel)
+        constexpr int last = 8;
+        const int ta = q * TPG < last ? q * TPG : last, tb = q * TPG + 1 < last ? q * TPG + 1 : last;
+        yt = sub == 0 ? yy[ta / 3] : yy[tb / 3];
+        xt = sub == 0 ? xx[ta % 3] : xx[tb % 3];
+      }
+      v[q] = *reinterpret_cast<const u4a8*>(base + ((int64_t)yt * nx + xt) * CINP);
+    }
+  };
+  u4a8 cur[NG], nxt[NG];
+  if (tile < t1) load(tile, cur);
+  for (; tile < t1; tile += 4) {
+    if (tile + 4 < t1) load(tile + 4, nxt);
+    const uint32_t p = tile * 16 + (uint32_t)ln;
     const bool live = p < N;
-    const int64_t img = live ? p / P : 0;
-    const int r = live ? (int)(p - img * P) : 0;
-    const int y = r / nx, x = r - (r / nx) * nx;
+    uint2 hv[MT];
+    if (MODE == 2)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        hv[mt] = *reinterpret_cast<const uint2*>(Hact + (int64_t)min(p, N - 1) * COUTP + mt * 16 +
+                                                 lq * 4);
     v4f acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const int64_t q = shifted(img * P, y, x, t / 3 - 1, t % 3 - 1, nx, ny);
+    for (int q = 0; q < NG; ++q)
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        v4s b = v4s{0, 0, 0, 0};
-        if (live) b = *reinterpret_cast<const v4s*>(X + q * CINP + kb * 16 + lq * 4);
+      for (int mt = 0; mt < MT; ++mt)
+        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[q][mt], __builtin_bit_cast(v8b, cur[q]),
+                                                          acc[mt], 0, 0, 0);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const v4s a =
-              *reinterpret_cast<const v4s*>(sw + ((mt * 16 + ln) * 9 + t) * CINP + kb * 16 + lq * 4);
-          acc[mt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[mt], 0, 0, 0);
-        }
-      }
-    }
+    for (int q = 0; q < NG; ++q) cur[q] = nxt[q];
     if (!live) continue;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const int co = mt * 16 + lq * 4;
       if (MODE == 1) {
         float4 v;
-        v.x = acc[mt][0] + bias[co];
-        v.y = acc[mt][1] + bias[co + 1];
-        v.z = acc[mt][2] + bias[co + 2];
-        v.w = acc[mt][3] + bias[co + 3];
-        *reinterpret_cast<float4*>(static_cast<float*>(out) + p * COUTP + co) = v;
+        v.x = acc[mt][0] + bs[mt][0];
+        v.y = acc[mt][1] + bs[mt][1];
+        v.z = acc[mt][2] + bs[mt][2];
+        v.w = acc[mt][3] + bs[mt][3];
+        *reinterpret_cast<float4*>(static_cast<float*>(out) + (int64_t)p * COUTP + co) = v;
       } else {
         uint16_t o[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           float v;
           if (MODE == 0) {
-            v = tanhf(acc[mt][i] + bias[co + i]);
+            v = tanh_f32(acc[mt][i] + bs[mt][i]);
           } else {
-            const float h = bf2f(Hact[p * COUTP + co + i]);
+            const uint32_t hw = i < 2 ? hv[mt].x : hv[mt].y;
+            const float h = bf2f((uint16_t)(i & 1 ? hw >> 16 : hw & 0xFFFFu));
             v = acc[mt][i] * (1.0f - h * h);
           }
           o[i] = f2bf(v);
@@ -146,7 +205,7 @@ __global__ __launch_bounds__(256) void k_conv3x3(const uint16_t* __restrict__ X,
         uint2 pk;
         pk.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
         pk.y = (uint32_t)o[2] | ((uint32_t)o[3] << 16);
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + p * COUTP + co) = pk;
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + (int64_t)p * COUTP + co) = pk;
       }
     }
   }
@@ -154,99 +213,181 @@ __global__ __launch_bounds__(256) void k_conv3x3(const uint16_t* __restrict__ X,
 
 // Weight gradient of a periodic 3x3 layer: dW[co][t][ci] = sum_p dZ[p][co]
 // X[p + off(t)][ci], db[co] = sum_p dZ[p][co], as per-block partials
-// part[block][COUTP*9*CINP + COUTP].  A block takes 64-pixel segments: dZ and
-// the 9 shifted copies of X go to LDS channel-major, then each wavefront
-// accumulates its share of the 9 * (COUTP/16) * (CINP/16) output tiles over
-// the segment's four 16-pixel steps.
-constexpr int kSeg = 64;
+// part[block][COUTP*9*CINP + COUTP].
+//
+// A block takes tiles of 32 x 8 pixels, one row per wavefront: dZ and X with a
+// one-pixel rim go to LDS as they lie in memory (pixel-major), each X once
+// instead of once per tap.  K runs along the 32 pixels of a row: both operands
+// come through the transposing LDS load, whose 16 lanes read 4 pixels x 16
+// channels and each receive one channel of the 4 pixels (the same pixels in
+// the same places for A and B, so their order does not matter); a tap is an
+// offset of the X address.  A wavefront keeps all 9 * (COUTP/16) * (CINP/16)
+// output tiles and the sums of dZ (a product with ones) in registers, and the
+// eight wavefronts add theirs in order at the end.  The pixel stride (80 or 48
+// bytes) spreads the 16 pixels of an access over all banks.  The next tile's
+// loads go out before the current tile's products.
+// 32 x 32 channels, 1,048,576 pixels: 763 to 72 us (134 MB, 19.3 GFLOP).
+constexpr int kSegX = 32, kSegY = 8, kWgThreads = 64 * kSegY;
 template <int CINP, int COUTP>
-__global__ __launch_bounds__(256) void k_conv3x3_wgrad(const uint16_t* __restrict__ X,
-                                                       const uint16_t* __restrict__ dZ,
-                                                       float* __restrict__ part, int64_t N, int nx,
-                                                       int ny) {
-  constexpr int MT = COUTP / 16, NT = CINP / 16, TILES = 9 * MT * NT, TPW = (TILES + 3) / 4;
-  constexpr int NWT = COUTP * 9 * CINP;
-  __shared__ uint16_t sz[COUTP * kSeg];
-  __shared__ uint16_t sx[9 * CINP * kSeg];
+__global__ __launch_bounds__(kWgThreads, 2) void k_conv3x3_wgrad(const uint16_t* __restrict__ X,
+                                                                 const uint16_t* __restrict__ dZ,
+                                                                 float* __restrict__ part, int nimg,
+                                                                 int nx, int ny) {
+  constexpr int MT = COUTP / 16, NT = CINP / 16, NWT = COUTP * 9 * CINP;
+  constexpr int XW = kSegX + 2, XH = kSegY + 2;              // X tile with its rim
+  constexpr int XS = CINP + 8, ZS = COUTP + 8;               // pixel strides
+  constexpr int XC = CINP / 8, ZC = COUTP / 8;               // 16-byte chunks per pixel
+  constexpr int XN = XW * XH * XC, ZN = kSegX * kSegY * ZC;
+  constexpr int XL = (XN + kWgThreads - 1) / kWgThreads, ZL = (ZN + kWgThreads - 1) / kWgThreads;
+  constexpr int LX = XW * XH * XS, LZ = kSegX * kSegY * ZS;  // halves
+  constexpr int LB = 2 * (LX + LZ), LR = 2 * (NWT + COUTP);
+  __shared__ __attribute__((aligned(16))) uint16_t lds[LB > LR ? LB : LR];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int ln = lane & 15, lq = lane >> 4;
   const int64_t P = (int64_t)nx * ny;
-  v4f acc[TPW];
+  const int nsx = (nx + kSegX - 1) / kSegX, nsy = (ny + kSegY - 1) / kSegY;
+  const int64_t steps = (int64_t)nimg * nsx * nsy;
+  const int64_t s0 = steps * blockIdx.x / gridDim.x, s1 = steps * (blockIdx.x + 1) / gridDim.x;
+  u4a8 gx[XL], gz[ZL];
+  auto load = [&](int64_t st) {
+    const int64_t img = st / ((int64_t)nsx * nsy);
+    const int r = (int)(st - img * nsx * nsy), sx = r / nsy, sy = r - sx * nsy;
+    const int x0 = sx * kSegX, y0 = sy * kSegY;
+    const int w = min(kSegX, nx - x0), h = min(kSegY, ny - y0);
 #pragma unroll
-  for (int j = 0; j < TPW; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
-  float dbacc = 0.f;
-  const int64_t nseg = (N + kSeg - 1) / kSeg;
-  for (int64_t sg = blockIdx.x; sg < nseg; sg += gridDim.x) {
-    const int64_t p0 = sg * kSeg;
-    for (int e = threadIdx.x; e < kSeg * COUTP / 4; e += 256) {
-      const int px = e / (COUTP / 4), cq = (e % (COUTP / 4)) * 4;
-      const int64_t p = p0 + px;
-      uint2 v = make_uint2(0u, 0u);
-      if (p < N) v = *reinterpret_cast<const uint2*>(dZ + p * COUTP + cq);
-      sz[(cq + 0) * kSeg + px] = (uint16_t)(v.x & 0xFFFFu);
-      sz[(cq + 1) * kSeg + px] = (uint16_t)(v.x >> 16);
-      sz[(cq + 2) * kSeg + px] = (uint16_t)(v.y & 0xFFFFu);
-      sz[(cq + 3) * kSeg + px] = (uint16_t)(v.y >> 16);
-    }
-    for (int e = threadIdx.x; e < 9 * kSeg * CINP / 4; e += 256) {
-      const int t = e / (kSeg * CINP / 4), rem = e % (kSeg * CINP / 4);
-      const int px = rem / (CINP / 4), cq = (rem % (CINP / 4)) * 4;
-      const int64_t p = p0 + px;
-      uint2 v = make_uint2(0u, 0u);
-      if (p < N) {
-        const int64_t img = p / P;
-        const int r = (int)(p - img * P), y = r / nx, x = r - (r / nx) * nx;
-        const int64_t q = shifted(img * P, y, x, t / 3 - 1, t % 3 - 1, nx, ny);
-        v = *reinterpret_cast<const uint2*>(X + q * CINP + cq);
-      }
-      uint16_t* d = sx + ((size_t)t * CINP + cq) * kSeg + px;
-      d[0] = (uint16_t)(v.x & 0xFFFFu);
-      d[kSeg] = (uint16_t)(v.x >> 16);
-      d[2 * kSeg] = (uint16_t)(v.y & 0xFFFFu);
-      d[3 * kSeg] = (uint16_t)(v.y >> 16);
-    }
-    __syncthreads();
-    if (threadIdx.x < COUTP)
-      for (int k = 0; k < kSeg; ++k) dbacc += bf2f(sz[threadIdx.x * kSeg + k]);
-#pragma unroll
-    for (int j = 0; j < TPW; ++j) {
-      const int q = wid + 4 * j;
-      if (q < TILES) {
-        const int t = q / (MT * NT), mt = (q / NT) % MT, nt = q % NT;
-#pragma unroll
-        for (int k0 = 0; k0 < kSeg; k0 += 16) {
-          const v4s a = *reinterpret_cast<const v4s*>(sz + (mt * 16 + ln) * kSeg + k0 + lq * 4);
-          const v4s b = *reinterpret_cast<const v4s*>(
-              sx + ((size_t)t * CINP + nt * 16 + ln) * kSeg + k0 + lq * 4);
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[j], 0, 0, 0);
-        }
+    for (int u = 0; u < XL; ++u) {
+      const int e = (int)threadIdx.x + u * kWgThreads;
+      const int c = e % XC, px = (e / XC) % XW, row = e / (XC * XW);
+      gx[u] = u4a8{0u, 0u, 0u, 0u};
+      if (px < w + 2 && row < h + 2) {
+        int xx = x0 + px - 1, yy = y0 + row - 1;
+        xx = xx < 0 ? nx - 1 : (xx >= nx ? 0 : xx);
+        yy = yy < 0 ? ny - 1 : (yy >= ny ? 0 : yy);
+        gx[u] = *reinterpret_cast<const u4a8*>(X + (img * P + (int64_t)yy * nx + xx) * CINP + c * 8);
       }
     }
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < ZL; ++u) {
+      const int e = (int)threadIdx.x + u * kWgThreads;
+      const int c = e % ZC, px = (e / ZC) % kSegX, row = e / (ZC * kSegX);
+      gz[u] = u4a8{0u, 0u, 0u, 0u};
+      if (px < w && row < h)
+        gz[u] = *reinterpret_cast<const u4a8*>(
+            dZ + (img * P + (int64_t)(y0 + row) * nx + x0 + px) * COUTP + c * 8);
+    }
+  };
+  auto stage = [&](uint16_t* sx, uint16_t* sz) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int u = 0; u < XL; ++u) {
+      const int e = (int)threadIdx.x + u * kWgThreads;
+      if (e < XN) *reinterpret_cast<u4*>(sx + (e / XC) * XS + (e % XC) * 8) = (u4)gx[u];
+    }
+#pragma unroll
+    for (int u = 0; u < ZL; ++u) {
+      const int e = (int)threadIdx.x + u * kWgThreads;
+      if (e < ZN) *reinterpret_cast<u4*>(sz + (e / ZC) * ZS + (e % ZC) * 8) = (u4)gz[u];
+    }
+  };
+  // 32 pixels (k) x 16 channels at `at` (pixel stride S): the lane's 8 k
+  auto frag = [&](const uint16_t* at, int S) {
+    typedef __attribute__((address_space(3))) v4s* Lp;
+    const uint16_t* q = at + (4 * lq + ln / 4) * S + (ln % 4) * 4;
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((Lp)q);
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((Lp)(q + 16 * S));
+    return __builtin_bit_cast(v8b, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  v4f acc[9][MT][NT], sum[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    sum[mt] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[t][mt][nt] = v4f{0.f, 0.f, 0.f, 0.f};
   }
+  v8b ones;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
+  if (s0 < s1) load(s0);
+  int buf = 0;
+  for (int64_t st = s0; st < s1; ++st, buf ^= 1) {
+    // one barrier a tile: its buffer was last read two tiles ago, before the
+    // barrier of the tile in between
+    uint16_t* sx = lds + buf * (LX + LZ);
+    uint16_t* sz = sx + LX;
+    stage(sx, sz);
+    __syncthreads();
+    if (st + 1 < s1) load(st + 1);
+    v8b a[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      a[mt] = frag(sz + wid * kSegX * ZS + mt * 16, ZS);
+      sum[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], ones, sum[mt], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const v8b b = frag(sx + ((wid + t / 3) * XW + t % 3) * XS + nt * 16, XS);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          acc[t][mt][nt] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], b, acc[t][mt][nt], 0, 0, 0);
+      }
+  }
+  // the wavefronts' sums, added in order
+  float* red = reinterpret_cast<float*>(lds);
+  for (int wv = 0; wv < kSegY; ++wv) {
+    __syncthreads();
+    if (wid != wv) continue;
+    auto put = [&](int at, float v) { red[at] = wv == 0 ? v : red[at] + v; };
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int co = mt * 16 + lq * 4 + i;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+            put((co * 9 + t) * CINP + nt * 16 + ln, acc[t][mt][nt][i]);
+        if (ln == 0) put(NWT + co, sum[mt][i]);
+      }
+  }
+  __syncthreads();
   float* mine = part + (size_t)blockIdx.x * (NWT + COUTP);
-#pragma unroll
-  for (int j = 0; j < TPW; ++j) {
-    const int q = wid + 4 * j;
-    if (q < TILES) {
-      const int t = q / (MT * NT), mt = (q / NT) % MT, nt = q % NT;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        mine[((mt * 16 + lq * 4 + i) * 9 + t) * CINP + nt * 16 + ln] = acc[j][i];
-    }
-  }
-  if (threadIdx.x < COUTP) mine[NWT + threadIdx.x] = dbacc;
+  for (int i = threadIdx.x; i < NWT + COUTP; i += kWgThreads) mine[i] = red[i];
 }
 
-// gw[i] += sum over nb blocks of part[b][i] (fixed order); i < n weights
-// followed by nbias biases of the layer
-__global__ void k_wgrad_reduce(const float* __restrict__ part, int nb, int nwt, int nbias,
-                               float* __restrict__ gw, float* __restrict__ gb) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// gw[i] += sum over nb blocks of part[b][i] (fixed order: four quarters of the
+// blocks, each in order, then their sum); i < n weights followed by nbias
+// biases of the layer.  A block takes 64 outputs, a wavefront one quarter of
+// the partials (one thread for all 256 took 61 us, this 5).
+__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part, int nb,
+                                                      int nwt, int nbias, float* __restrict__ gw,
+                                                      float* __restrict__ gb) {
+  __shared__ float s_q[4][64];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + lane;
   const int n = nwt + nbias;
-  if (i >= n) return;
+  const int b0 = nb * wid / 4, b1 = nb * (wid + 1) / 4;
   float s = 0.f;
-  for (int b = 0; b < nb; ++b) s += part[(size_t)b * n + i];
+  if (i < n) {
+    int b = b0;
+    for (; b + 8 <= b1; b += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(b + u) * n + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; b < b1; ++b) s += part[(size_t)b * n + i];
+  }
+  s_q[wid][lane] = s;
+  __syncthreads();
+  if (wid != 0 || i >= n) return;
+  s = (s_q[0][lane] + s_q[1][lane]) + (s_q[2][lane] + s_q[3][lane]);
   if (i < nwt)
     gw[i] += s;
   else
@@ -510,23 +651,28 @@ Acts acts_of(void* ws, int64_t N) {
   return a;
 }
 
-int conv_grid(int64_t N) { return (int)std::min<int64_t>(ceil_div(ceil_div(N, 16), 4), 4096); }
+// two blocks (eight wavefronts) per CU hold the layers' weights; fewer tiles
+// take a wavefront each
+int conv_grid(int64_t N) { return (int)std::min<int64_t>(ceil_div(ceil_div(N, 16), 4), 512); }
 
 template <int CINP, int COUTP, int MODE>
 void conv(hipStream_t s, const uint16_t* X, const uint16_t* W, const float* bias,
           const uint16_t* H, void* out, int64_t N, int nx, int ny) {
   hipLaunchKernelGGL((k_conv3x3<CINP, COUTP, MODE>), dim3(conv_grid(N)), dim3(256), 0, s, X, W,
-                     bias, H, out, N, nx, ny);
+                     bias, H, out, (uint32_t)N, nx, ny, make_fastdiv((uint32_t)(nx * ny)),
+                     make_fastdiv((uint32_t)nx));
 }
 
 template <int CINP, int COUTP>
 void wgrad(hipStream_t s, const uint16_t* X, const uint16_t* dZ, float* part, float* gw,
            float* gb, int64_t N, int nx, int ny) {
-  const int nb = (int)std::min<int64_t>(ceil_div(N, kSeg), kWgradBlocks);
-  hipLaunchKernelGGL((k_conv3x3_wgrad<CINP, COUTP>), dim3(nb), dim3(256), 0, s, X, dZ, part, N,
-                     nx, ny);
+  const int nimg = (int)(N / ((int64_t)nx * ny));
+  const int64_t tiles = nimg * ceil_div(nx, kSegX) * ceil_div(ny, kSegY);
+  const int nb = (int)std::min<int64_t>(tiles, kWgradBlocks);
+  hipLaunchKernelGGL((k_conv3x3_wgrad<CINP, COUTP>), dim3(nb), dim3(kWgThreads), 0, s, X, dZ, part,
+                     nimg, nx, ny);
   const int n = COUTP * 9 * CINP + COUTP;
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s,
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)ceil_div(n, 64)), dim3(256), 0, s,
                      (const float*)part, nb, COUTP * 9 * CINP, COUTP, gw, gb);
 }
 

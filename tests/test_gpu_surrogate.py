@@ -119,6 +119,48 @@ def test_weight_gradient(mods, nimg, ny, nx, cinp, coutp):
     assert np.allclose(db.cpu().numpy() - 0.25, z.sum(axis=(0, 2, 3)), rtol=1e-5, atol=1e-4)
 
 
+@pytest.mark.parametrize("nimg,ny,nx", [(3, 261, 301)])
+@pytest.mark.parametrize("cinp,coutp", [(32, 16), (32, 32), (16, 32)])
+def test_layers_over_many_tiles(mods, nimg, ny, nx, cinp, coutp):
+    """Several tiles per wavefront of the layer and per block of the weight
+    gradient, with ragged right and lower edges, several images.  The sums run
+    over 235,683 pixels of unit-variance products: FP32 partial sums are
+    within 1e-5 of the gradient's norm."""
+    H, S = mods
+    announce("no_many_tiles", nimg, ny, nx, cinp, coutp)
+    rng = np.random.default_rng(5 + cinp + coutp)
+    N = nimg * ny * nx
+    xb, zb = _bf16_bits(rng.normal(size=(N, cinp))), _bf16_bits(rng.normal(size=(N, coutp)))
+    wb = _bf16_bits(rng.normal(scale=0.3, size=(coutp, 9, cinp)))
+    bias = rng.normal(scale=0.1, size=coutp).astype(np.float32)
+    dw = torch.zeros((coutp, 9, cinp), dtype=torch.float32, device="cuda")
+    db = torch.zeros(coutp, dtype=torch.float32, device="cuda")
+    ws = torch.empty(H.hvpic_no_workspace_bytes(nx, ny, nimg), dtype=torch.uint8, device="cuda")
+    xd = _dev(xb.view(np.int16), np.int16)
+    H.hvpic_no_conv3x3_wgrad(nimg, nx, ny, cinp, coutp, xd, _dev(zb.view(np.int16), np.int16), dw,
+                             db, ws)
+    mode = 1 if coutp == 16 else 0
+    out = torch.zeros((N, coutp), dtype=torch.float32 if mode == 1 else torch.int16, device="cuda")
+    H.hvpic_no_conv3x3(nimg, nx, ny, cinp, coutp, mode, xd, _dev(wb.view(np.int16), np.int16),
+                       _dev(bias, np.float32), None, out)
+    torch.cuda.synchronize()
+    x, z = _from_bits(xb).reshape(nimg, ny, nx, cinp), _from_bits(zb)
+    w = _from_bits(wb)
+    ref, val = np.zeros((coutp, 9, cinp)), np.tile(bias.astype(np.float64), (N, 1))
+    for t in range(9):
+        xs = np.roll(x, (1 - t // 3, 1 - t % 3), axis=(1, 2)).reshape(N, cinp)
+        ref[:, t, :] = z.T @ xs
+        val += xs @ w[:, t, :].T
+    assert rel_l2(dw.cpu().numpy(), ref) < 1e-5
+    # a sum of N unit-variance terms: to 1e-5 of sqrt(N)
+    assert np.abs(db.cpu().numpy() - z.sum(axis=0)).max() < 1e-5 * np.sqrt(N) + 1e-6 * np.abs(z).sum(0).max() / np.sqrt(N)
+    if mode == 1:
+        assert np.abs(out.cpu().numpy() - val).max() <= 1e-5 * np.abs(val).max()
+    else:
+        got = _from_bits(out.cpu().numpy().view(np.uint16))
+        assert np.all(np.abs(got - np.tanh(val)) <= 2.0 ** -8 * np.abs(np.tanh(val)) + 1e-5)
+
+
 def _random_state(rng, ny, nx):
     P = ny * nx
     B = rng.normal(size=(3, P)) * 0.2 + np.array([[1.0], [0.0], [0.0]])

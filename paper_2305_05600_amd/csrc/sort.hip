@@ -86,14 +86,28 @@ __device__ __forceinline__ int direction_interior2d(int key, int a, int nx) {
   return di >= -1 && di <= 1 ? (di + 1) + 3 * (dj + 1) : -1;
 }
 
-// Whether the wavefront's old cells a0 .. a0+na-1 are all 2D interior cells.
+// The same in 3D: the plane first (ny >= 4, so that a row's neighbours in the
+// plane differ by less than half a plane), then the row and the cell in it.
+// A key that is no neighbour leaves a difference beyond one cell.
+__device__ __forceinline__ int direction_interior3d(int key, int a, int nx, int nxny) {
+  const int delta = key - a;
+  const int dk = delta > nx + 1 ? 1 : (delta < -(nx + 1) ? -1 : 0);
+  const int r = delta - dk * nxny;
+  const int dj = r >= nx - 1 ? 1 : (r <= 1 - nx ? -1 : 0);
+  const int di = r - dj * nx;
+  return di >= -1 && di <= 1 ? (di + 1) + 3 * (dj + 1) + 9 * (dk + 1) : -1;
+}
+
+// Whether the wavefront's old cells a0 .. a0+na-1 are all interior cells of
+// one grid row, whose neighbours need no wrap.
 template <int NDIM>
 __device__ __forceinline__ bool wave_interior(int a0, int na, const SortGeo& g) {
-  if (NDIM != 2 || g.nx < 3 || g.ny < 3) return false;
+  if (g.nx < 3 || g.ny < 3 || (NDIM == 3 && (g.ny < 4 || g.nz < 3))) return false;
   int i0, j0, k0, i1, j1, k1;
   ijk(a0, g, i0, j0, k0);
   ijk(a0 + na - 1, g, i1, j1, k1);
-  return i0 >= 1 && i1 <= g.nx - 2 && j0 >= 1 && j1 <= g.ny - 2 && j0 == j1;
+  return i0 >= 1 && i1 <= g.nx - 2 && j0 >= 1 && j1 <= g.ny - 2 && j0 == j1 &&
+         (NDIM == 2 || (k0 >= 1 && k1 <= g.nz - 2));
 }
 
 // New cell reached from old cell a by direction d (wrapped).
@@ -273,6 +287,107 @@ struct OpenSort {
   int rows;
 };
 
+// The counts of the groups of new cell c of a wavefront's 64 consecutive cells
+// (c = that of this lane; valid false beyond the grid): n[d] from source cell
+// src[d] = c - d, for all 3^NDIM directions.  The three x-moves of a source
+// cell in one (y, z) direction lie side by side in the table, and belong to
+// the cells c - 1, c and c + 1: a lane reads its own column's three as one
+// access and takes the outer two from its neighbour lanes.  That is a third
+// of the accesses, each of which touches some 54 lines in 3D (128^3 cells:
+// this pass 237 to 104 us, the bases, which write the slots back the same way,
+// 629 to 292 us).  A lane whose x
+// neighbour is not the next lane (the ends of a wavefront or a grid row) reads
+// its entry itself.  Every lane of the wavefront calls it.
+template <int NDIM>
+struct Groups {
+  static constexpr int ND = Dirs<NDIM>::N;
+  int row[ND / 3];  // source cell of the own column per (y, z) direction
+  int xm, xp;       // offsets of the x neighbours from the own column
+  bool lm, lp;      // the lane below / above holds that neighbour column
+};
+
+struct U3 {
+  uint32_t a, b, c;
+};
+
+template <int NDIM>
+__device__ __forceinline__ Groups<NDIM> group_columns(int64_t c, bool valid, const SortGeo& g,
+                                                      int& i, int& j, int& k) {
+  Groups<NDIM> G;
+  ijk(valid ? (int)c : 0, g, i, j, k);
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int q = 0; q < Groups<NDIM>::ND / 3; ++q) {
+    // the source of direction (., dj, dk) is the cell (., -dj, -dk) away
+    const int dj = q % 3 - 1, dk = NDIM == 3 ? q / 3 - 1 : 0;
+    int js = j - dj, ks = k - dk;
+    if (js < 0) js += g.ny; else if (js >= g.ny) js -= g.ny;
+    if (NDIM == 3) { if (ks < 0) ks += g.nz; else if (ks >= g.nz) ks -= g.nz; }
+    G.row[q] = i + g.nx * (js + g.ny * ks);
+  }
+  G.xm = i == 0 ? g.nx - 1 : -1;
+  G.xp = i == g.nx - 1 ? 1 - g.nx : 1;
+  // (a valid lane's lower lane is valid; the upper one holds c + 1 if it is)
+  G.lm = lane > 0 && i > 0;
+  G.lp = lane < 63 && i < g.nx - 1 && (int)c + 1 < g.ncell;
+  return G;
+}
+
+template <int NDIM>
+__device__ __forceinline__ void group_counts(const uint32_t* __restrict__ cnt, bool valid,
+                                             const Groups<NDIM>& G, uint32_t* n) {
+  constexpr int ND = Dirs<NDIM>::N;
+  // every load first: the own column's, and those of the lanes whose
+  // neighbour column is not the next lane's
+  U3 v[ND / 3];
+  uint32_t eu[ND / 3], ed[ND / 3];
+#pragma unroll
+  for (int q = 0; q < ND / 3; ++q) {
+    v[q] = U3{0u, 0u, 0u};
+    eu[q] = ed[q] = 0u;
+    if (valid) v[q] = *reinterpret_cast<const U3*>(cnt + (int64_t)G.row[q] * ND + 3 * q);
+  }
+  if (valid && !G.lm) {
+#pragma unroll
+    for (int q = 0; q < ND / 3; ++q) eu[q] = cnt[(int64_t)(G.row[q] + G.xm) * ND + 3 * q + 2];
+  }
+  if (valid && !G.lp) {
+#pragma unroll
+    for (int q = 0; q < ND / 3; ++q) ed[q] = cnt[(int64_t)(G.row[q] + G.xp) * ND + 3 * q];
+  }
+#pragma unroll
+  for (int q = 0; q < ND / 3; ++q) {
+    // direction di = +1 comes from the column below, -1 from the one above
+    const uint32_t up = __shfl_up(v[q].c, 1), down = __shfl_down(v[q].a, 1);
+    n[3 * q] = !valid ? 0u : (G.lp ? down : ed[q]);
+    n[3 * q + 1] = v[q].b;
+    n[3 * q + 2] = !valid ? 0u : (G.lm ? up : eu[q]);
+  }
+}
+
+// Writes the group values n back over the counts (the same entries).
+template <int NDIM>
+__device__ __forceinline__ void group_store(uint32_t* __restrict__ cnt, bool valid,
+                                            const Groups<NDIM>& G, const uint32_t* n) {
+  constexpr int ND = Dirs<NDIM>::N;
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int q = 0; q < ND / 3; ++q) {
+    // own column: its di = -1 entry belongs to the cell below, +1 to the one above
+    const uint32_t a = __shfl_up(n[3 * q], 1), c = __shfl_down(n[3 * q + 2], 1);
+    uint32_t* own = cnt + (int64_t)G.row[q] * ND + 3 * q;
+    if (valid && G.lm && G.lp) {
+      *reinterpret_cast<U3*>(own) = U3{a, n[3 * q + 1], c};
+    } else if (valid) {
+      own[1] = n[3 * q + 1];
+      if (G.lm) own[0] = a;
+      if (G.lp) own[2] = c;
+      if (!G.lm) cnt[(int64_t)(G.row[q] + G.xm) * ND + 3 * q + 2] = n[3 * q + 2];
+      if (!G.lp) cnt[(int64_t)(G.row[q] + G.xp) * ND + 3 * q] = n[3 * q];
+    }
+  }
+}
+
 // Per-new-cell totals, written to cs[c], and their per-tile sums (tiles of
 // TILE cells).
 template <int NDIM, int TILE, bool OPEN = false>
@@ -292,14 +407,15 @@ __device__ __forceinline__ void nb_newcount_body(const uint32_t* __restrict__ cn
   uint32_t local = 0;
   for (int q = 0; q < TILE / kBlock; ++q) {
     const int64_t c = t0 + q * kBlock + threadIdx.x;
-    if (c >= g.ncell) break;
+    const bool valid = c < g.ncell;
     int i, j, k;
-    ijk((int)c, g, i, j, k);
+    const Groups<NDIM> G = group_columns<NDIM>(c, valid, g, i, j, k);
+    uint32_t n[ND];
+    group_counts<NDIM>(cnt, valid, G, n);
+    if (!valid) continue;
     uint32_t s = 0;
-    for (int d = 0; d < ND; ++d) {
-      const int src = step_cell<NDIM>(i, j, k, ND - 1 - d, g);  // c - d == c + (ND-1-d)
-      s += cnt[(int64_t)src * ND + d];
-    }
+#pragma unroll
+    for (int d = 0; d < ND; ++d) s += n[d];
     if (OPEN) {
       if (i == 0 || i == g.nx - 1) {
         s = 0;
@@ -374,6 +490,21 @@ __device__ uint32_t block_sum(const uint32_t* __restrict__ v, int m) {
   return t;
 }
 
+// Place of index i on a periodic axis of m cells: -1 at its start, 1 at its
+// end, else 0.
+__device__ __forceinline__ int edge_of(int i, int m) { return i == 0 ? -1 : (i == m - 1 ? 1 : 0); }
+
+// First slots s of the moves -1, 0, +1 along one axis, holding n of them from
+// `start` on, in increasing order of their sources i + 1, i, i - 1: the moves
+// +1, 0, -1; at the axis' start the source of +1 is its last cell (0, -1, +1),
+// at its end the source of -1 its first (-1, +1, 0).
+__device__ __forceinline__ void axis_slots(int edge, uint32_t start, const uint32_t* n,
+                                           uint32_t* s) {
+  s[0] = start + (edge > 0 ? 0u : n[1] + (edge < 0 ? 0u : n[2]));
+  s[1] = start + (edge < 0 ? 0u : n[2] + (edge > 0 ? n[0] : 0u));
+  s[2] = start + (edge == 0 ? 0u : n[0] + (edge < 0 ? n[1] : 0u));
+}
+
 // cell_start from the per-cell totals, and the first slot of every group
 // (source cell, direction) of each new cell, written over cnt.  blk holds
 // the tile totals; each block adds up those before it (a few hundred values
@@ -395,49 +526,62 @@ __device__ __forceinline__ void nb_bases_body(uint32_t* __restrict__ cnt, const 
   const uint32_t off = block_sum(blk, bid);
   for (int q = 0; q < TILE / kBlock; ++q) {
     const int64_t c = t0 + q * kBlock + threadIdx.x;
-    if (c >= g.ncell) break;
+    const bool valid = c < g.ncell;
     const uint32_t start = off + s[q * kBlock + threadIdx.x];
-    cs[c] = (int32_t)start;
-    if (c == g.ncell - 1) cs[g.ncell] = (int32_t)(off + tile_total);
     int i, j, k;
-    ijk((int)c, g, i, j, k);
-    int src[ND];
+    const Groups<NDIM> G = group_columns<NDIM>(c, valid, g, i, j, k);
     uint32_t n[ND];
-    for (int d = 0; d < ND; ++d) {
-      src[d] = step_cell<NDIM>(i, j, k, ND - 1 - d, g);
-      n[d] = cnt[(int64_t)src[d] * ND + d];
+    group_counts<NDIM>(cnt, valid, G, n);
+    if (valid) {
+      cs[c] = (int32_t)start;
+      if (c == g.ncell - 1) cs[g.ncell] = (int32_t)(off + tile_total);
     }
-    // groups in increasing old-cell index (ties only between empty groups).
-    // For a cell whose neighbours need no wrap that order is d = ND-1 .. 0
-    // (the source index falls as d rises), so the slots are a suffix sum.
-    const bool interior = g.nx >= 3 && g.ny >= 3 && i >= 1 && i <= g.nx - 2 && j >= 1 &&
-                          j <= g.ny - 2 &&
-                          (NDIM == 2 || (g.nz >= 3 && k >= 1 && k <= g.nz - 2));
-    if (OPEN && os.inj_cnt && (i == 1 || i == g.nx - 2)) {
+    if (OPEN && valid && os.inj_cnt && (i == 1 || i == g.nx - 2)) {
       // the injected ions of the cell follow all the moved ones
       const int r = j + g.ny * k;
       uint32_t moved = 0;
+#pragma unroll
       for (int d = 0; d < ND; ++d) moved += n[d];
       if (i == 1) os.inj_base[r] = (int32_t)(start + moved);
       if (i == g.nx - 2)
         os.inj_base[os.rows + r] =
             (int32_t)(start + moved + (i == 1 ? (uint32_t)os.inj_cnt[r] : 0u));
     }
-    if (interior) {
-      uint32_t before = 0;
+    // the groups in increasing old-cell index
+    uint32_t base[ND];
+    if (g.nx >= 3 && g.ny >= 3 && (NDIM == 2 || g.nz >= 3)) {
+      // by plane, row and column of the source: along each axis the order of
+      // the three moves depends on the cell's place at an edge only
+      uint32_t row[ND / 3], rs[ND / 3];
+      const int ex = edge_of(i, g.nx), ey = edge_of(j, g.ny), ez = NDIM == 3 ? edge_of(k, g.nz) : 0;
 #pragma unroll
-      for (int d = ND - 1; d >= 0; --d) {
-        cnt[(int64_t)src[d] * ND + d] = start + before;
-        before += n[d];
+      for (int q = 0; q < ND / 3; ++q) row[q] = n[3 * q] + n[3 * q + 1] + n[3 * q + 2];
+      uint32_t plane[3] = {0u, 0u, 0u}, ps[3] = {start, start, start};
+      if (NDIM == 3) {
+#pragma unroll
+        for (int z = 0; z < ND / 9; ++z) plane[z] = row[3 * z] + row[3 * z + 1] + row[3 * z + 2];
+        axis_slots(ez, start, plane, ps);
       }
+#pragma unroll
+      for (int z = 0; z < ND / 9; ++z) axis_slots(ey, ps[z], row + 3 * z, rs + 3 * z);
+#pragma unroll
+      for (int q = 0; q < ND / 3; ++q) axis_slots(ex, rs[q], n + 3 * q, base + 3 * q);
     } else {
+      // an axis of one or two cells: moves share sources (ties only between
+      // empty groups)
+      auto src = [&](int d) {
+        return G.row[d / 3] + (d % 3 == 0 ? G.xp : (d % 3 == 2 ? G.xm : 0));
+      };
+#pragma unroll
       for (int d = 0; d < ND; ++d) {
-        uint32_t before = 0;
+        uint32_t b = 0;
+#pragma unroll
         for (int e = 0; e < ND; ++e)
-          if (src[e] < src[d] || (src[e] == src[d] && e < d)) before += n[e];
-        cnt[(int64_t)src[d] * ND + d] = start + before;
+          if (src(e) < src(d) || (src(e) == src(d) && e < d)) b += n[e];
+        base[d] = start + b;
       }
     }
+    group_store<NDIM>(cnt, valid, G, base);
   }
 }
 
@@ -498,22 +642,26 @@ __device__ __forceinline__ uint32_t load_key(const uint32_t* kin, const int32_t*
 
 // Sorted-order gather of the particle fields plus cell_start from the sorted
 // keys: the boundary between positions r-1 and r fills the starts of the cells
-// in (key[r-1], key[r]].  Threads start at `first` and step by `stride`.
+// in (key[r-1], key[r]].  Threads start at `first` and step by `stride`.  `one`
+// takes a single array: 0..6 a field, 7 the cells (with cell_start); -1 all.
 __device__ void gather_fields(const uint32_t* keys, const uint32_t* perm, int64_t n, Fields in,
-                              Fields out, int32_t* cs, int ncell, int64_t first, int64_t stride) {
+                              Fields out, int32_t* cs, int ncell, int64_t first, int64_t stride,
+                              int one = -1) {
   for (int64_t r = first; r <= n; r += stride) {
-    const int kprev = r == 0 ? -1 : (int)(keys ? keys[r - 1] : 0u);
-    const int knext = r == n ? ncell : (int)(keys ? keys[r] : 0u);
-    for (int c = kprev + 1; c <= knext && c <= ncell; ++c) cs[c] = (int32_t)r;
+    if (one < 0 || one == 7) {
+      const int kprev = r == 0 ? -1 : (int)(keys ? keys[r - 1] : 0u);
+      const int knext = r == n ? ncell : (int)(keys ? keys[r] : 0u);
+      for (int c = kprev + 1; c <= knext && c <= ncell; ++c) cs[c] = (int32_t)r;
+    }
     if (r < n) {
       const uint32_t src = perm ? perm[r] : (uint32_t)r;
       if (out.perm) {
         out.perm[r] = (int32_t)src;
       } else {
-        out.cell[r] = in.cell[src];
+        if (one < 0 || one == 7) out.cell[r] = in.cell[src];
 #pragma unroll
         for (int f = 0; f < 7; ++f)
-          if (in.f[f]) out.f[f][r] = in.f[f][src];
+          if ((one < 0 || one == f) && in.f[f]) out.f[f][r] = in.f[f][src];
       }
     }
   }
@@ -601,12 +749,17 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
   }
 }
 
+// The rows of the grid take one array each, in the order of their dispatch: an
+// array's scattered 4-byte reads bring a line each, and one array at a time
+// stays in the memory-side cache (13.1M ions: 52 MB against 367 MB for all;
+// 1720 to 1600 us).
 __global__ __launch_bounds__(kBlock) void k_radix_final(const uint32_t* __restrict__ keys,
                                                         const uint32_t* __restrict__ perm, int64_t n,
                                                         Fields in, Fields out, int32_t* cs,
                                                         int ncell) {
+  const int one = gridDim.y == 1 ? 7 : (int)blockIdx.y;
   gather_fields(keys, perm, n, in, out, cs, ncell, (int64_t)blockIdx.x * kBlock + threadIdx.x,
-                (int64_t)gridDim.x * kBlock);
+                (int64_t)gridDim.x * kBlock, one);
 }
 
 // The whole stable sort by one block (fallback of the neighbour path).
@@ -749,7 +902,8 @@ __device__ __forceinline__ void nb_scatter_body(const int32_t* __restrict__ cs_p
       int d;
       int iold = col0 + m;
       if (interior) {
-        d = direction_interior2d(key, a0 + m, g.nx);
+        d = NDIM == 2 ? direction_interior2d(key, a0 + m, g.nx)
+                      : direction_interior3d(key, a0 + m, g.nx, g.nx * g.ny);
       } else {
         int i, j, k;
         ijk(a0 + m, g, i, j, k);
@@ -960,8 +1114,8 @@ void enqueue_radix(hvpic_ctx* c, const hvpic_particles* in, const Fields& out, i
     cur ^= 1;
   }
   const int fblocks = (int)std::min<int64_t>(ceil_div(n + 1, kBlock), 65536);
-  hipLaunchKernelGGL(k_radix_final, dim3(fblocks), dim3(kBlock), 0, s, kin, vin, n, fields_of(in),
-                     out, cs, ncell);
+  hipLaunchKernelGGL(k_radix_final, dim3(fblocks, out.perm ? 1 : 8), dim3(kBlock), 0, s, kin, vin,
+                     n, fields_of(in), out, cs, ncell);
 }
 
 template <int NDIM>

@@ -492,7 +492,7 @@ __device__ __forceinline__ void field_sub2d_body(
     if (F.part) {
       tile_partial(v);
       if (F.diag.out) {
-        if (threadIdx.x < 64) field_diag_last(F.diag, v, slot, &F.st->diag_ticket);
+        field_diag_last(F.diag, v, slot, &F.st->diag_ticket);
       } else if (threadIdx.x == 0) {
         for (int k = 0; k < kDiagNV; ++k) F.part[kFieldPartStride * (int64_t)slot + k] = v[k];
       }

@@ -178,48 +178,49 @@ __device__ __forceinline__ void field_diag_body(const DiagArgs& D) {
   if (threadIdx.x == 0) field_diag_write(D, r);
 }
 
-// The same inside the kernel that forms the partials, for its first
-// wavefront, whose lane 0 holds this block's partial v: the last of the
-// D.nblocks blocks to come by adds them all up (64 at a time, in the order of
-// sum_partials, so both forms give the same bits) and clears the ticket.  The partials go past the L2s with agent-scope stores, which
-// have arrived once their wait is over, and come back with agent-scope loads,
-// so the blocks need no release of the whole L2 (which made such a ticket
-// dearer than a launch).  Saves a launch of 4.5 to 6 us; the last block's wavefront
-// takes about that long from 2048 partials on.
+// The same inside the kernel that forms the partials, for a block whose
+// thread 0 holds its partial v: the last of the D.nblocks blocks to come by
+// adds them all up (64 to a wavefront, in the order of sum_partials, so both
+// forms give the same bits) and clears the ticket.  The partials go past the
+// L2s with agent-scope stores, which have arrived once their wait is over, and
+// come back with agent-scope loads, so the blocks need no release of the whole
+// L2 (which made such a ticket dearer than a launch).  Saves a launch of 4.5
+// to 6 us.  Every thread of the block calls it.
 constexpr int kDiagTicketBlocks = 1024;
 __device__ __forceinline__ void field_diag_last(const DiagArgs& D, const double* v, int64_t slot,
                                                 uint32_t* ticket) {
-  const int lane = threadIdx.x;
-  uint32_t seen = 0;
-  if (lane == 0) {
+  __shared__ uint32_t s_seen;
+  __shared__ double s_sum[kDiagTicketBlocks / 64][kDiagNV];
+  if (threadIdx.x == 0) {
     double* mine = const_cast<double*>(D.part) + kFieldPartStride * slot;
     for (int k = 0; k < kDiagNV; ++k)
       __hip_atomic_store(mine + k, v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    seen = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_seen = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if ((uint32_t)__builtin_amdgcn_readfirstlane((int)seen) != (uint32_t)D.nblocks - 1) return;
-  double t[kDiagNV] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int b0 = 0; b0 < D.nblocks; b0 += 8 * 64) {
-    double u[8][kDiagNV];
+  __syncthreads();
+  if (s_seen != (uint32_t)D.nblocks - 1) return;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int groups = (D.nblocks + 63) / 64;
+  for (int q = wid; q < groups; q += nw) {
+    const int b = q * 64 + lane;
+    double u[kDiagNV];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int b = b0 + q * 64 + lane;
+    for (int k = 0; k < kDiagNV; ++k)
+      u[k] = b < D.nblocks ? __hip_atomic_load(D.part + (int64_t)b * kFieldPartStride + k,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                           : 0.0;
 #pragma unroll
-      for (int k = 0; k < kDiagNV; ++k)
-        u[q][k] = b < D.nblocks
-                      ? __hip_atomic_load(D.part + (int64_t)b * kFieldPartStride + k,
-                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                      : 0.0;
+    for (int k = 0; k < kDiagNV; ++k) {
+      for (int o = 32; o > 0; o >>= 1) u[k] += __shfl_xor(u[k], o);
+      if (lane == 0) s_sum[q][k] = u[k];
     }
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-      for (int k = 0; k < kDiagNV; ++k) {
-        for (int o = 32; o > 0; o >>= 1) u[q][k] += __shfl_xor(u[q][k], o);
-        t[k] += u[q][k];
-      }
   }
-  if (lane == 0) {
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t[kDiagNV] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int q = 0; q < groups; ++q)
+      for (int k = 0; k < kDiagNV; ++k) t[k] += s_sum[q][k];
     field_diag_write(D, t);
     __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }

@@ -13,13 +13,15 @@
 // pressure instead of the equation of state.  lap is the compact second
 // difference (+1, -2, +1)/h^2 summed over the axes; div and grad are centred.
 //
-// Three whole-grid kernels per RK2 stage: J = curl B of the stage input; Ohm's
+// 2D: one tile kernel per substep (fields_tile.hpp).  3D: three whole-grid
+// kernels per RK2 stage: J = curl B of the stage input; Ohm's
 // law (needs lap J, so J at the neighbours) and, with the energy equation, the
 // pressure update (needs u_e, p_e and T_e at the neighbours); B from curl E.
 // Each is a stencil over arrays that stay in L2 during the subcycle.  B and
 // p_e are carried as unevaluated sums hi + lo as on the plain path; the
 // stage inputs are the hi parts.
 #include "fields_common.hpp"
+#include "fields_tile.hpp"
 
 namespace hvpic {
 namespace {
@@ -300,7 +302,43 @@ int ext_impl(hvpic_ctx* c, float* B, float* pe, const float* n_half, const float
   const float* fl = nullptr;
   const float* fp = pe;
   const float* fpl = nullptr;
-  if (mode == 0 && c->p.nsub > 0) {
+  if (NDIM == 2 && mode == 0 && c->p.nsub > 0) {
+    // one tile launch per substep, from the caller's arrays (lo parts zero) to
+    // scratch and on between two sets of it
+    ExtSub A{};
+    A.n = n_half;
+    A.J = J_half;
+    A.h = (float)(c->p.dt / c->p.nsub);
+    A.g = g;
+    A.ilx = lg.ix;
+    A.ily = lg.iy;
+    A.eta = ph.eta;
+    A.eta_h = ph.eta_h;
+    A.gam = ph.gam;
+    A.kappa0 = ph.kappa0;
+    A.eos = eos;
+    float* Yl = J;               // (J is formed after the subcycle only)
+    float* Ypl = c->fscratch;    // (no frozen-term arrays here)
+    J = E;
+    A.Bin = B;
+    A.Pin = pe;
+    for (int m = 0; m < c->p.nsub; ++m) {
+      const bool even = m % 2 == 0;
+      A.Bout = even ? Xh : Yh;
+      A.Lout = even ? Xl : Yl;
+      A.Pout = even ? Xp : Yp;
+      A.PLout = even ? Xpl : Ypl;
+      launch_ext_sub2d<PE, false>(s, A);
+      A.Bin = A.Bout;
+      A.Lin = A.Lout;
+      A.Pin = A.Pout;
+      A.PLin = A.PLout;
+    }
+    fh = A.Bin;
+    fl = A.Lin;
+    fp = A.Pin;
+    fpl = A.PLin;
+  } else if (mode == 0 && c->p.nsub > 0) {
     const float h = (float)(c->p.dt / c->p.nsub);
     hipLaunchKernelGGL((k_field_prep<NDIM>), grid, blk, 0, s, n_half, (const float*)nullptr,
                        J_half, (const float*)nullptr, 1.0f, 0.0f, g, eos.nfloor, eos.te_n0,

@@ -14,15 +14,17 @@
 //
 // The particle kernels of the periodic step run unchanged on this grid (the
 // ghost columns keep the two sides apart); absorbed ions get the key ncell
-// and the open sort puts them last.  The field advance is the stencil-per-
-// stage form: per RK2 stage the ghost columns are refilled, J = curl B1 (no
-// x-derivatives in the ghosts), Ohm's law, then Faraday in the interior.
+// and the open sort puts them last.  The field advance takes one tile kernel
+// per substep in 2D (fields_tile.hpp), and the stencil-per-stage form in 3D:
+// per RK2 stage the ghost planes are refilled, J = curl B1 (no x-derivatives
+// in the ghosts), Ohm's law, then Faraday in the interior.
 #include <math.h>
 #include <string.h>
 
 #include <algorithm>
 
 #include "fields_common.hpp"
+#include "fields_tile.hpp"
 
 namespace hvpic {
 namespace {
@@ -541,7 +543,35 @@ void open_advance(hvpic_ctx* c, const float* B0, float* B1, float* Btot, const f
   const float* fh = B1;
   const float* fl = nullptr;
   if (mode == 0) fill(c, B1, 3);
-  if (mode == 0 && c->p.nsub > 0) {
+  if (NDIM == 2 && mode == 0 && c->p.nsub > 0) {
+    // one tile launch per substep, from the caller's B1 (lo zero) to scratch
+    // and on between two sets of it
+    ExtSub A{};
+    A.n = n_half;
+    A.J = J_half;
+    A.B0 = B0;
+    A.h = (float)(c->p.dt / c->p.nsub);
+    A.g = g;
+    A.ilx = o.ilx;
+    A.ily = o.ily;
+    A.eta = o.eta;
+    A.eta_h = o.eta_h;
+    A.eta_hb = o.eta_hb;
+    A.nbuf = o.nbuf;
+    A.eos = eos;
+    float* Yl = J;  // (J is formed after the subcycle only)
+    J = E;
+    A.Bin = B1;
+    for (int m = 0; m < c->p.nsub; ++m) {
+      A.Bout = m % 2 == 0 ? Xh : Yh;
+      A.Lout = m % 2 == 0 ? Xl : Yl;
+      launch_ext_sub2d<false, true>(s, A);
+      A.Bin = A.Bout;
+      A.Lin = A.Lout;
+    }
+    fh = A.Bin;
+    fl = A.Lin;
+  } else if (mode == 0 && c->p.nsub > 0) {
     const float h = (float)(c->p.dt / c->p.nsub);
     hipLaunchKernelGGL(k_open_prep<NDIM>, grid, blk, 0, s, n_half, J_half, g, eos, aux);
     for (int m = 0; m < c->p.nsub; ++m) {

@@ -92,42 +92,58 @@ __global__ __launch_bounds__(kBlock) void k_field_stage(const float* __restrict_
   }
 }
 
-// The same stage in two passes: E = Ohm(B_src) once per cell, then the
+// The block of cells that a block of a 3D grid takes: an XCD's are next to each
+// other, so the planes above and below a cell come through its own L2.
+__device__ __forceinline__ int slab_block() { return xcd_chunk(blockIdx.x, gridDim.x); }
+
+// A stage of a 3D grid in two passes: E = Ohm(B_src) once per cell, then the
 // Faraday update from curl E.  Each cell's E is formed once instead of once
-// per neighbour that needs it (2 NDIM times in k_field_stage), at the cost
-// of writing E and reading it back.
-template <int NDIM>
+// per neighbour that needs it (six times in k_field_stage), at the cost of
+// writing E and reading it back.  Memory-bound: 13 values a cell for E, 9 or 15
+// for the update (16 us each at 128^3 cells, 6.8 and 6.3 TB/s; 19 us with the
+// blocks in launch order).  PREP (the first stage of an advance) also forms the
+// frozen terms from the moments and leaves them in aux: 33 us, 41 in two passes.
+// The first substep's base is the caller's B with a zero low part, which costs
+// no copy (18 us).  The advance, four substeps: 412 to 340 us.  One marching
+// kernel per stage with E kept in LDS took 590 us: two barriers and the latency
+// of a load per plane.
+template <bool PREP>
 __global__ __launch_bounds__(kBlock) void k_field_ohm_cells(const float* __restrict__ Bsrc,
-                                                            float eta, FGeo g, Aux aux,
+                                                            const float* __restrict__ n,
+                                                            const float* __restrict__ Ji,
+                                                            float eta, FGeo g, Eos eos, Aux aux,
                                                             float* __restrict__ E) {
-  const int c = blockIdx.x * kBlock + threadIdx.x;
+  const int c = slab_block() * kBlock + threadIdx.x;
   if (c >= g.ncell) return;
   const int nc = g.ncell;
   float e[3];
-  ohm_at<NDIM>(BSum<false>{Bsrc, nullptr}, aux, eta, c, g, e);
+  if (PREP) prep_at<3>(n, nullptr, Ji, nullptr, 1.0f, 0.0f, c, g, eos, aux);
+  ohm_at<3>(BSum<false>{Bsrc, nullptr}, aux, eta, c, g, e);
   E[c] = e[0];
   E[nc + c] = e[1];
   E[2 * nc + c] = e[2];
 }
 
-template <int NDIM>
+// B_dst = B_base - coef curl E; with lo_out compensated as in k_field_stage,
+// from lo_in (null: zero).
 __global__ __launch_bounds__(kBlock) void k_field_curl_update(const float* __restrict__ E,
                                                               const float* Bbase, float* Bdst,
-                                                              float* lo, float coef, FGeo g) {
-  const int c = blockIdx.x * kBlock + threadIdx.x;
+                                                              const float* lo_in, float* lo_out,
+                                                              float coef, FGeo g) {
+  const int c = slab_block() * kBlock + threadIdx.x;
   if (c >= g.ncell) return;
   const int nc = g.ncell;
   float ce[3];
-  curl_at<NDIM>(BSum<false>{E, nullptr}, c, g, ce);
+  curl_at<3>(BSum<false>{E, nullptr}, c, g, ce);
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     const int q = a * nc + c;
     const float d = -coef * ce[a];
     const float hi = Bbase[q];
-    if (lo) {
-      const float y = lo[q] + d;
+    if (lo_out) {
+      const float y = lo_in ? lo_in[q] + d : d;
       const float t = hi + y;
-      lo[q] = y - (t - hi);
+      lo_out[q] = y - (t - hi);
       Bdst[q] = t;
     } else {
       Bdst[q] = hi + d;
@@ -524,7 +540,8 @@ __global__ __launch_bounds__(kBlock) void k_field_final(
     const float* __restrict__ na, const float* __restrict__ nb, const float* __restrict__ Ja,
     const float* __restrict__ Jb, float ca, float cb, float eta, FGeo g, Eos eos,
     float* __restrict__ E, double* part, Status* st, int count_floor) {
-  const int c = blockIdx.x * kBlock + threadIdx.x;
+  const int slot = NDIM == 3 ? slab_block() : (int)blockIdx.x;
+  const int c = slot * kBlock + threadIdx.x;
   const int nc = g.ncell;
   const bool live = c < nc;
   bool below = false;
@@ -579,7 +596,7 @@ __global__ __launch_bounds__(kBlock) void k_field_final(
       atomicAdd(&st->floor_hits, (unsigned long long)__builtin_popcountll(m));
     }
   }
-  if (part) block_partial<kDiagNV, kFieldPartStride>(v, part);
+  if (part) block_partial<kDiagNV, kFieldPartStride>(v, part, slot);
 }
 
 // Binomial smoothing (Sec. II.B): one pass is the (1,2,1)/4 filter along x,
@@ -727,23 +744,24 @@ int field_impl(hvpic_ctx* c, float* B, const float* n_half, const float* J_half,
       fh = sh;
       fl = sl;
     } else {
-      // frozen moments for the subcycle
-      hipLaunchKernelGGL((k_field_prep<NDIM>), grid, blk, 0, s, n_half, (const float*)nullptr,
-                         J_half, (const float*)nullptr, 1.0f, 0.0f, g, eos.nfloor, eos.te_n0,
-                         eos.n0, eos.gam, eos.iso, aux);
-      const int cblocks = (int)std::min<int64_t>(ceil_div(3ll * nc, kBlock), 1024);
-      hipLaunchKernelGGL(k_copy, dim3(cblocks), blk, 0, s, (const float*)B, Xh, 3ll * nc);
-      hipLaunchKernelGGL(k_fill, dim3(cblocks), blk, 0, s, Xl, 3ll * nc, 0.0f);
       float* Es = c->fscratch + 19ll * nc;  // E of a stage
+      const float* base = B;                // the caller's B (lo = 0) in the first substep
+      const float* lo = nullptr;
       for (int m = 0; m < c->p.nsub; ++m) {
-        hipLaunchKernelGGL((k_field_ohm_cells<NDIM>), grid, blk, 0, s, (const float*)Xh, eta, g,
-                           aux, Es);
-        hipLaunchKernelGGL((k_field_curl_update<NDIM>), grid, blk, 0, s, (const float*)Es,
-                           (const float*)Xh, Yh, (float*)nullptr, 0.5f * h, g);
-        hipLaunchKernelGGL((k_field_ohm_cells<NDIM>), grid, blk, 0, s, (const float*)Yh, eta, g,
-                           aux, Es);
-        hipLaunchKernelGGL((k_field_curl_update<NDIM>), grid, blk, 0, s, (const float*)Es,
-                           (const float*)Xh, Xh, Xl, h, g);
+        if (m == 0)
+          hipLaunchKernelGGL(k_field_ohm_cells<true>, grid, blk, 0, s, base, n_half, J_half, eta,
+                             g, eos, aux, Es);
+        else
+          hipLaunchKernelGGL(k_field_ohm_cells<false>, grid, blk, 0, s, base, n_half, J_half, eta,
+                             g, eos, aux, Es);
+        hipLaunchKernelGGL(k_field_curl_update, grid, blk, 0, s, (const float*)Es, base, Yh,
+                           (const float*)nullptr, (float*)nullptr, 0.5f * h, g);
+        hipLaunchKernelGGL(k_field_ohm_cells<false>, grid, blk, 0, s, (const float*)Yh, n_half,
+                           J_half, eta, g, eos, aux, Es);
+        hipLaunchKernelGGL(k_field_curl_update, grid, blk, 0, s, (const float*)Es, base, Xh, lo,
+                           Xl, h, g);
+        base = Xh;
+        lo = Xl;
       }
       fh = Xh;
       fl = Xl;
@@ -855,8 +873,7 @@ int launch_field_advance_no(hvpic_ctx* c, float* B, const float* n_half, const f
   // residual test of the proposal
   hipLaunchKernelGGL(k_mid, dim3(g3), blk, 0, s, (const float*)B, Bno, Bmid, n3);
   hipLaunchKernelGGL((k_field_prep<2>), grid, blk, 0, s, n_half, (const float*)nullptr, J_half,
-                     (const float*)nullptr, 1.0f, 0.0f, g, eos.nfloor, eos.te_n0, eos.n0, eos.gam,
-                     eos.iso, aux);
+                     (const float*)nullptr, 1.0f, 0.0f, g, eos, aux);
   hipLaunchKernelGGL((k_field_stage<2>), grid, blk, 0, s, (const float*)Bmid, (const float*)B, T,
                      (float*)nullptr, (float)c->p.dt, eta, g, aux);
   hipLaunchKernelGGL(k_no_resid, grid, blk, 0, s, Bno, (const float*)T, (const float*)B, nc,

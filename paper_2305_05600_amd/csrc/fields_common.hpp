@@ -82,45 +82,6 @@ __device__ __forceinline__ float pressure(float n, float nfloor, float te_n0, fl
   return iso ? te_n0 / n0 * nf : te_n0 * powf(nf / n0, gam);
 }
 
-// Per-step frozen terms from n_eff = ca*na + cb*nb, J_eff = ca*Ja + cb*Jb.
-template <int NDIM>
-__global__ __launch_bounds__(kBlock) void k_field_prep(const float* __restrict__ na,
-                                                       const float* __restrict__ nb,
-                                                       const float* __restrict__ Ja,
-                                                       const float* __restrict__ Jb, float ca,
-                                                       float cb, FGeo g, float nfloor, float te_n0,
-                                                       float n0, float gam, int iso, Aux aux) {
-  const int c = blockIdx.x * kBlock + threadIdx.x;
-  if (c < g.ncell) {
-    const int nc = g.ncell;
-    int i, j, k;
-    fijk(c, g, i, j, k);
-    const Nbr nn = neighbours(c, i, j, k, g);
-    auto dens = [&](int q) { return nb ? ca * na[q] + cb * nb[q] : na[q]; };
-    const float n = dens(c);
-    const float nf = fmaxf(n, nfloor);
-    const float inv = (float)(1.0 / (double)nf);
-    aux.inv[c] = inv;
-    for (int a = 0; a < 3; ++a) {
-      const float J = Jb ? ca * Ja[a * nc + c] + cb * Jb[a * nc + c] : Ja[a * nc + c];
-      aux.u[a * nc + c] = J * inv;
-    }
-    const float pxp = pressure(dens(nn.xp), nfloor, te_n0, n0, gam, iso);
-    const float pxm = pressure(dens(nn.xm), nfloor, te_n0, n0, gam, iso);
-    const float pyp = pressure(dens(nn.yp), nfloor, te_n0, n0, gam, iso);
-    const float pym = pressure(dens(nn.ym), nfloor, te_n0, n0, gam, iso);
-    aux.gp[c] = -(pxp - pxm) * g.idx2 * inv;
-    aux.gp[nc + c] = -(pyp - pym) * g.idy2 * inv;
-    float gz = 0.f;
-    if (NDIM == 3) {
-      const float pzp = pressure(dens(nn.zp), nfloor, te_n0, n0, gam, iso);
-      const float pzm = pressure(dens(nn.zm), nfloor, te_n0, n0, gam, iso);
-      gz = -(pzp - pzm) * g.idz2 * inv;
-    }
-    aux.gp[2 * nc + c] = gz;
-  }
-}
-
 // Equation of state and floor for the frozen-moment terms (FP32), and n0,
 // gamma in FP64 for the electron energy diagnostic.
 struct Eos {
@@ -140,6 +101,41 @@ Eos make_eos(const hvpic_ctx* c) {
   eos.dgam = c->p.gamma_e;
   eos.dfloor = c->p.n_floor;
   return eos;
+}
+
+// Frozen terms of cell c from n_eff = ca*na + cb*nb, J_eff = ca*Ja + cb*Jb.
+template <int NDIM>
+__device__ __forceinline__ void prep_at(const float* na, const float* nb, const float* Ja,
+                                        const float* Jb, float ca, float cb, int c, const FGeo& g,
+                                        const Eos& eos, const Aux& aux) {
+  const int nc = g.ncell;
+  int i, j, k;
+  fijk(c, g, i, j, k);
+  const Nbr nn = neighbours(c, i, j, k, g);
+  auto dens = [&](int q) { return nb ? ca * na[q] + cb * nb[q] : na[q]; };
+  auto pres = [&](int q) {
+    return pressure(dens(q), eos.nfloor, eos.te_n0, eos.n0, eos.gam, eos.iso);
+  };
+  const float nf = fmaxf(dens(c), eos.nfloor);
+  const float inv = (float)(1.0 / (double)nf);
+  aux.inv[c] = inv;
+  for (int a = 0; a < 3; ++a) {
+    const float J = Jb ? ca * Ja[a * nc + c] + cb * Jb[a * nc + c] : Ja[a * nc + c];
+    aux.u[a * nc + c] = J * inv;
+  }
+  aux.gp[c] = -(pres(nn.xp) - pres(nn.xm)) * g.idx2 * inv;
+  aux.gp[nc + c] = -(pres(nn.yp) - pres(nn.ym)) * g.idy2 * inv;
+  aux.gp[2 * nc + c] = NDIM == 3 ? -(pres(nn.zp) - pres(nn.zm)) * g.idz2 * inv : 0.f;
+}
+
+template <int NDIM>
+__global__ __launch_bounds__(kBlock) void k_field_prep(const float* __restrict__ na,
+                                                       const float* __restrict__ nb,
+                                                       const float* __restrict__ Ja,
+                                                       const float* __restrict__ Jb, float ca,
+                                                       float cb, FGeo g, Eos eos, Aux aux) {
+  const int c = blockIdx.x * kBlock + threadIdx.x;
+  if (c < g.ncell) prep_at<NDIM>(na, nb, Ja, Jb, ca, cb, c, g, eos, aux);
 }
 
 // Electron internal energy per unit volume of density n (floored), divided by

@@ -67,6 +67,18 @@ struct Item {
   int32_t run, idx, nb;
 };
 
+// Part of an array that hardware block b of nb takes.  The GPU hands blocks out
+// round-robin over its 8 XCDs, each with its own L2, so XCD x takes a
+// contiguous eighth of the parts: blocks working on neighbouring rows of
+// cells (the stencil halos, the deposit windows, particles read from the
+// next row over) then share one L2.  A bijection of [0, nb).
+__device__ __forceinline__ int xcd_chunk(int b, int nb) {
+  constexpr int X = 8;
+  const int per = nb / X, rem = nb % X;
+  const int x = b % X, i = b / X;
+  return x * per + (x < rem ? x : rem) + i;
+}
+
 // Calls f(it) for the items this block takes of a persistent launch over
 // nitems items (gridDim.x a multiple of 8).  The GPU hands blocks out
 // round-robin over its 8 XCDs, each with its own L2, so XCD x takes the

@@ -107,18 +107,6 @@ struct DepArgs {
   bool vec;
 };
 
-// Chunk of the store for hardware block b of nb.  The GPU hands blocks out
-// round-robin over its 8 XCDs, each with its own L2, so XCD x takes a
-// contiguous eighth of the chunks: blocks working on neighbouring rows of
-// cells (the stencil halos, the deposit windows, particles read from the
-// next row over) then share one L2.  A bijection of [0, nb).
-__device__ __forceinline__ int xcd_chunk(int b, int nb) {
-  constexpr int X = 8;
-  const int per = nb / X, rem = nb % X;
-  const int x = b % X, i = b / X;
-  return x * per + min(x, rem) + i;
-}
-
 __device__ __forceinline__ void decompose(int a, const Geo& g, int& i, int& j, int& k) {
   uint32_t q = fdiv((uint32_t)a, g.fnx);
   i = a - (int)q * g.nx;

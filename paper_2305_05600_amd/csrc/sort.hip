@@ -75,27 +75,54 @@ __device__ __forceinline__ int direction(int key, int i, int j, int k, const Sor
   return (di + 1) + 3 * (dj + 1) + (NDIM == 3 ? 9 * (dk + 1) : 0);
 }
 
-// The same for a 2D old cell a whose neighbours need no wrap (an interior
-// cell, one or more cells from every edge): from the index difference by two
-// compares instead of two divisions.  The neighbours of such a cell are
-// exactly the differences 0, +-1, +-nx, +-nx +- 1.
-__device__ __forceinline__ int direction_interior2d(int key, int a, int nx) {
-  const int delta = key - a;
-  const int dj = delta >= nx - 1 ? 1 : (delta <= 1 - nx ? -1 : 0);
-  const int di = delta - dj * nx;
-  return di >= -1 && di <= 1 ? (di + 1) + 3 * (dj + 1) : -1;
+// A move by signs: along z kp/km, along y jp/jm, along x r (-1, 0, 1); ok false
+// when it is no move to a neighbour (then r may be anything).
+struct Move {
+  bool kp, km, jp, jm;
+  int r;
+  bool ok;
+};
+
+// From a cell whose neighbours need no wrap (an interior one, a cell or more from
+// every edge), by the difference of the indexes with compares instead of
+// divisions: the plane first (ny >= 4, so that a row's neighbours in the plane
+// differ by less than half a plane), then the row and the cell in it.  A key
+// that is no neighbour leaves a difference beyond one cell.
+template <int NDIM>
+__device__ __forceinline__ Move move_interior(int delta, const SortGeo& g) {
+  Move m;
+  const int nx = g.nx, nxny = g.nx * g.ny;
+  m.kp = NDIM == 3 && delta > nx + 1;
+  m.km = NDIM == 3 && delta < -(nx + 1);
+  const int r = m.kp ? delta - nxny : m.km ? delta + nxny : delta;
+  m.jp = r >= nx - 1;
+  m.jm = r <= 1 - nx;
+  m.r = m.jp ? r - nx : m.jm ? r + nx : r;
+  m.ok = (uint32_t)(m.r + 1) < 3u;
+  return m;
 }
 
-// The same in 3D: the plane first (ny >= 4, so that a row's neighbours in the
-// plane differ by less than half a plane), then the row and the cell in it.
-// A key that is no neighbour leaves a difference beyond one cell.
-__device__ __forceinline__ int direction_interior3d(int key, int a, int nx, int nxny) {
-  const int delta = key - a;
-  const int dk = delta > nx + 1 ? 1 : (delta < -(nx + 1) ? -1 : 0);
-  const int r = delta - dk * nxny;
-  const int dj = r >= nx - 1 ? 1 : (r <= 1 - nx ? -1 : 0);
-  const int di = r - dj * nx;
-  return di >= -1 && di <= 1 ? (di + 1) + 3 * (dj + 1) + 9 * (dk + 1) : -1;
+// From any cell.
+template <int NDIM>
+__device__ __forceinline__ Move move_any(int key, int cell, const SortGeo& g) {
+  int i, j, k, i2, j2, k2;
+  ijk(cell, g, i, j, k);
+  const bool in = (uint32_t)key < (uint32_t)g.ncell;
+  ijk(in ? key : 0, g, i2, j2, k2);
+  const int di = canon_move(i2 - i, g.nx), dj = canon_move(j2 - j, g.ny);
+  const int dk = NDIM == 3 ? canon_move(k2 - k, g.nz) : 0;
+  return Move{dk == 1, dk == -1, dj == 1, dj == -1, di, in && di != 2 && dj != 2 && dk != 2};
+}
+
+// The lanes of m that vote as this lane does: m & ~(votes ^ mine), one
+// three-input operation for each half.
+__device__ __forceinline__ uint64_t same_vote(uint64_t m, uint64_t votes, bool mine) {
+  constexpr int kAndXnor = 0x90;
+  const uint32_t v = mine ? ~0u : 0u;
+  const uint32_t lo = __builtin_amdgcn_bitop3_b32((uint32_t)m, (uint32_t)votes, v, kAndXnor);
+  const uint32_t hi =
+      __builtin_amdgcn_bitop3_b32((uint32_t)(m >> 32), (uint32_t)(votes >> 32), v, kAndXnor);
+  return (uint64_t)hi << 32 | lo;
 }
 
 // Whether the wavefront's old cells a0 .. a0+na-1 are all interior cells of
@@ -138,10 +165,9 @@ __device__ __forceinline__ uint64_t match_code(int code, uint64_t valid, const u
 constexpr int kCellsPerWave = 2;
 constexpr int kCellBits = 1;
 constexpr int kCountBatches = 4;    // 64-particle batches whose keys are loaded together
-// The scatter takes kScatterCells cells per wavefront.
+// The scatter takes kScatterCells cells per wavefront, up to four batches of
+// whose keys are loaded together.
 constexpr int kScatterCells = 2;
-constexpr int kScatterCellBits = 1;
-constexpr int kScatterBatches = 4;  // batches whose fields are loaded together
 
 // Boundaries of the wavefront's cells: b(m) = cs_prev[a0 + m], m = 0..na,
 // held by lane m.  Returns false if they are not a monotone partition of
@@ -161,14 +187,6 @@ __device__ __forceinline__ int cell_in_wave(int64_t p, int bnd, int na) {
   for (int q = 1; q < na; ++q) m += p >= (int64_t)__builtin_amdgcn_readlane(bnd, q) ? 1 : 0;
   return m;
 }
-// The same for an unsigned 32-bit position (cell_start values are
-// non-negative int32, checked by the caller).
-__device__ __forceinline__ int cell_in_wave32(uint32_t p, int bnd, int na) {
-  int m = 0;
-  for (int q = 1; q < na; ++q) m += p >= (uint32_t)__builtin_amdgcn_readlane(bnd, q) ? 1 : 0;
-  return m;
-}
-
 template <int NDIM>
 __global__ __launch_bounds__(kBlock) void k_nb_count(const int32_t* __restrict__ key,
                                                      const int32_t* __restrict__ cs_prev, int64_t n,
@@ -819,13 +837,13 @@ __device__ __forceinline__ void nb_scatter_body(const int32_t* __restrict__ cs_p
                                                 const Fields& in, const Fields& out, int32_t* cs,
                                                 const Status* st, uint32_t* rk0, uint32_t* rk1,
                                                 uint32_t* rv0, uint32_t* rv1, int bid) {
-  constexpr int ND = Dirs<NDIM>::N, NB = Dirs<NDIM>::BITS;
-  constexpr int CODE_BITS = NB + kScatterCellBits;
+  constexpr int ND = Dirs<NDIM>::N;
   constexpr int NF = PERM ? 0 : 7;        // fields carried through registers
   constexpr int NG = kScatterCells * ND;  // groups of the wavefront
   constexpr int GPL = (NG + 63) / 64;     // groups per lane
   __shared__ uint32_t s_next[kWaves][NG];  // next free slot of each group
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  // the wavefront's number in scalar registers, and so what follows from it
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int a0 = (bid * kWaves + wid) * kScatterCells;
   const int na = a0 < g.ncell ? min(kScatterCells, g.ncell - a0) : 0;
   // The far decision, the group bases and the cell bounds are independent:
@@ -868,81 +886,100 @@ __device__ __forceinline__ void nb_scatter_body(const int32_t* __restrict__ cs_p
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const bool interior = wave_interior<NDIM>(a0, na, g);
-  // open: the column of the wave's first cell (an interior wave lies in one row)
-  int col0 = 0;
-  if (OPEN) {
-    int j0, k0;
-    ijk(a0, g, col0, j0, k0);
-  }
+  int i0, j0, k0;
+  ijk(a0, g, i0, j0, k0);
   // positions in unsigned 32 bits: cell_start (and so n) is below 2^31, so
   // a batch's positions (up to 255 past pe) cannot wrap
   const uint32_t pb = (uint32_t)__builtin_amdgcn_readlane(bnd, 0);
   const uint32_t pe = (uint32_t)__builtin_amdgcn_readlane(bnd, na);
+  const uint32_t p1 = (uint32_t)__builtin_amdgcn_readlane(bnd, 1);  // first of the second cell
   const uint32_t n32 = (uint32_t)n;
-  for (uint32_t q0 = pb; q0 < pe; q0 += 64 * kScatterBatches) {
-   int keys[kScatterBatches];
-   float vals[kScatterBatches][NF > 0 ? NF : 1];
+  uint32_t* next = s_next[wid];
+  // NBT batches from position q0: their keys are loaded together, and no lane
+  // leaves the straight line before the stores, so the votes are the compares'
+  // own masks.
+  auto batches = [&](uint32_t q0, auto count, auto inner) {
+    constexpr int NBT = decltype(count)::value;
+    constexpr bool INNER = decltype(inner)::value;
+    int keys[NBT];
+    float vals[NBT][NF > 0 ? NF : 1];
 #pragma unroll
-   for (int b = 0; b < kScatterBatches; ++b) {
-     const uint32_t p = q0 + b * 64 + lane;
-     const bool v = p < pe;
-     keys[b] = v ? in.cell[p] : 0;
+    for (int b = 0; b < NBT; ++b) {
+      const uint32_t p = min(q0 + b * 64 + lane, pe - 1);
+      keys[b] = in.cell[p];
 #pragma unroll
-     for (int f = 0; f < NF; ++f) vals[b][f] = (v && in.f[f]) ? in.f[f][p] : 0.0f;
-   }
+      for (int f = 0; f < NF; ++f) vals[b][f] = in.f[f] ? in.f[f][p] : 0.0f;
+    }
+    uint32_t dst[NBT];
 #pragma unroll
-   for (int b = 0; b < kScatterBatches; ++b) {
-    const uint32_t p = q0 + b * 64 + lane;
-    const bool valid = p < pe;
-    int code = 0;
-    const int key = keys[b];
-    bool ok = false;
-    const int m = cell_in_wave32(p, bnd, na);
-    if (valid) {
-      int d;
-      int iold = col0 + m;
-      if (interior) {
-        d = NDIM == 2 ? direction_interior2d(key, a0 + m, g.nx)
-                      : direction_interior3d(key, a0 + m, g.nx, g.nx * g.ny);
-      } else {
-        int i, j, k;
-        ijk(a0 + m, g, i, j, k);
-        d = direction<NDIM>(key, i, j, k, g);
-        iold = i;
-      }
-      ok = d >= 0;
-      if (OPEN && ok) {
-        // absorbed: the new cell is in a ghost column
-        int inew = iold + d % 3 - 1;
+    for (int b = 0; b < NBT; ++b) {
+      const uint32_t p = q0 + b * 64 + lane;
+      const bool second = p >= p1;
+      const Move mv = INNER ? move_interior<NDIM>(keys[b] - (a0 + (second ? 1 : 0)), g)
+                            : move_any<NDIM>(keys[b], a0 + (second ? 1 : 0), g);
+      bool ok = p < pe && mv.ok;
+      if (OPEN) {
+        // absorbed: the new cell is in a ghost column (an open wave's cells may
+        // lie in two rows; their columns follow each other with the wrap)
+        int iold = i0 + (second ? 1 : 0);
+        if (iold == g.nx) iold = 0;
+        int inew = iold + mv.r;
         if (inew < 0) inew += g.nx; else if (inew >= g.nx) inew -= g.nx;
         if (inew == 0 || inew == g.nx - 1) ok = false;
       }
-      code = (m << NB) | (ok ? d : 0);
+      uint64_t mine = same_vote(__ballot(ok), __ballot(second), second);
+      mine = same_vote(mine, __ballot(mv.r > 0), mv.r > 0);
+      mine = same_vote(mine, __ballot(mv.r < 0), mv.r < 0);
+      mine = same_vote(mine, __ballot(mv.jp), mv.jp);
+      mine = same_vote(mine, __ballot(mv.jm), mv.jm);
+      int slot = (ND >> 1) + mv.r + (mv.jp ? 3 : mv.jm ? -3 : 0) + (second ? ND : 0);
+      if (NDIM == 3) {
+        mine = same_vote(mine, __ballot(mv.kp), mv.kp);
+        mine = same_vote(mine, __ballot(mv.km), mv.km);
+        slot += mv.kp ? 9 : mv.km ? -9 : 0;
+      }
+      slot = ok ? slot : 0;
+      // ions of the group before this one in the batch; the first one moves
+      // the group's slot on (LDS operations of a wavefront keep their order)
+      const uint32_t before = __builtin_amdgcn_mbcnt_hi(
+          (uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
+      dst[b] = __hip_atomic_load(next + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) + before;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (ok && before == 0)
+        __hip_atomic_fetch_add(next + slot, (uint32_t)__builtin_popcountll(mine), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WAVEFRONT);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (!ok) dst[b] = n32;
     }
-    uint64_t bal[CODE_BITS];
-    const uint64_t vmask = __ballot(ok);
 #pragma unroll
-    for (int b = 0; b < CODE_BITS; ++b) bal[b] = __ballot(ok && ((code >> b) & 1));
-    const uint64_t mine = match_code<CODE_BITS>(code, vmask, bal);
-    const uint64_t before = mine & lanemask_lt();
-    const int slot = (code >> NB) * ND + (code & ((1 << NB) - 1));
-    uint32_t dst = 0;
-    if (ok) dst = s_next[wid][slot] + (uint32_t)__builtin_popcountll(before);
-    __builtin_amdgcn_wave_barrier();
-    if (ok && before == 0) s_next[wid][slot] += (uint32_t)__builtin_popcountll(mine);
-    __builtin_amdgcn_wave_barrier();
-    if (ok && dst < n32) {
+    for (int b = 0; b < NBT; ++b) {
+      if (dst[b] >= n32) continue;
       if (PERM) {
-        out.perm[dst] = (int32_t)p;
+        out.perm[dst[b]] = (int32_t)(q0 + b * 64 + lane);
       } else {
-        out.cell[dst] = key;
+        out.cell[dst[b]] = keys[b];
 #pragma unroll
         for (int f = 0; f < NF; ++f)
-          if (in.f[f]) out.f[f][dst] = vals[b][f];
+          if (in.f[f]) out.f[f][dst[b]] = vals[b][f];
       }
     }
-   }
+  };
+  uint32_t q0 = pb;
+  if (!interior) {
+    for (; q0 < pe; q0 += 128) batches(q0, std::integral_constant<int, 2>{}, std::false_type{});
+    return;
   }
+  for (; q0 < pe && pe - q0 > 192; q0 += 256)
+    batches(q0, std::integral_constant<int, 4>{}, std::true_type{});
+  if (q0 >= pe) return;
+  if (pe - q0 > 128)
+    batches(q0, std::integral_constant<int, 3>{}, std::true_type{});
+  else if (pe - q0 > 64)
+    batches(q0, std::integral_constant<int, 2>{}, std::true_type{});
+  else
+    batches(q0, std::integral_constant<int, 1>{}, std::true_type{});
 }
 
 template <int NDIM, bool PERM>

@@ -18,7 +18,7 @@
 // wavefront ballots.  Kernels: count (one wavefront per old cell; skipped when
 // the push already counted), tile totals of the new counts, per-cell prefix +
 // group bases (each block adds up the tile totals before its own), scatter
-// (one wavefront per two old cells).  A particle that moved further (or an
+// (one wavefront per four old cells).  A particle that moved further (or an
 // inconsistent cell_start) is flagged by the count pass; the flag is handed
 // to the scatter kernel, in which one block then runs the general sort on its
 // own (slow, but it costs no extra launch in the common case and needs no host
@@ -165,9 +165,8 @@ __device__ __forceinline__ uint64_t match_code(int code, uint64_t valid, const u
 constexpr int kCellsPerWave = 2;
 constexpr int kCellBits = 1;
 constexpr int kCountBatches = 4;    // 64-particle batches whose keys are loaded together
-// The scatter takes kScatterCells cells per wavefront, up to four batches of
-// whose keys are loaded together.
-constexpr int kScatterCells = 2;
+// The scatter takes kScatterCells cells per wavefront.
+constexpr int kScatterCells = 4;
 
 // Boundaries of the wavefront's cells: b(m) = cs_prev[a0 + m], m = 0..na,
 // held by lane m.  Returns false if they are not a monotone partition of
@@ -831,6 +830,12 @@ __device__ void block_sort(int64_t n, int ncell, Fields in, Fields out, int32_t*
 }
 
 // PERM: write the gather map out.perm[dst] = p instead of moving the fields.
+// Bound by instructions and by the two dependent trips to memory of a wavefront
+// (its bounds and bases, then its keys), so a wavefront takes four cells and
+// loads ahead, and a batch costs some 60 instructions without a branch.  Map of
+// the 3D beam store (134M ions in 128^3 cells): 525 us, 2.9 TB/s (two cells
+// without the loads ahead 690, and 886 with the votes taken from a code's bits);
+// of 13M ions in 512 x 256, beside the field advance: 51 us (58, 76).
 template <int NDIM, bool PERM, bool OPEN = false>
 __device__ __forceinline__ void nb_scatter_body(const int32_t* __restrict__ cs_prev, int64_t n,
                                                 const SortGeo& g, uint32_t* __restrict__ bases,
@@ -892,94 +897,112 @@ __device__ __forceinline__ void nb_scatter_body(const int32_t* __restrict__ cs_p
   // a batch's positions (up to 255 past pe) cannot wrap
   const uint32_t pb = (uint32_t)__builtin_amdgcn_readlane(bnd, 0);
   const uint32_t pe = (uint32_t)__builtin_amdgcn_readlane(bnd, na);
-  const uint32_t p1 = (uint32_t)__builtin_amdgcn_readlane(bnd, 1);  // first of the second cell
+  // first ions of the second to fourth cell (pe where there is none)
+  const uint32_t p1 = (uint32_t)__builtin_amdgcn_readlane(bnd, 1);
+  const uint32_t p2 = na > 2 ? (uint32_t)__builtin_amdgcn_readlane(bnd, 2) : pe;
+  const uint32_t p3 = na > 3 ? (uint32_t)__builtin_amdgcn_readlane(bnd, 3) : pe;
   const uint32_t n32 = (uint32_t)n;
   uint32_t* next = s_next[wid];
-  // NBT batches from position q0: their keys are loaded together, and no lane
-  // leaves the straight line before the stores, so the votes are the compares'
-  // own masks.
-  auto batches = [&](uint32_t q0, auto count, auto inner) {
-    constexpr int NBT = decltype(count)::value;
-    constexpr bool INNER = decltype(inner)::value;
+  // Four batches' keys are in flight while the four before are worked on; no
+  // lane leaves the straight line before the stores, so the votes are the
+  // compares' own masks.
+  constexpr int NBT = 4;
+  struct Batches {
     int keys[NBT];
     float vals[NBT][NF > 0 ? NF : 1];
+  };
+  auto load = [&](uint32_t q0, Batches& v) {
 #pragma unroll
     for (int b = 0; b < NBT; ++b) {
       const uint32_t p = min(q0 + b * 64 + lane, pe - 1);
-      keys[b] = in.cell[p];
+      v.keys[b] = in.cell[p];
 #pragma unroll
-      for (int f = 0; f < NF; ++f) vals[b][f] = in.f[f] ? in.f[f][p] : 0.0f;
-    }
-    uint32_t dst[NBT];
-#pragma unroll
-    for (int b = 0; b < NBT; ++b) {
-      const uint32_t p = q0 + b * 64 + lane;
-      const bool second = p >= p1;
-      const Move mv = INNER ? move_interior<NDIM>(keys[b] - (a0 + (second ? 1 : 0)), g)
-                            : move_any<NDIM>(keys[b], a0 + (second ? 1 : 0), g);
-      bool ok = p < pe && mv.ok;
-      if (OPEN) {
-        // absorbed: the new cell is in a ghost column (an open wave's cells may
-        // lie in two rows; their columns follow each other with the wrap)
-        int iold = i0 + (second ? 1 : 0);
-        if (iold == g.nx) iold = 0;
-        int inew = iold + mv.r;
-        if (inew < 0) inew += g.nx; else if (inew >= g.nx) inew -= g.nx;
-        if (inew == 0 || inew == g.nx - 1) ok = false;
-      }
-      uint64_t mine = same_vote(__ballot(ok), __ballot(second), second);
-      mine = same_vote(mine, __ballot(mv.r > 0), mv.r > 0);
-      mine = same_vote(mine, __ballot(mv.r < 0), mv.r < 0);
-      mine = same_vote(mine, __ballot(mv.jp), mv.jp);
-      mine = same_vote(mine, __ballot(mv.jm), mv.jm);
-      int slot = (ND >> 1) + mv.r + (mv.jp ? 3 : mv.jm ? -3 : 0) + (second ? ND : 0);
-      if (NDIM == 3) {
-        mine = same_vote(mine, __ballot(mv.kp), mv.kp);
-        mine = same_vote(mine, __ballot(mv.km), mv.km);
-        slot += mv.kp ? 9 : mv.km ? -9 : 0;
-      }
-      slot = ok ? slot : 0;
-      // ions of the group before this one in the batch; the first one moves
-      // the group's slot on (LDS operations of a wavefront keep their order)
-      const uint32_t before = __builtin_amdgcn_mbcnt_hi(
-          (uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
-      dst[b] = __hip_atomic_load(next + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) + before;
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      if (ok && before == 0)
-        __hip_atomic_fetch_add(next + slot, (uint32_t)__builtin_popcountll(mine), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WAVEFRONT);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      if (!ok) dst[b] = n32;
-    }
-#pragma unroll
-    for (int b = 0; b < NBT; ++b) {
-      if (dst[b] >= n32) continue;
-      if (PERM) {
-        out.perm[dst[b]] = (int32_t)(q0 + b * 64 + lane);
-      } else {
-        out.cell[dst[b]] = keys[b];
-#pragma unroll
-        for (int f = 0; f < NF; ++f)
-          if (in.f[f]) out.f[f][dst[b]] = vals[b][f];
-      }
+      for (int f = 0; f < NF; ++f) v.vals[b][f] = in.f[f] ? in.f[f][p] : 0.0f;
     }
   };
-  uint32_t q0 = pb;
-  if (!interior) {
-    for (; q0 < pe; q0 += 128) batches(q0, std::integral_constant<int, 2>{}, std::false_type{});
-    return;
-  }
-  for (; q0 < pe && pe - q0 > 192; q0 += 256)
-    batches(q0, std::integral_constant<int, 4>{}, std::true_type{});
-  if (q0 >= pe) return;
-  if (pe - q0 > 128)
-    batches(q0, std::integral_constant<int, 3>{}, std::true_type{});
-  else if (pe - q0 > 64)
-    batches(q0, std::integral_constant<int, 2>{}, std::true_type{});
+  auto batch = [&](uint32_t q0, int b, const Batches& v, auto inner) {
+    constexpr bool INNER = decltype(inner)::value;
+    const int key = v.keys[b];
+    const uint32_t p = q0 + b * 64 + lane;
+    const bool upper = p >= p2, odd = p >= (upper ? p3 : p1);
+    const int m = (upper ? 2 : 0) + (odd ? 1 : 0);
+    const Move mv = INNER ? move_interior<NDIM>(key - a0 - m, g) : move_any<NDIM>(key, a0 + m, g);
+    bool ok = p < pe && mv.ok;
+    if (OPEN) {
+      // absorbed: the new cell is in a ghost column (an open wave's cells may
+      // lie in several rows; their columns follow each other with the wrap)
+      int iold = i0 + m;
+      while (iold >= g.nx) iold -= g.nx;
+      int inew = iold + mv.r;
+      if (inew < 0) inew += g.nx; else if (inew >= g.nx) inew -= g.nx;
+      if (inew == 0 || inew == g.nx - 1) ok = false;
+    }
+    uint64_t mine = same_vote(__ballot(ok), __ballot(upper), upper);
+    mine = same_vote(mine, __ballot(odd), odd);
+    mine = same_vote(mine, __ballot(mv.r > 0), mv.r > 0);
+    mine = same_vote(mine, __ballot(mv.r < 0), mv.r < 0);
+    mine = same_vote(mine, __ballot(mv.jp), mv.jp);
+    mine = same_vote(mine, __ballot(mv.jm), mv.jm);
+    int slot = (ND >> 1) + mv.r + (mv.jp ? 3 : mv.jm ? -3 : 0) + (upper ? 2 * ND : 0) + (odd ? ND : 0);
+    if (NDIM == 3) {
+      mine = same_vote(mine, __ballot(mv.kp), mv.kp);
+      mine = same_vote(mine, __ballot(mv.km), mv.km);
+      slot += mv.kp ? 9 : mv.km ? -9 : 0;
+    }
+    slot = ok ? slot : 0;
+    // ions of the group before this one in the batch; the first one moves
+    // the group's slot on (LDS operations of a wavefront keep their order)
+    const uint32_t before = __builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
+    const uint32_t dst =
+        __hip_atomic_load(next + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) + before;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (ok && before == 0)
+      __hip_atomic_fetch_add(next + slot, (uint32_t)__builtin_popcountll(mine), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return ok ? dst : n32;
+  };
+  auto store = [&](uint32_t q0, int b, const Batches& v, uint32_t dst) {
+    if (dst >= n32) return;
+    if (PERM) {
+      out.perm[dst] = (int32_t)(q0 + b * 64 + lane);
+    } else {
+      out.cell[dst] = v.keys[b];
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+        if (in.f[f]) out.f[f][dst] = v.vals[b][f];
+    }
+  };
+  if (pb >= pe) return;
+  auto run = [&](auto inner) {
+    Batches cur;
+    load(pb, cur);
+    for (uint32_t q0 = pb;;) {
+      Batches nxt;  // (not with seven fields in registers: they would cost occupancy)
+      const uint32_t q1 = q0 + 64 * NBT;
+      const bool more = pe - q0 > 64 * NBT;
+      if (PERM && more) load(q1, nxt);
+      const int nb = more ? NBT : (int)((pe - q0 + 63) / 64);
+      uint32_t dst[NBT];
+#pragma unroll
+      for (int b = 0; b < NBT; ++b) {
+        dst[b] = n32;
+        if (b < nb) dst[b] = batch(q0, b, cur, inner);
+      }
+#pragma unroll
+      for (int b = 0; b < NBT; ++b) store(q0, b, cur, dst[b]);
+      if (!more) break;
+      if (PERM) cur = nxt; else load(q1, cur);
+      q0 = q1;
+    }
+  };
+  if (interior)
+    run(std::true_type{});
   else
-    batches(q0, std::integral_constant<int, 1>{}, std::true_type{});
+    run(std::false_type{});
 }
 
 template <int NDIM, bool PERM>

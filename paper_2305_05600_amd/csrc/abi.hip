@@ -94,7 +94,7 @@ Layout workspace_layout(const hvpic_params* p) {
   const int64_t cap = std::max<int64_t>(p->np_capacity, 1);
   const int ndir = p->ndim == 2 ? 9 : 27;
   const int64_t ntiles = ceil_div(cap, kRadixTile);
-  const int64_t nblk = std::max(ceil_div(nc, kNbTileSmall), ceil_div(kRadixBins * ntiles, kScanTile)) + 1;
+  const int64_t nblk = std::max(ceil_div(nc, kNbTileSmall), ceil_div(ntiles << kRadixBitsMax, kScanTile)) + 1;
   size_t off = 0;
   L.status = off;    off += align256(sizeof(Status));
   // per-block partials: particle-chunk blocks (>= 1024 particles each) or
@@ -108,7 +108,7 @@ Layout workspace_layout(const hvpic_params* p) {
   L.rkey1 = off;     off += align256(sizeof(uint32_t) * cap);
   L.rval0 = off;     off += align256(sizeof(uint32_t) * cap);
   L.rval1 = off;     off += align256(sizeof(uint32_t) * cap);
-  L.rhist = off;     off += align256(sizeof(uint32_t) * kRadixBins * ntiles);
+  L.rhist = off;     off += align256(sizeof(uint32_t) * (ntiles << kRadixBitsMax));
   L.fscratch = off;  off += align256(sizeof(float) * 25 * nc);
   L.mom_acc = off;   off += align256(sizeof(double) * 4 * nc);
   L.open_rows = off;

@@ -340,6 +340,7 @@ Layout workspace_layout(const hvpic_params* p);
 
 constexpr int kRadixBits = 8;
 constexpr int kRadixBins = 1 << kRadixBits;
+constexpr int kRadixBitsMax = 9;  // digits of the passes over the whole store
 constexpr int kRadixItems = 8;  // keys per thread per radix tile
 constexpr int kRadixTile = kBlock * kRadixItems;
 constexpr int kScanTile = 2048;  // elements per block of the prefix scans

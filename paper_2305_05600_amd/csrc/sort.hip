@@ -24,8 +24,8 @@
 // own (slow, but it costs no extra launch in the common case and needs no host
 // round trip).
 //
-// General path.  LSD radix sort of (cell, index) pairs with 8-bit digits;
-// each pass is a per-tile digit histogram, a scan of the digit-major
+// General path.  LSD radix sort of (cell, index) pairs with digits of 8 or 9
+// bits; each pass is a per-tile digit histogram, a scan of the digit-major
 // histogram, and a stable scatter whose in-tile ranks come from per-wavefront
 // match masks.  The permutation then gathers the particle fields.  The same
 // tile ranking drives the single-block fallback.
@@ -684,21 +684,24 @@ __device__ void gather_fields(const uint32_t* keys, const uint32_t* perm, int64_
   }
 }
 
-// Per-tile histogram of one digit; hist is digit-major [bin][tile].
+// Per-tile histogram of one digit of BITS bits; hist is digit-major [bin][tile].
+template <int BITS>
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t* __restrict__ keys,
                                                        const int32_t* __restrict__ cells, int64_t n,
                                                        int shift, uint32_t* __restrict__ hist,
                                                        int ntiles, int ncell) {
-  __shared__ uint32_t h[kRadixBins];
-  for (int b = threadIdx.x; b < kRadixBins; b += kBlock) h[b] = 0;
+  constexpr int BINS = 1 << BITS;
+  __shared__ uint32_t h[BINS];
+  for (int b = threadIdx.x; b < BINS; b += kBlock) h[b] = 0;
   __syncthreads();
-  const int64_t t0 = (int64_t)blockIdx.x * kRadixTile;
+  const int tile = xcd_chunk(blockIdx.x, ntiles);
+  const int64_t t0 = (int64_t)tile * kRadixTile;
   for (int q = 0; q < kRadixItems; ++q) {
     const int64_t idx = t0 + q * kBlock + threadIdx.x;
-    if (idx < n) atomicAdd(&h[(load_key(keys, cells, idx, ncell) >> shift) & (kRadixBins - 1)], 1u);
+    if (idx < n) atomicAdd(&h[(load_key(keys, cells, idx, ncell) >> shift) & (BINS - 1)], 1u);
   }
   __syncthreads();
-  for (int b = threadIdx.x; b < kRadixBins; b += kBlock) hist[(int64_t)b * ntiles + blockIdx.x] = h[b];
+  for (int b = threadIdx.x; b < BINS; b += kBlock) hist[(int64_t)b * ntiles + tile] = h[b];
 }
 
 // Generic 3-kernel exclusive scan of a uint32 array (tile sums, scan of the
@@ -739,30 +742,71 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(uint32_t* __restrict__ v,
   }
 }
 
-// Stable scatter of one digit.  Within a tile the order is item-major:
-// element (q, t) is tile[q*kBlock + t], matching the global index order.
+// Stable scatter of one digit of BITS bits.  A wavefront takes a run of the
+// tile and ranks it batch by batch on its own, against the counts in its row of
+// LDS (the lanes with the same digit from votes, the ones before from mbcnt);
+// the block meets only to turn the rows into first slots.  Consecutive tiles,
+// whose runs of a digit follow each other in the output, belong to one XCD, so
+// its L2 completes their lines.  13.1M pairs, eight bits: 169 to 90 us, 2.3 TB/s
+// (nine bits: 121; tiles of twice the size no better).
+template <int BITS>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(
     const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
     const int32_t* __restrict__ cells, int64_t n, int shift, const uint32_t* __restrict__ offs,
     int ntiles, uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, int ncell) {
-  __shared__ uint32_t wcnt[kWaves][kRadixBins];
-  __shared__ uint32_t run[kRadixBins];
-  for (int b = threadIdx.x; b < kRadixBins; b += kBlock)
-    run[b] = offs[(int64_t)b * ntiles + blockIdx.x];
-  const int64_t t0 = (int64_t)blockIdx.x * kRadixTile;
+  constexpr int BINS = 1 << BITS;
+  __shared__ uint32_t cnt[kWaves][BINS];
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tile = xcd_chunk(blockIdx.x, ntiles);
+  const int64_t w0 = (int64_t)tile * kRadixTile + wid * (kRadixItems * 64) + lane;
+  uint32_t key[kRadixItems], val[kRadixItems], rank[kRadixItems];
+#pragma unroll
   for (int q = 0; q < kRadixItems; ++q) {
-    const int64_t idx = t0 + q * kBlock + threadIdx.x;
-    const bool valid = idx < n;
-    uint32_t key = 0, val = 0;
-    if (valid) {
-      key = load_key(kin, cells, idx, ncell);
-      val = vin ? vin[idx] : (uint32_t)idx;
+    const int64_t idx = min(w0 + q * 64, n - 1);
+    key[q] = load_key(kin, cells, idx, ncell);
+    val[q] = vin ? vin[idx] : (uint32_t)idx;
+  }
+  for (int b = threadIdx.x; b < kWaves * BINS; b += kBlock) (&cnt[0][0])[b] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kRadixItems; ++q) {
+    const bool valid = w0 + q * 64 < n;
+    const uint32_t digit = (key[q] >> shift) & (BINS - 1);
+    uint64_t mine = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+      const bool bit = digit & (1u << b);
+      mine = same_vote(mine, __ballot(bit), bit);
     }
-    const uint32_t dst = tile_dest(valid, (key >> shift) & (kRadixBins - 1), wcnt, run);
-    if (valid) {
-      kout[dst] = key;
-      vout[dst] = val;
+    const uint32_t before = __builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
+    rank[q] = before + __hip_atomic_load(&cnt[wid][digit], __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (valid && before == 0)
+      __hip_atomic_fetch_add(&cnt[wid][digit], (uint32_t)__builtin_popcountll(mine),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < BINS; b += kBlock) {
+    uint32_t at = offs[(int64_t)b * ntiles + tile];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const uint32_t m = cnt[w][b];
+      cnt[w][b] = at;
+      at += m;
     }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kRadixItems; ++q) {
+    if (w0 + q * 64 >= n) continue;
+    const uint32_t dst = cnt[wid][(key[q] >> shift) & (BINS - 1)] + rank[q];
+    kout[dst] = key[q];
+    vout[dst] = val[q];
   }
 }
 
@@ -1152,23 +1196,34 @@ void enqueue_radix(hvpic_ctx* c, const hvpic_particles* in, const Fields& out, i
   const int64_t n = in->n;
   const int ncell = nkeys;
   const int ntiles = (int)ceil_div(std::max<int64_t>(n, 1), kRadixTile);
-  const int passes = (radix_bits(ncell) + kRadixBits - 1) / kRadixBits;
+  // digits of eight bits, or of nine where that saves a pass (13.1M ions in 2^17
+  // cells: histograms, scans and scatters 390 us in three passes, 335 in two)
+  const int bits = radix_bits(ncell);
+  const int width = ceil_div(bits, kRadixBitsMax) < ceil_div(bits, kRadixBits) ? kRadixBitsMax
+                                                                             : kRadixBits;
+  const int passes = (int)ceil_div(bits, width);
   const uint32_t* kin = nullptr;
   const uint32_t* vin = nullptr;
   int cur = 0;
-  const int64_t m = (int64_t)kRadixBins * ntiles;
+  const int64_t m = ((int64_t)1 << width) * ntiles;
   const int mtiles = (int)ceil_div(m, kScanTile);
   uint32_t* blk = (uint32_t*)c->sort_blk;
   for (int pass = 0; pass < passes && n > 0; ++pass) {
-    const int shift = pass * kRadixBits;
-    hipLaunchKernelGGL(k_radix_hist, dim3(ntiles), dim3(kBlock), 0, s, kin, in->cell, n, shift,
-                       c->rhist, ntiles, ncell);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(mtiles), dim3(kBlock), 0, s, c->rhist, m, blk);
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, s, blk, mtiles);
-    hipLaunchKernelGGL(k_scan_apply, dim3(mtiles), dim3(kBlock), 0, s, c->rhist, m,
-                       (const uint32_t*)blk);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(ntiles), dim3(kBlock), 0, s, kin, vin, in->cell, n,
-                       shift, c->rhist, ntiles, c->rkey[cur], c->rval[cur], ncell);
+    const int shift = pass * width;
+    auto run = [&](auto hist, auto scatter) {
+      hipLaunchKernelGGL(hist, dim3(ntiles), dim3(kBlock), 0, s, kin, in->cell, n, shift, c->rhist,
+                         ntiles, ncell);
+      hipLaunchKernelGGL(k_scan_reduce, dim3(mtiles), dim3(kBlock), 0, s, c->rhist, m, blk);
+      hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, s, blk, mtiles);
+      hipLaunchKernelGGL(k_scan_apply, dim3(mtiles), dim3(kBlock), 0, s, c->rhist, m,
+                         (const uint32_t*)blk);
+      hipLaunchKernelGGL(scatter, dim3(ntiles), dim3(kBlock), 0, s, kin, vin, in->cell, n, shift,
+                         c->rhist, ntiles, c->rkey[cur], c->rval[cur], ncell);
+    };
+    if (width == kRadixBits)
+      run(k_radix_hist<kRadixBits>, k_radix_scatter<kRadixBits>);
+    else
+      run(k_radix_hist<kRadixBitsMax>, k_radix_scatter<kRadixBitsMax>);
     kin = c->rkey[cur];
     vin = c->rval[cur];
     cur ^= 1;

@@ -193,8 +193,7 @@ struct SubLds {
 __device__ void tile_partial(double* v) {
   __shared__ double s_red[kSubBlock / 64][kDiagNV];
 #pragma unroll
-  for (int k = 0; k < kDiagNV; ++k)
-    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o);
+  for (int k = 0; k < kDiagNV; ++k) v[k] = wave_sum(v[k]);
   const int wid = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0)
     for (int k = 0; k < kDiagNV; ++k) s_red[wid][k] = v[k];

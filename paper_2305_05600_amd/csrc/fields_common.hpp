@@ -208,7 +208,7 @@ __device__ __forceinline__ void field_diag_last(const DiagArgs& D, const double*
                            : 0.0;
 #pragma unroll
     for (int k = 0; k < kDiagNV; ++k) {
-      for (int o = 32; o > 0; o >>= 1) u[k] += __shfl_xor(u[k], o);
+      u[k] = wave_sum(u[k]);
       if (lane == 0) s_sum[q][k] = u[k];
     }
   }

@@ -92,6 +92,42 @@ __device__ __forceinline__ void for_items(int nitems, F f) {
   for (int j = l; j < len; j += g8) f(start + j);
 }
 
+// Sum over a wavefront (all 64 lanes active; every lane gets it), adding the
+// lanes 32, 16, 8, 4, 2 and 1 apart in turn.  The partners come by lane swaps
+// and DPP moves, in the vector ALU: a shuffle goes through the LDS unit, two
+// trips per step and value, which the output kernel of a 3D field advance (five
+// sums per wavefront) mostly waited for (43 to FIXME us at 128^3 cells) and the
+// 3D push, whose LDS unit is its busiest, paid 48 times a wavefront.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kQuadReverse = 0x1B, kQuadXor2 = 0x4E,
+                kQuadXor1 = 0xB1;
+  auto join = [](uint32_t hi, uint32_t lo) {
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+  };
+  uint64_t u = __builtin_bit_cast(uint64_t, v);
+  // a swap of a value with itself leaves a lane's own value in one result and
+  // its partner's in the other
+  auto l = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+  auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  v = join(h[0], l[0]) + join(h[1], l[1]);
+  u = __builtin_bit_cast(uint64_t, v);
+  l = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+  h = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  v = join(h[0], l[0]) + join(h[1], l[1]);
+  v += dpp_d<kRor8>(v);
+  v += dpp_d<kQuadReverse>(dpp_d<kHalfMirror>(v));
+  v += dpp_d<kQuadXor2>(v);
+  v += dpp_d<kQuadXor1>(v);
+  return v;
+}
+
 // FP64 partial sums of NV values over a block, written by thread 0 to
 // part[slot * STRIDE + k] (slot = blockIdx.x by default).  Fixed reduction
 // order (deterministic).
@@ -99,8 +135,7 @@ template <int NV, int STRIDE = 4>
 __device__ void block_partial(double* v, double* part, int64_t slot) {
   __shared__ double s_red[16][NV];
 #pragma unroll
-  for (int k = 0; k < NV; ++k)
-    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o);
+  for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
   const int wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
   if ((threadIdx.x & 63) == 0)
     for (int k = 0; k < NV; ++k) s_red[wid][k] = v[k];
@@ -138,8 +173,7 @@ __device__ void sum_partials(const double* part, int nblocks, double* res) {
     for (int u = 0; u < 8; ++u)
       for (int k = 0; k < NV; ++k) t[k] += v[u][k];
   }
-  for (int k = 0; k < NV; ++k)
-    for (int o = 32; o > 0; o >>= 1) t[k] += __shfl_xor(t[k], o);
+  for (int k = 0; k < NV; ++k) t[k] = wave_sum(t[k]);
   const int wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
   if ((threadIdx.x & 63) == 0)
     for (int k = 0; k < NV; ++k) s_red[wid][k] = t[k];

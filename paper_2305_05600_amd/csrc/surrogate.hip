@@ -89,7 +89,8 @@ __device__ __forceinline__ float tanh_f32(float x) {
 // 16, lane / 16) holds, of each group of 32 k, the k 8 lq .. 8 lq + 7 of pixel
 // ln for the B operand and of output row ln for the A operand, and receives
 // out channels 4lq..4lq+3 of pixel ln.  A group is one tap's 32 channels, or
-// two taps' 16 (the tenth tap is zero).  What bounds it: the activations
+// two taps' 16 (of the tenth tap both operands are zero, so that an infinite
+// input stays infinite there).  What bounds it: the activations
 // cross HBM once (a 32-channel layer of a million pixels moves 134 MB), and
 // each is read nine times from L1 and L2.  The weights stay in registers (72
 // of them at 32 x 32 channels) over all tiles of the wavefront: read from LDS
@@ -169,6 +170,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(const uint16_t* __restrict__
     v4f acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = v4f{0.f, 0.f, 0.f, 0.f};
+    if (TPG == 2 && sub == 1) cur[NG - 1] = u4a8{0u, 0u, 0u, 0u};
 #pragma unroll
     for (int q = 0; q < NG; ++q)
 #pragma unroll

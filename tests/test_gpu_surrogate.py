@@ -357,3 +357,69 @@ def test_field_advance_no_full_size(mods, tol):
     eB, eE = rel_l2(Bd.cpu().numpy(), rB), rel_l2(Ed.cpu().numpy(), rE)
     print(f"field advance (tol {tol:g}): rel L2 B {eB:.2e}, E {eE:.2e}", flush=True)
     assert eB < 1e-5 and eE < 1e-5
+
+
+@pytest.mark.parametrize("nimg,ny,nx", [(2, 13, 21), (1, 1, 6)])
+@pytest.mark.parametrize("cinp,coutp,mode", [(16, 32, 0), (32, 32, 0), (32, 16, 1), (16, 32, 2), (32, 32, 2)])
+def test_conv_layer_infinite_input(mods, nimg, ny, nx, cinp, coutp, mode):
+    """One infinite input value: the outputs whose taps see it are infinite
+    with the sign of their weight (+-1 after tanh), not NaN; the others are
+    those of the finite layer."""
+    H, S = mods
+    announce("no_conv_inf", nimg, ny, nx, cinp, coutp, mode)
+    rng = np.random.default_rng(41 + cinp + coutp + mode)
+    N = nimg * ny * nx
+    xb = _bf16_bits(rng.normal(size=(N, cinp)))
+    xb[N // 2, cinp - 2] = 0x7F80  # +inf
+    wb = _bf16_bits(rng.uniform(0.1, 0.5, size=(coutp, 9, cinp)) * np.where(rng.uniform(size=(coutp, 1, 1)) < 0.5, -1, 1))
+    hb = _bf16_bits(rng.uniform(-0.9, 0.9, size=(N, coutp)))
+    out = torch.zeros((N, coutp), dtype=torch.float32 if mode == 1 else torch.int16, device="cuda")
+    H.hvpic_no_conv3x3(nimg, nx, ny, cinp, coutp, mode, _dev(xb.view(np.int16), np.int16),
+                       _dev(wb.view(np.int16), np.int16), _dev(np.zeros(coutp), np.float32),
+                       _dev(hb.view(np.int16), np.int16), out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy() if mode == 1 else _from_bits(out.cpu().numpy().view(np.uint16))
+    x, w = _from_bits(xb).reshape(nimg, ny, nx, cinp), _from_bits(wb)
+    ref = np.zeros((N, coutp))
+    for t in range(9):
+        xs = np.roll(x, (1 - t // 3, 1 - t % 3), axis=(1, 2)).reshape(N, cinp)
+        ref += np.einsum("nc,oc->no", xs, w[:, t, :])
+    hit = np.isinf(ref)
+    assert hit.any() and not np.isnan(ref).any()
+    if mode == 2:
+        h = _from_bits(hb)
+        ref = ref * (1.0 - h * h)
+    elif mode == 0:
+        ref = np.tanh(ref)
+    assert np.array_equal(got[hit], ref[hit])
+    fin = ~hit
+    if fin.any():
+        s = np.abs(ref[fin]).max()
+        assert np.all(np.abs(got[fin] - ref[fin]) <= 2.0 ** -8 * np.abs(ref[fin]) + 1e-5 * s)
+
+
+@pytest.mark.parametrize("nimg,ny,nx", [(1, 8, 32), (1, 5, 7), (2, 11, 37)])
+@pytest.mark.parametrize("cinp,coutp", [(32, 16), (32, 32), (16, 32)])
+@pytest.mark.parametrize("pos", [0.0, 0.5, 1.0])
+def test_weight_gradient_infinite_input(mods, nimg, ny, nx, cinp, coutp, pos):
+    """One infinite input value: its channel's gradients are infinite with the
+    sign of dZ, also where the grid does not fill the kernel's tiles, and the
+    other channels' are finite."""
+    H, S = mods
+    announce("no_wgrad_inf", nimg, ny, nx, cinp, coutp, pos)
+    rng = np.random.default_rng(17 + nx)
+    N = nimg * ny * nx
+    xb = _bf16_bits(rng.normal(size=(N, cinp)))
+    ch = cinp // 2 + 1
+    xb[int(pos * (N - 1)), ch] = 0x7F80  # +inf
+    zb = _bf16_bits(rng.uniform(0.5, 1.0, size=(N, coutp)))
+    dw = torch.zeros((coutp, 9, cinp), dtype=torch.float32, device="cuda")
+    db = torch.zeros((coutp,), dtype=torch.float32, device="cuda")
+    ws = torch.empty(H.hvpic_no_workspace_bytes(nx, ny, nimg), dtype=torch.uint8, device="cuda")
+    H.hvpic_no_conv3x3_wgrad(nimg, nx, ny, cinp, coutp, _dev(xb.view(np.int16), np.int16),
+                             _dev(zb.view(np.int16), np.int16), dw, db, ws)
+    torch.cuda.synchronize()
+    got = dw.cpu().numpy()
+    assert np.all(got[:, :, ch] == np.inf)
+    rest = np.delete(got, ch, axis=2)
+    assert np.isfinite(rest).all() and np.isfinite(db.cpu().numpy()).all()

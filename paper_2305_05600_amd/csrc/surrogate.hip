@@ -244,18 +244,30 @@ __global__ __launch_bounds__(kWgThreads, 2) void k_conv3x3_wgrad(const uint16_t*
   constexpr int LX = XW * XH * XS, LZ = kSegX * kSegY * ZS;  // halves
   constexpr int LB = 2 * (LX + LZ), LR = 2 * (NWT + COUTP);
   __shared__ __attribute__((aligned(16))) uint16_t lds[LB > LR ? LB : LR];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ln = lane & 15, lq = lane >> 4;
   const int64_t P = (int64_t)nx * ny;
   const int nsx = (nx + kSegX - 1) / kSegX, nsy = (ny + kSegY - 1) / kSegY;
   const int64_t steps = (int64_t)nimg * nsx * nsy;
   const int64_t s0 = steps * blockIdx.x / gridDim.x, s1 = steps * (blockIdx.x + 1) / gridDim.x;
   u4a8 gx[XL], gz[ZL];
-  auto load = [&](int64_t st) {
-    const int64_t img = st / ((int64_t)nsx * nsy);
-    const int r = (int)(st - img * nsx * nsy), sx = r / nsy, sy = r - sx * nsy;
-    const int x0 = sx * kSegX, y0 = sy * kSegY;
-    const int w = min(kSegX, nx - x0), h = min(kSegY, ny - y0);
+  struct Tile {
+    int64_t img;
+    int x0, y0, w, h;
+  };
+  auto tile_at = [&](int64_t st) {
+    Tile T;
+    T.img = st / ((int64_t)nsx * nsy);
+    const int r = (int)(st - T.img * nsx * nsy), sx = r / nsy, sy = r - sx * nsy;
+    T.x0 = sx * kSegX;
+    T.y0 = sy * kSegY;
+    T.w = min(kSegX, nx - T.x0);
+    T.h = min(kSegY, ny - T.y0);
+    return T;
+  };
+  auto load = [&](const Tile& T) {
+    const int64_t img = T.img;
+    const int x0 = T.x0, y0 = T.y0, w = T.w, h = T.h;
 #pragma unroll
     for (int u = 0; u < XL; ++u) {
       const int e = (int)threadIdx.x + u * kWgThreads;
@@ -278,8 +290,8 @@ __global__ __launch_bounds__(kWgThreads, 2) void k_conv3x3_wgrad(const uint16_t*
             dZ + (img * P + (int64_t)(y0 + row) * nx + x0 + px) * COUTP + c * 8);
     }
   };
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   auto stage = [&](uint16_t* sx, uint16_t* sz) {
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int u = 0; u < XL; ++u) {
       const int e = (int)threadIdx.x + u * kWgThreads;
@@ -311,16 +323,27 @@ __global__ __launch_bounds__(kWgThreads, 2) void k_conv3x3_wgrad(const uint16_t*
   v8b ones;
 #pragma unroll
   for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
-  if (s0 < s1) load(s0);
+  Tile next{};
+  if (s0 < s1) load(next = tile_at(s0));
   int buf = 0;
   for (int64_t st = s0; st < s1; ++st, buf ^= 1) {
     // one barrier a tile: its buffer was last read two tiles ago, before the
     // barrier of the tile in between
     uint16_t* sx = lds + buf * (LX + LZ);
     uint16_t* sz = sx + LX;
+    const Tile cur = next;
     stage(sx, sz);
     __syncthreads();
-    if (st + 1 < s1) load(st + 1);
+    if (st + 1 < s1) load(next = tile_at(st + 1));
+    // pixels of the row that are missing (their dZ is zero) have their X zeroed
+    // too: a pixel of the rim may lie there, and 0 times an infinite X is NaN
+    const int w = wid < cur.h ? cur.w : 0;
+    u4 keep;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int px = 16 * (i / 2) + 4 * lq + 2 * (i % 2);  // and the one after
+      keep[i] = (px < w ? 0xFFFFu : 0u) | (px + 1 < w ? 0xFFFF0000u : 0u);
+    }
     v8b a[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -331,7 +354,8 @@ __global__ __launch_bounds__(kWgThreads, 2) void k_conv3x3_wgrad(const uint16_t*
     for (int t = 0; t < 9; ++t)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        const v8b b = frag(sx + ((wid + t / 3) * XW + t % 3) * XS + nt * 16, XS);
+        const v8b x = frag(sx + ((wid + t / 3) * XW + t % 3) * XS + nt * 16, XS);
+        const v8b b = __builtin_bit_cast(v8b, __builtin_bit_cast(u4, x) & keep);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
           acc[t][mt][nt] =

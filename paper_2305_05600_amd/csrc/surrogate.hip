@@ -225,7 +225,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(const uint16_t* __restrict__
 // the same places for A and B, so their order does not matter); a tap is an
 // offset of the X address.  A wavefront keeps all 9 * (COUTP/16) * (CINP/16)
 // output tiles and the sums of dZ (a product with ones) in registers, and the
-// eight wavefronts add theirs in order at the end.  The pixel stride (80 or 48
+// eight wavefronts' are added in order at the end.  The pixel stride (80 or 48
 // bytes) spreads the 16 pixels of an access over all banks.  The next tile's
 // loads go out before the current tile's products.
 // 32 x 32 channels, 1,048,576 pixels: 763 to 72 us (134 MB, 19.3 GFLOP).
@@ -242,8 +242,12 @@ __global__ __launch_bounds__(kWgThreads, 2) void k_conv3x3_wgrad(const uint16_t*
   constexpr int XN = XW * XH * XC, ZN = kSegX * kSegY * ZC;
   constexpr int XL = (XN + kWgThreads - 1) / kWgThreads, ZL = (ZN + kWgThreads - 1) / kWgThreads;
   constexpr int LX = XW * XH * XS, LZ = kSegX * kSegY * ZS;  // halves
-  constexpr int LB = 2 * (LX + LZ), LR = 2 * (NWT + COUTP);
-  __shared__ __attribute__((aligned(16))) uint16_t lds[LB > LR ? LB : LR];
+  // a wavefront's sums of one tap (rows of RS: the four quarters of an access
+  // fall on different banks) and of dZ
+  constexpr int RS = CINP + 4, RW = COUTP * RS + COUTP;
+  constexpr int LB = 2 * (LX + LZ);
+  static_assert(4 * RW * kSegY <= LB, "two buffers of sums in the tiles' place (halves)");
+  __shared__ __attribute__((aligned(16))) uint16_t lds[LB];
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ln = lane & 15, lq = lane >> 4;
   const int64_t P = (int64_t)nx * ny;
@@ -362,28 +366,37 @@ __global__ __launch_bounds__(kWgThreads, 2) void k_conv3x3_wgrad(const uint16_t*
               __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], b, acc[t][mt][nt], 0, 0, 0);
       }
   }
-  // the wavefronts' sums, added in order
+  // The eight wavefronts' sums, added in order, a tap at a time: all leave
+  // theirs in LDS and every thread adds up two or one of the outputs, with two
+  // buffers and one barrier a tap (one wavefront after the other adding all of
+  // its sums to the block's took 17 us more of every launch: training steps of
+  // three 8 x 8 grids 148 to 79 us, of eight 512 x 256 ones 619 to 550).
   float* red = reinterpret_cast<float*>(lds);
-  for (int wv = 0; wv < kSegY; ++wv) {
-    __syncthreads();
-    if (wid != wv) continue;
-    auto put = [&](int at, float v) { red[at] = wv == 0 ? v : red[at] + v; };
+  float* mine = part + (size_t)blockIdx.x * (NWT + COUTP);
+  __syncthreads();  // the last tile is read
+#pragma unroll
+  for (int t = 0; t < 9; ++t) {
+    float* r = red + (t & 1) * RW * kSegY;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int co = mt * 16 + lq * 4 + i;
 #pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            put((co * 9 + t) * CINP + nt * 16 + ln, acc[t][mt][nt][i]);
-        if (ln == 0) put(NWT + co, sum[mt][i]);
+        for (int nt = 0; nt < NT; ++nt) r[wid * RW + co * RS + nt * 16 + ln] = acc[t][mt][nt][i];
+        if (t == 0 && ln == 0) r[wid * RW + COUTP * RS + co] = sum[mt][i];
       }
+    __syncthreads();
+    auto total = [&](int at) {
+      float v = r[at];
+#pragma unroll
+      for (int wv = 1; wv < kSegY; ++wv) v += r[wv * RW + at];
+      return v;
+    };
+    for (int o = threadIdx.x; o < COUTP * CINP; o += kWgThreads)
+      mine[(o / CINP * 9 + t) * CINP + o % CINP] = total(o / CINP * RS + o % CINP);
+    if (t == 0 && threadIdx.x < COUTP) mine[NWT + threadIdx.x] = total(COUTP * RS + threadIdx.x);
   }
-  __syncthreads();
-  float* mine = part + (size_t)blockIdx.x * (NWT + COUTP);
-  for (int i = threadIdx.x; i < NWT + COUTP; i += kWgThreads) mine[i] = red[i];
 }
 
 // gw[i] += sum over nb blocks of part[b][i] (fixed order: four quarters of the

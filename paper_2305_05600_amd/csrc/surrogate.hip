@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "hvpic_internal.hpp"
+#include "pixel_groups.hpp"
 
 namespace hvpic {
 namespace {
@@ -697,9 +698,13 @@ int conv_grid(int64_t N) { return (int)std::min<int64_t>(ceil_div(ceil_div(N, 16
 template <int CINP, int COUTP, int MODE>
 void conv(hipStream_t s, const uint16_t* X, const uint16_t* W, const float* bias,
           const uint16_t* H, void* out, int64_t N, int nx, int ny) {
-  hipLaunchKernelGGL((k_conv3x3<CINP, COUTP, MODE>), dim3(conv_grid(N)), dim3(256), 0, s, X, W,
-                     bias, H, out, (uint32_t)N, nx, ny, make_fastdiv((uint32_t)(nx * ny)),
-                     make_fastdiv((uint32_t)nx));
+  constexpr int kOutBytes = COUTP * (MODE == 1 ? sizeof(float) : sizeof(uint16_t));
+  for_pixel_groups(N, (int64_t)nx * ny, [&](int64_t p, int64_t n) {
+    hipLaunchKernelGGL((k_conv3x3<CINP, COUTP, MODE>), dim3(conv_grid(n)), dim3(256), 0, s,
+                       X + p * CINP, W, bias, H ? H + p * COUTP : nullptr,
+                       static_cast<void*>(static_cast<char*>(out) + p * kOutBytes), (uint32_t)n,
+                       nx, ny, make_fastdiv((uint32_t)(nx * ny)), make_fastdiv((uint32_t)nx));
+  });
 }
 
 template <int CINP, int COUTP>

@@ -67,18 +67,25 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// tanh in FP32: the odd Taylor series below 0.35 (next term 2.4e-7 of x),
-// else 1 - 2 / (1 + exp(2|x|)) with the sign of x, by the hardware's exp2 and
-// reciprocal (1 ulp each): within 3e-7 of the value.  The math library's took
-// twice the time of the layer's matrix instructions.
+// tanh in FP32.  Below 1: x + x^3 p(x^2), p fitted for the least relative error,
+// its coefficients rounded one after the other with the rest fitted again.
+// Above: 1 - 2 / (1 + exp(2|x|)) with the sign of x, by the hardware's exp2 and
+// reciprocal (1 ulp each).  A NaN takes the polynomial.  Over all floats of
+// [2^-12, 12): at most 1.35 ulp, 0.290 on average (root mean square); the
+// math library's 1.41 and 0.295, at twice the time of the layer's matrix
+// instructions.
 __device__ __forceinline__ float tanh_f32(float x) {
   const float a = fabsf(x), s = x * x;
   const float e = __builtin_amdgcn_exp2f(2.88539008f * a);
-  const float big = copysignf(1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + e), x);
-  float p = fmaf(s, 62.0f / 2835.0f, -17.0f / 315.0f);
-  p = fmaf(s, p, 2.0f / 15.0f);
-  p = fmaf(s, p, -1.0f / 3.0f);
-  return a < 0.35f ? fmaf(x * s, p, x) : big;
+  const float big = copysignf(fmaf(-2.0f, __builtin_amdgcn_rcpf(1.0f + e), 1.0f), x);
+  float p = fmaf(s, 0x1.e77086p-14f, -0x1.ae8e98p-11f);
+  p = fmaf(s, p, 0x1.8f86c0p-9f);
+  p = fmaf(s, p, -0x1.18db78p-7f);
+  p = fmaf(s, p, 0x1.64c046p-6f);
+  p = fmaf(s, p, -0x1.b9f6dap-5f);
+  p = fmaf(s, p, 0x1.11103cp-3f);
+  p = fmaf(s, p, -0x1.555552p-2f);
+  return a >= 1.0f ? big : fmaf(x * s, p, x);
 }
 
 // One periodic 3x3 layer over N = nimg*ny*nx pixels.  W: bf16
@@ -192,7 +199,9 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(const uint16_t* __restrict__
         v.w = acc[mt][3] + bs[mt][3];
         *reinterpret_cast<float4*>(static_cast<float*>(out) + (int64_t)p * COUTP + co) = v;
       } else {
-        uint16_t o[4];
+        // (the conversion rounds to nearest even, two values an instruction)
+        typedef __bf16 v4b __attribute__((ext_vector_type(4)));
+        v4b o;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           float v;
@@ -203,11 +212,9 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(const uint16_t* __restrict__
             const float h = bf2f((uint16_t)(i & 1 ? hw >> 16 : hw & 0xFFFFu));
             v = acc[mt][i] * (1.0f - h * h);
           }
-          o[i] = f2bf(v);
+          o[i] = (__bf16)v;
         }
-        uint2 pk;
-        pk.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
-        pk.y = (uint32_t)o[2] | ((uint32_t)o[3] << 16);
+        const uint2 pk = __builtin_bit_cast(uint2, o);
         *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + (int64_t)p * COUTP + co) = pk;
       }
     }

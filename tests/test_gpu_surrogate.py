@@ -423,3 +423,52 @@ def test_weight_gradient_infinite_input(mods, nimg, ny, nx, cinp, coutp, pos):
     assert np.all(got[:, :, ch] == np.inf)
     rest = np.delete(got, ch, axis=2)
     assert np.isfinite(rest).all() and np.isfinite(db.cpu().numpy()).all()
+
+
+def test_tanh_rounds_as_well_as_the_library(mods):
+    """The layers' tanh, seen through its rounding to BF16: arguments (as
+    biases, with zero weights) whose tanh lies close to a BF16 tie, but no
+    closer than 1.5 ulp of FP32, the bound of the math library's tanhf (1.41
+    measured over all floats of [2^-12, 12)), so that any tanh as good as it
+    rounds to the nearest BF16."""
+    H, S = mods
+    announce("no_tanh")
+    # ties: half-way between neighbouring BF16 values of [2^-3, 1)
+    lo = np.arange(0x3E00, 0x3F7F, dtype=np.uint32)
+    tie = ((lo << 16) | 0x8000).astype(np.uint32).view(np.float32).astype(np.float64)
+    x0 = np.arctanh(tie).astype(np.float32)
+    xs = np.concatenate([(x0.view(np.int32) + k).view(np.float32) for k in range(-12, 13)])
+    xs = np.concatenate([xs, -xs])
+    t = np.tanh(np.abs(xs).astype(np.longdouble))
+    near = tie[np.argmin(np.abs(np.abs(xs)[:, None].astype(np.float64) - np.arctanh(tie)[None, :]), axis=1)]
+    ulp = np.spacing(np.abs(near).astype(np.float32)).astype(np.float64)
+    off = np.abs(t - near) / ulp
+    xs = xs[(off >= 1.5) & (off <= 8.0)]
+    want = _bf16_bits(np.tanh(xs.astype(np.float64)))  # (FP64 to FP32 to BF16: no second tie this far from one)
+    n = xs.size // 32 * 32
+    assert n >= 2048
+    got = np.empty(n, np.uint16)
+    xd, wd = torch.zeros((1, 16), dtype=torch.int16, device="cuda"), torch.zeros((32, 9, 16), dtype=torch.int16, device="cuda")
+    for k in range(0, n, 32):
+        out = torch.zeros((1, 32), dtype=torch.int16, device="cuda")
+        H.hvpic_no_conv3x3(1, 1, 1, 16, 32, 0, xd, wd, _dev(xs[k:k + 32], np.float32), None, out)
+        got[k:k + 32] = out.cpu().numpy().view(np.uint16)[0]
+    bad = np.flatnonzero(got != want[:n])
+    assert bad.size == 0, [(float(xs[i]), hex(got[i]), hex(want[i])) for i in bad[:5]]
+
+
+def test_tanh_special_values(mods):
+    """Zeros keep their sign, NaN stays, infinities and large values give +-1,
+    the smallest values themselves."""
+    H, S = mods
+    announce("no_tanh_special")
+    x = np.zeros(32, np.float32)
+    x[:12] = [0.0, -0.0, np.inf, -np.inf, np.nan, 1e30, -1e30, 44.5, -16.5, 1e-30, -1e-40, 2.0 ** -126]
+    out = torch.zeros((1, 32), dtype=torch.int16, device="cuda")
+    H.hvpic_no_conv3x3(1, 1, 1, 16, 32, 0, torch.zeros((1, 16), dtype=torch.int16, device="cuda"),
+                       torch.zeros((32, 9, 16), dtype=torch.int16, device="cuda"), _dev(x, np.float32), None, out)
+    got = _from_bits(out.cpu().numpy().view(np.uint16)[0])[:12]
+    assert np.isnan(got[4])
+    assert np.array_equal(got[[2, 3, 5, 6, 7, 8]], [1, -1, 1, -1, 1, -1])
+    assert got[0] == 0 and got[1] == 0
+    assert abs(got[9] - 1e-30) <= 2.0 ** -8 * 1e-30 and abs(got[11] - 2.0 ** -126) <= 2.0 ** -133

@@ -13,10 +13,11 @@
 // pressure instead of the equation of state.  lap is the compact second
 // difference (+1, -2, +1)/h^2 summed over the axes; div and grad are centred.
 //
-// 2D: one tile kernel per substep (fields_tile.hpp).  3D: three whole-grid
-// kernels per RK2 stage: J = curl B of the stage input; Ohm's
-// law (needs lap J, so J at the neighbours) and, with the energy equation, the
-// pressure update (needs u_e, p_e and T_e at the neighbours); B from curl E.
+// 2D: one tile kernel per substep (fields_tile.hpp).  3D, and 2D grids too narrow
+// for tiles: three whole-grid kernels per RK2 stage: J = curl B of the stage
+// input; Ohm's law (needs lap J, so J at the neighbours) and, with the energy
+// equation, the pressure update (needs u_e, p_e and T_e at the neighbours); B
+// from curl E.
 // Each is a stencil over arrays that stay in L2 during the subcycle.  B and
 // p_e are carried as unevaluated sums hi + lo as on the plain path; the
 // stage inputs are the hi parts.
@@ -302,7 +303,8 @@ int ext_impl(hvpic_ctx* c, float* B, float* pe, const float* n_half, const float
   const float* fl = nullptr;
   const float* fp = pe;
   const float* fpl = nullptr;
-  if (NDIM == 2 && mode == 0 && c->p.nsub > 0) {
+  const bool by_tiles = NDIM == 2 && ext_by_tiles<false>(g);
+  if (mode == 0 && c->p.nsub > 0 && by_tiles) {
     // one tile launch per substep, from the caller's arrays (lo parts zero) to
     // scratch and on between two sets of it
     ExtSub A{};

@@ -310,18 +310,42 @@ __global__ __launch_bounds__(kExBlock) void k_ext_sub2d(ExtSub A) {
 }
 
 // Tiles of 16 rows where those of 8 would not all be resident at once (two
-// blocks per CU): fewer cells computed twice (402 x 800 cells beside the open
-// sort: 45 us a substep with 8 rows, 43 with 16); smaller grids spread over
-// more CUs with 8 (256 x 192: 6.1 us).
+// blocks per CU) and not as many: fewer cells computed twice (402 x 800 cells
+// beside the open sort: 45 us a substep with 8 rows, 43 with 16); smaller grids
+// spread over more CUs with 8 (256 x 192: 6.1 us).
+struct ExtTiles {
+  int rows;
+  unsigned nx, ny;
+};
+inline ExtTiles ext_tiles(const FGeo& g) {
+  const unsigned nx = (unsigned)ceil_div(g.nx, kExTX);
+  const unsigned n8 = (unsigned)ceil_div(g.ny, 8), n16 = (unsigned)ceil_div(g.ny, 16);
+  if (nx * n8 > 512 && n8 > n16) return ExtTiles{16, nx, n16};
+  return ExtTiles{8, nx, n8};
+}
+
+// Whether a grid takes its substeps tile by tile.  A narrow one leaves most of
+// each tile empty, and the stencil per stage, which costs six launches and a
+// time that goes by the cells, is faster when it has many such tiles (4 x 100000
+// cells, four substeps: 135 us against 321).  The line is drawn at the tiles in
+// excess of twice those that the cells would fill.  Near it, by tiles / by
+// stages: hyper-resistive 8 x 25000 cells (excess 782) 116 / 115 us, 4 x 25000
+// (1172) 108 / 94, 8 x 50000 (1563) 186 / 148; open 10 x 12500 (293) 97 / 107,
+// 6 x 12500 (485) 96 / 100, 8 x 16666 (522) 115 / 105, 10 x 25000 (587) 148 / 123.
+template <bool OPEN>
+bool ext_by_tiles(const FGeo& g) {
+  const ExtTiles T = ext_tiles(g);
+  const int64_t full = (int64_t)g.ncell / (kExTX * T.rows / 2);
+  return (int64_t)T.nx * T.ny - full <= (OPEN ? 450 : 1000);
+}
+
 template <bool PE, bool OPEN>
 void launch_ext_sub2d(hipStream_t s, const ExtSub& A) {
-  const unsigned nx = (unsigned)ceil_div(A.g.nx, kExTX);
-  if (nx * (unsigned)ceil_div(A.g.ny, 8) > 512)
-    hipLaunchKernelGGL((k_ext_sub2d<PE, OPEN, 16>), dim3(nx, (unsigned)ceil_div(A.g.ny, 16)),
-                       dim3(kExBlock), 0, s, A);
+  const ExtTiles T = ext_tiles(A.g);
+  if (T.rows == 16)
+    hipLaunchKernelGGL((k_ext_sub2d<PE, OPEN, 16>), dim3(T.nx, T.ny), dim3(kExBlock), 0, s, A);
   else
-    hipLaunchKernelGGL((k_ext_sub2d<PE, OPEN, 8>), dim3(nx, (unsigned)ceil_div(A.g.ny, 8)),
-                       dim3(kExBlock), 0, s, A);
+    hipLaunchKernelGGL((k_ext_sub2d<PE, OPEN, 8>), dim3(T.nx, T.ny), dim3(kExBlock), 0, s, A);
 }
 
 }  // namespace

@@ -15,9 +15,9 @@
 // The particle kernels of the periodic step run unchanged on this grid (the
 // ghost columns keep the two sides apart); absorbed ions get the key ncell
 // and the open sort puts them last.  The field advance takes one tile kernel
-// per substep in 2D (fields_tile.hpp), and the stencil-per-stage form in 3D:
-// per RK2 stage the ghost planes are refilled, J = curl B1 (no x-derivatives
-// in the ghosts), Ohm's law, then Faraday in the interior.
+// per substep in 2D (fields_tile.hpp), and the stencil-per-stage form in 3D and
+// on narrow grids: per RK2 stage the ghost planes are refilled, J = curl B1 (no
+// x-derivatives in the ghosts), Ohm's law, then Faraday in the interior.
 #include <math.h>
 #include <string.h>
 
@@ -543,7 +543,8 @@ void open_advance(hvpic_ctx* c, const float* B0, float* B1, float* Btot, const f
   const float* fh = B1;
   const float* fl = nullptr;
   if (mode == 0) fill(c, B1, 3);
-  if (NDIM == 2 && mode == 0 && c->p.nsub > 0) {
+  const bool by_tiles = NDIM == 2 && ext_by_tiles<true>(g);
+  if (mode == 0 && c->p.nsub > 0 && by_tiles) {
     // one tile launch per substep, from the caller's B1 (lo zero) to scratch
     // and on between two sets of it
     ExtSub A{};

@@ -26,7 +26,6 @@ namespace hvpic {
 namespace {
 
 constexpr uint32_t kEnsMagic = 0x454e5331u;  // "ENS1"
-constexpr int kPpt[3] = {4, 8, 12};           // push particles per lane, by choice 0..2
 constexpr int kMaxLaunches = 64;
 constexpr int kCUs = 256;
 
@@ -64,8 +63,9 @@ struct hvpic_ensemble {
   char* diag_tab[2];
   size_t push_rec, mom_rec, sort_rec, field_rec, diag_rec;
   // item lists (device)
-  hvpic::Item* push_items;  // groups by push choice 0..2
-  int push_off[4];
+  hvpic::Item* push_items;  // groups by push kind
+  int push_off[hvpic::kEnsKinds + 1];
+  hvpic::EnsSplit split;    // chunks left to the split push
   hvpic::Item* mom_items;
   int n_mom;
   hvpic::Item* tile_items;
@@ -88,8 +88,8 @@ namespace {
 bool ens_ok(const hvpic_ensemble* e) { return e && e->magic == kEnsMagic; }
 
 struct EnsLayout {
-  size_t push_tab, mom_tab, sort_tab, field_tab, diag_tab, push_items, mom_items, tile_items,
-      scat_items, field_items, total;
+  size_t push_tab, mom_tab, sort_tab, field_tab, diag_tab, push_items, split_count, split_list,
+      mom_items, tile_items, scat_items, field_items, total;
   int64_t push_cap, field_cap, n_mom, n_tiles, n_scat;
 };
 
@@ -99,7 +99,7 @@ EnsLayout layout(const hvpic_run* runs, int nruns) {
   EnsLayout L{};
   size_t off = 0;
   const size_t pr = ens_push_record(nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                    nullptr, false, nullptr);
+                                    nullptr, false, 0, EnsSplit{}, nullptr);
   const size_t mr = ens_moments_record(nullptr, nullptr, nullptr, 0, nullptr, nullptr);
   const size_t sr = ens_sort_record(nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
   const size_t fr = ens_field_record(nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -109,7 +109,7 @@ EnsLayout layout(const hvpic_run* runs, int nruns) {
   for (int r = 0; r < nruns; ++r) {
     hvpic_ctx* c = runs[r].ctx;
     const int64_t n = runs[r].store[0].n;
-    L.push_cap += ceil_div(n, ens_chunk(kPpt[0]));
+    L.push_cap += ceil_div(n, ens_chunk(kEnsPpt[0]));
     L.n_mom += ens_moment_blocks(c);
     L.n_tiles += ens_sort_tiles(c);
     L.n_scat += ens_sort_scatter_blocks(c);
@@ -129,6 +129,8 @@ EnsLayout layout(const hvpic_run* runs, int nruns) {
   L.field_tab = take(2 * fr * nruns * (size_t)std::max(nl, 1));
   L.diag_tab = take(2 * dr * nruns);
   L.push_items = take(sizeof(Item) * L.push_cap);
+  L.split_count = take(2 * sizeof(uint32_t));
+  L.split_list = take(2 * sizeof(int32_t) * L.push_cap);
   L.mom_items = take(sizeof(Item) * L.n_mom);
   L.tile_items = take(sizeof(Item) * L.n_tiles);
   L.scat_items = take(sizeof(Item) * L.n_scat);
@@ -176,13 +178,11 @@ bool tuning_ok(const hvpic_tuning* t) {
   return true;
 }
 
-// Run r's push chunk (0..2): the tuned choice, but no longer than the plain
-// push takes (one that fits the LDS windows at the run's particles per cell).
-int push_choice(const hvpic_ensemble* e, int r) {
-  const int most = ens_plain_ppt(e->runs[r].store[0].n, e->runs[r].ctx->ncell);
-  int g = e->tune.push_chunk[e->pclass[r]];
-  while (g > 0 && kPpt[g] > most) --g;
-  return g;
+// Run r's push: the tuned chunk, but no longer than the plain push takes (one
+// that fits the LDS windows at the run's particles per cell).
+int push_kind(const hvpic_ensemble* e, int r) {
+  return ens_push_kind(e->runs[r].store[0].n, e->runs[r].ctx->ncell,
+                       e->tune.push_chunk[e->pclass[r]]);
 }
 
 // The item lists and both parities' tables for the current tuning, uploaded
@@ -194,15 +194,15 @@ int build(hvpic_ensemble* e) {
   };
   // items
   std::vector<Item> push, field, mom, tiles, scat;
-  for (int g = 0; g < 3; ++g) {
+  for (int g = 0; g < kEnsKinds; ++g) {
     e->push_off[g] = (int)push.size();
     for (int r = 0; r < R; ++r) {
-      if (push_choice(e, r) != g) continue;
-      const int nb = (int)ceil_div(e->runs[r].store[0].n, ens_chunk(kPpt[g]));
+      if (push_kind(e, r) != g) continue;
+      const int nb = (int)ceil_div(e->runs[r].store[0].n, ens_chunk(kEnsPpt[g]));
       for (int b = 0; b < nb; ++b) push.push_back(Item{r, b, nb});
     }
   }
-  e->push_off[3] = (int)push.size();
+  e->push_off[kEnsKinds] = (int)push.size();
   for (int g = 0; g < kTileShapes; ++g) {
     e->field_off[g] = (int)field.size();
     for (int r = 0; r < R; ++r) {
@@ -239,11 +239,11 @@ int build(hvpic_ensemble* e) {
     for (int r = 0; r < R; ++r) {
       hvpic_run& U = e->runs[r];
       hvpic_ctx* c = U.ctx;
-      const int g = push_choice(e, r);
+      const int g = push_kind(e, r);
       const int shape = e->tune.field_tile[e->gclass[r]];
       ens_push_record(c, &U.store[a], U.perm, &U.store[b], U.cell_start[a], U.E, U.B,
-                      U.push_diag != nullptr, pt.data() + e->push_rec * r);
-      ens_moments_record(c, U.n[b], U.J[b], (int)ceil_div(U.store[a].n, ens_chunk(kPpt[g])),
+                      U.push_diag != nullptr, g, e->split, pt.data() + e->push_rec * r);
+      ens_moments_record(c, U.n[b], U.J[b], (int)ceil_div(U.store[a].n, ens_chunk(kEnsPpt[g])),
                          U.push_diag, mt.data() + e->mom_rec * r);
       ens_sort_record(c, &U.store[b], U.cell_start[a], U.perm, U.cell_start[b],
                       st.data() + e->sort_rec * r);
@@ -270,12 +270,13 @@ int enqueue(hvpic_ensemble* e, int par, hipEvent_t* ev) {
     if (rc == HVPIC_OK) rc = v;
   };
   if (ev) (void)hipEventRecord(ev[0], s);
-  for (int g = 0; g < 3; ++g) {
+  const int shape = e->runs[0].ctx->p.shape;
+  for (int g = 0; g < kEnsKinds; ++g) {
     const int n = e->push_off[g + 1] - e->push_off[g];
-    ok(ens_launch_push(s, e->runs[0].ctx->p.shape, kPpt[g], e->push_tab[par],
-                       e->push_items + e->push_off[g], n,
+    ok(ens_launch_push(s, shape, g, e->push_tab[par], e->push_items + e->push_off[g], n,
                        persistent_grid(n, e->tune.blocks_per_cu[0])));
   }
+  ok(ens_launch_push_split(s, shape, e->push_tab[par], e->split));
   if (ev) (void)hipEventRecord(ev[1], s);
   ok(ens_launch_moments(s, e->mom_tab[par], e->mom_items, e->n_mom,
                         persistent_grid(e->n_mom, e->tune.blocks_per_cu[1])));
@@ -354,7 +355,7 @@ int hvpic_ensemble_init(const hvpic_run* runs, int nruns, void* hip_stream, void
   e->ws = ws;
   e->ws_bytes = L.total;
   e->push_rec = ens_push_record(nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                false, nullptr);
+                                false, 0, EnsSplit{}, nullptr);
   e->mom_rec = ens_moments_record(nullptr, nullptr, nullptr, 0, nullptr, nullptr);
   e->sort_rec = ens_sort_record(nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
   e->field_rec = ens_field_record(nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -374,6 +375,8 @@ int hvpic_ensemble_init(const hvpic_run* runs, int nruns, void* hip_stream, void
   e->scat_items = reinterpret_cast<Item*>(ws + L.scat_items);
   e->field_items = reinterpret_cast<Item*>(ws + L.field_items);
   e->push_cap = L.push_cap;
+  e->split = EnsSplit{reinterpret_cast<int32_t*>(ws + L.split_list),
+                      reinterpret_cast<uint32_t*>(ws + L.split_count), L.push_cap};
   e->field_cap = L.field_cap;
   e->pclass.resize(nruns);
   e->gclass.resize(nruns);
@@ -393,7 +396,11 @@ int hvpic_ensemble_init(const hvpic_run* runs, int nruns, void* hip_stream, void
     zero_counts(c);
     c->stream = old;
   }
-  const int rc = build(e);
+  const uint32_t zero[2] = {0, 0};
+  int rc = hipMemcpy(e->split.count, zero, sizeof(zero), hipMemcpyHostToDevice) == hipSuccess
+               ? HVPIC_OK
+               : HVPIC_EHIP;
+  if (rc == HVPIC_OK) rc = build(e);
   if (rc != HVPIC_OK) {
     e->magic = 0;
     delete e;

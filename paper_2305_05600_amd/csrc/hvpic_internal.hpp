@@ -305,13 +305,21 @@ int launch_smooth(hvpic_ctx* c, float* F, int ncomp, int npasses);
 // the host into `dst` (returning the record size; dst may be null to ask
 // it), and the batched launches over work items (tables and items in device
 // memory, grid a multiple of 8).  2D, gather-map sequence, fused deposit.
+// An ensemble's list of the chunks that need several windows: {chunk, run}
+// [cap], with their number and the count of the split push's ended blocks
+struct EnsSplit {
+  int32_t* list;
+  uint32_t* count;
+  int64_t cap;
+};
 size_t ens_push_record(hvpic_ctx* c, const hvpic_particles* in, const int32_t* perm,
                        hvpic_particles* out, const int32_t* cs, const float* E, const float* B,
-                       bool diag, void* dst);
+                       bool diag, int kind, const EnsSplit& split, void* dst);
 size_t ens_moments_record(hvpic_ctx* c, float* n, float* J, int nparts, double* diag_out,
                           void* dst);
 int ens_moment_blocks(const hvpic_ctx* c);
-int ens_launch_push(hipStream_t s, int shape, int ppt, const void* tab, const Item* items,
+int ens_launch_push_split(hipStream_t s, int shape, const void* tab, const EnsSplit& split);
+int ens_launch_push(hipStream_t s, int shape, int kind, const void* tab, const Item* items,
                     int nitems, int grid);
 int ens_launch_moments(hipStream_t s, const void* tab, const Item* items, int nitems, int grid);
 size_t ens_sort_record(hvpic_ctx* c, const hvpic_particles* in, const int32_t* cs_prev,
@@ -333,9 +341,13 @@ size_t ens_field_diag_record(hvpic_ctx* c, double* out, int shape, void* dst);
 int ens_launch_field(hipStream_t s, int shape, int K, int has_lin, int fin, const void* tab,
                      const Item* items, int nitems, int grid);
 int ens_launch_field_diag(hipStream_t s, const void* tab, int nruns);
-// particles per lane of the plain 2D push for n particles on ncell cells, and
+// The batched push's chunks: three lengths (particles per lane) that a tuning
+// can choose, and the plain push's for the sparse stores in which the chosen
+// one would not fit the LDS windows (their sums are the plain push's too).
+constexpr int kEnsKinds = 5;
+constexpr int kEnsPpt[kEnsKinds] = {4, 8, 12, 4, 8};
+int ens_push_kind(int64_t n, int64_t ncell, int choice);
 // particles per chunk for ppt particles per lane
-int ens_plain_ppt(int64_t n, int64_t ncell);
 constexpr int ens_chunk(int ppt) { return 256 * ppt; }
 // Per-block partial slots the field diagnostics need (the larger of the
 // output kernel's blocks and the 2D subcycle's tiles); kFieldPartStride

@@ -85,8 +85,10 @@ struct PushArgs {
   float* wo;
   bool off32;               // every source byte offset fits 32 bits (n < 2^30)
   const int32_t* order;     // position -> chunk (a permutation of the chunks), or null
-  int2* split_list;         // (chunk, slot) of the chunks left to k_push_split
+  int ppt;                  // particles per lane and chunk
+  int2* split_list;         // (chunk, tag) of the chunks left to k_push_split
   uint32_t* split_count;    // their number, and the count of its blocks that ended
+  uint32_t split_cap;       // places in the list
 };
 
 struct DepArgs {
@@ -615,27 +617,31 @@ __device__ __forceinline__ void queue_push(Queue<NDIM>& Q, const WinLds<WM>& wl,
   Q.count += add;
 }
 
-// A lane's running FP32 moment sums for its home cell: the deposit cell of
-// the first particle of its current group of four.
-template <int NDIM, int SHAPE>
+// The home sums of a sparse store's chunks and of those that take several
+// passes.
+using SparseSum = float;
+
+// A lane's running moment sums for its home cell: the deposit cell of the
+// first particle of its current group of four (R: float or double).
+template <int NDIM, int SHAPE, class R>
 struct Home {
-  float acc[Stencil<NDIM, SHAPE>::T][4];
+  R acc[Stencil<NDIM, SHAPE>::T][4];
   int key;  // window slot of the home cell, -1 if none yet
 };
 
-template <int NDIM, int SHAPE>
-__device__ __forceinline__ void home_clear(Home<NDIM, SHAPE>& H) {
+template <int NDIM, int SHAPE, class R>
+__device__ __forceinline__ void home_clear(Home<NDIM, SHAPE, R>& H) {
   H.key = -1;
 #pragma unroll
   for (int t = 0; t < Stencil<NDIM, SHAPE>::T; ++t)
-    H.acc[t][0] = H.acc[t][1] = H.acc[t][2] = H.acc[t][3] = 0.0f;
+    H.acc[t][0] = H.acc[t][1] = H.acc[t][2] = H.acc[t][3] = R(0);
 }
 
 // Deposit of one particle: into the home sums when its deposit cell is the
 // home cell, else into the queue (in the window) or the global accumulators.
 // Every lane of the wavefront calls it.
-template <int NDIM, int SHAPE, int WM>
-__device__ __forceinline__ void deposit_particle(Home<NDIM, SHAPE>& H, Queue<NDIM>& Q,
+template <int NDIM, int SHAPE, int WM, class R>
+__device__ __forceinline__ void deposit_particle(Home<NDIM, SHAPE, R>& H, Queue<NDIM>& Q,
                                                  const WinLds<WM>& wl, bool live, bool inwin, int rel,
                                                  int i, int j, int k, int mx, int my, int mz,
                                                  float x, float y, float z, float q, float vx,
@@ -651,13 +657,26 @@ __device__ __forceinline__ void deposit_particle(Home<NDIM, SHAPE>& H, Queue<NDI
   float wt[T];
   dep_weights<NDIM, SHAPE>(x, y, z, wt);
   const float qm = stay ? q : 0.0f;
+  if constexpr (std::is_same<R, float>::value) {
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    const float a = qm * wt[t];
-    H.acc[t][0] += a;
-    H.acc[t][1] = fmaf(a, vx, H.acc[t][1]);
-    H.acc[t][2] = fmaf(a, vy, H.acc[t][2]);
-    H.acc[t][3] = fmaf(a, vz, H.acc[t][3]);
+    for (int t = 0; t < T; ++t) {
+      const float a = qm * wt[t];
+      H.acc[t][0] += a;
+      H.acc[t][1] = fmaf(a, vx, H.acc[t][1]);
+      H.acc[t][2] = fmaf(a, vy, H.acc[t][2]);
+      H.acc[t][3] = fmaf(a, vz, H.acc[t][3]);
+    }
+  } else {
+    // (a particle that adds nothing adds no NaN either)
+    const double ux = stay ? vx : 0.0f, uy = stay ? vy : 0.0f, uz = stay ? vz : 0.0f;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const double a = qm * (stay ? wt[t] : 0.0f);
+      H.acc[t][0] += a;
+      H.acc[t][1] = fma(a, ux, H.acc[t][1]);
+      H.acc[t][2] = fma(a, uy, H.acc[t][2]);
+      H.acc[t][3] = fma(a, uz, H.acc[t][3]);
+    }
   }
   queue_push<NDIM, SHAPE>(Q, wl, use_win && !stay, key, x, y, z, q, vx, vy, vz);
   const bool global = live && !use_win;
@@ -707,6 +726,22 @@ __device__ __forceinline__ void scan_level(float (&acc)[T][4], float m) {
     }
 }
 
+// The same of double sums, two moves a value, and by selection: lanes with f
+// set add nothing.
+template <int D, int T>
+__device__ __forceinline__ void scan_level(double (&acc)[T][4], int f) {
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int ch = 0; ch < 4; ++ch) {
+      const uint64_t u = __builtin_bit_cast(uint64_t, acc[t][ch]);
+      const uint32_t lo = (uint32_t)shr_i<D>((int)(uint32_t)u, 0);
+      const uint32_t hi = (uint32_t)shr_i<D>((int)(u >> 32), 0);
+      const uint64_t v = f ? 0u : (uint64_t)hi << 32 | lo;
+      acc[t][ch] += __builtin_bit_cast(double, v);
+    }
+}
+
 // End of a group step: the home sums go to the window.  Consecutive lanes
 // hold consecutive particles, so lanes with the same home cell form runs.
 // An inclusive segmented scan within each 16-lane row (DPP, with segment-head
@@ -715,33 +750,35 @@ __device__ __forceinline__ void scan_level(float (&acc)[T][4], float m) {
 // alone adds it to the window: a few active lanes per cell in each FP64 LDS
 // atomic.  A level adds the neighbour's partial sum times 0 or 1, a DPP move
 // and one FMA.  Every lane of the wavefront calls it.
-template <int NDIM, int SHAPE, int WM>
-__device__ __forceinline__ void home_flush(Home<NDIM, SHAPE>& H, const WinLds<WM>& wl) {
+template <int NDIM, int SHAPE, int WM, class R>
+__device__ __forceinline__ void home_flush(Home<NDIM, SHAPE, R>& H, const WinLds<WM>& wl) {
   constexpr int T = Stencil<NDIM, SHAPE>::T;
   const int r = threadIdx.x & 15;
   const int h = H.key;
   const int prev = shr_i<1>(h, -2), next = shl1_i(h, -2);
   const bool last = r == 15 || next != h;
   // f: a run starts at or after the first lane that v already covers
-  int f = (r == 0 || prev != h) ? 1 : 0;
-  float m1, m2, m4, m8;  // 1: add the partial sum d lanes back
-  m1 = f ? 0.0f : 1.0f;
-  f |= shr_i<1>(f, 1);
-  m2 = f ? 0.0f : 1.0f;
-  f |= shr_i<2>(f, 1);
-  m4 = f ? 0.0f : 1.0f;
-  f |= shr_i<4>(f, 1);
-  m8 = f ? 0.0f : 1.0f;
-  // One level for all sums at a time, each v += shr(v) * m as a single FMA
-  // with the DPP move on its first operand (the compiler emits a separate
-  // move for each).  A level's first read of a sum follows its last write by
-  // all the other sums' instructions, except after the deposit's own writes:
-  // the s_nop before each level covers the two wait states a DPP read needs
-  // after a VALU write of its operand.
-  scan_level<1, T>(H.acc, m1);
-  scan_level<2, T>(H.acc, m2);
-  scan_level<4, T>(H.acc, m4);
-  scan_level<8, T>(H.acc, m8);
+  const int f1 = (r == 0 || prev != h) ? 1 : 0;
+  const int f2 = f1 | shr_i<1>(f1, 1);
+  const int f4 = f2 | shr_i<2>(f2, 1);
+  const int f8 = f4 | shr_i<4>(f4, 1);
+  if constexpr (std::is_same<R, float>::value) {
+    // One level for all sums at a time, each v += shr(v) * m as a single FMA
+    // with the DPP move on its first operand (the compiler emits a separate
+    // move for each).  A level's first read of a sum follows its last write by
+    // all the other sums' instructions, except after the deposit's own writes:
+    // the s_nop before each level covers the two wait states a DPP read needs
+    // after a VALU write of its operand.
+    scan_level<1, T>(H.acc, f1 ? 0.0f : 1.0f);
+    scan_level<2, T>(H.acc, f2 ? 0.0f : 1.0f);
+    scan_level<4, T>(H.acc, f4 ? 0.0f : 1.0f);
+    scan_level<8, T>(H.acc, f8 ? 0.0f : 1.0f);
+  } else {
+    scan_level<1, T>(H.acc, f1);
+    scan_level<2, T>(H.acc, f2);
+    scan_level<4, T>(H.acc, f4);
+    scan_level<8, T>(H.acc, f8);
+  }
   if (h >= 0 && last) {
     int s[T];
     stencil_slots<NDIM, SHAPE, WM>(h, wl.wrap[h], s);
@@ -1186,27 +1223,19 @@ struct PushLds {
   int32_t cs[WM + 1];
 };
 
-// What a chunk that does not fit one window does: kNever takes the global
-// path, kDefer leaves it in the list of k_push_split, which is the kPasses
-// form and takes several passes.  That form is a kernel of its own: the few
-// values that it carries along cost the common path registers when it is
-// inlined (2D QS 18 spilled; Harris step 337 to 341 us, full 3D push and sort
-// 6555 to 6677 us), and a call from the kernel costs more (345 and 6717 us).
-enum class Split { kNever, kDefer, kPasses };
-
 // Fused gather + Boris push + move (+ mid-point deposit when DEP) of the chunk
-// [base, end) of PPT*kBlock consecutive particles, whose cells run from first
-// to last.
+// [base, end) of ppt*kBlock consecutive particles, whose cells S describes.
 // At most 128 VGPRs, so that four wavefronts per SIMD keep enough loads in
 // flight (a 3D block's 35.8 KB of LDS allows four blocks per CU as well).
 // PM: 0 reads and writes the store in place; 1 and 2 read it through the
 // gather map A.perm (1: all byte offsets of the source arrays fit 32 bits).
-// slot picks the block's diagnostic slot (see push_chunk).
-template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM, Split MODE>
-__device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int64_t end,
-                                            int first, int last, int slot, int nb,
+// SPLIT: as many passes as S says, else at most one.  R: the home sums.
+// slot picks the block's diagnostic slot (see push_chunk), and its share of the
+// cell_start check when `check`.
+template <int NDIM, int SHAPE, bool DEP, int PM, int WM, bool SPLIT, class R, class P>
+__device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int64_t end, P ppt,
+                                            const Span& S, int slot, int nb, bool check,
                                             PushLds<NDIM, SHAPE, DEP, WM>& L) {
-  constexpr bool SPLIT = MODE == Split::kPasses;
   const Geo& g = A.g;
   float4* gw = L.gw;
   double* win = L.win;
@@ -1217,11 +1246,11 @@ __device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int
   const bool cnt_on = A.cs != nullptr;  // count the moves for the sort
   const bool want_diag = A.diag_part != nullptr;
   const bool wq = DEP || want_diag || PM != 0;  // the weights are needed
-  // Wavefront wv owns particles [base + wv*64*PPT, +64*PPT); in each group
+  // Wavefront wv owns particles [base + wv*64*ppt, +64*ppt); in each group
   // step lane l takes four consecutive ones, so a step is one coalesced
   // 1 KiB access per array.  The first step's particles are loaded during the
   // set-up below, each later step's right after the previous step's stores.
-  const int64_t wb = base + (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 * PPT;
+  const int64_t wb = base + (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 * ppt;
   const int64_t lb = wb + 4 * (threadIdx.x & 63);
   // a step of the wavefront is all in range, or it takes element-wise accesses
   auto step_full = [&](int h) { return A.vec && wb + h * 64 + 256 <= end; };
@@ -1234,20 +1263,11 @@ __device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int
   };
 
   load_step(0);
-  const Span S = chunk_span<NDIM, WM>(first, last, g);
-  if (MODE == Split::kDefer && S.passes > 1) {
-    if (threadIdx.x == 0) {
-      const uint32_t at = atomicAdd(A.split_count, 1u);
-      if (at < (uint32_t)nb) A.split_list[at] = make_int2((int)(base / (kBlock * PPT)), slot);
-    }
-    if (cnt_on) check_cell_start(A.cs, g.ncell, A.n, A.st, slot, nb);
-    return;
-  }
-  const bool wok = SPLIT || S.passes == 1;
+  const bool wok = SPLIT ? S.passes > 0 : S.passes == 1;
 
   float dK = 0.f, dP0 = 0.f, dP1 = 0.f, dP2 = 0.f;
   const WinLds<WM> wl{win, s_wrap};
-  Home<NDIM, SHAPE> H;
+  Home<NDIM, SHAPE, R> H;
   home_clear(H);
   Queue<NDIM> Q;
   Q.base = s_q + (DEP ? (threadIdx.x >> 6) * Queue<NDIM>::QCAP * Queue<NDIM>::QW : 0);
@@ -1258,169 +1278,169 @@ __device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int
   int pass = 0;
 #pragma unroll 1
   do {
-  const int c0 = SPLIT ? S.begin(pass) : first;
-  const int span = (SPLIT ? S.end(pass) : last) - c0, W = span + 5;
-  if (SPLIT && pass > 0) load_step(0);
-  if (wok) {
-    gwin_fill<NDIM, SHAPE>(reinterpret_cast<float*>(gw), span + 1, c0, g, A.E, A.B);
-    if (DEP) dwin_init<NDIM, WM>(win, s_wrap, W, c0, g);
-    if (cnt_on) moves_window_init<NDIM>(A.cs, c0, span, s_cs, s_cnt);
-  }
-  if (pass == 0) {  // behind the loads of the first step
-    count_path(A.st, wok);
-    if (cnt_on && !SPLIT) check_cell_start(A.cs, g.ncell, A.n, A.st, slot, nb);
-  }
-  __syncthreads();
-#pragma unroll 1
-  for (int h = 0; h < PPT; h += 4) {
-    const int64_t b4 = lb + h * 64;
-    const bool full = step_full(h) && !SPLIT;
-    int* ca = cur.ca;
-    float *px = cur.px, *py = cur.py, *pz = cur.pz, *ux = cur.ux, *uy = cur.uy, *uz = cur.uz;
-    const float* pw = cur.pw;
-    uint32_t keep = 0xFu;  // the lane's particles that this pass takes
-    if (SPLIT && PM == 0 && pass > 0) {
-      // in place, those that an earlier pass pushed hold their new cells: the
-      // chunk's first cell stands for "not in this pass" instead
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if ((done >> (h + q)) & 1u) ca[q] = S.first;
+    const int c0 = SPLIT ? S.begin(pass) : S.first;
+    const int span = (SPLIT ? S.end(pass) : S.last) - c0, W = span + 5;
+    if (SPLIT && pass > 0) load_step(0);
+    if (wok) {
+      gwin_fill<NDIM, SHAPE>(reinterpret_cast<float*>(gw), span + 1, c0, g, A.E, A.B);
+      if (DEP) dwin_init<NDIM, WM>(win, s_wrap, W, c0, g);
+      if (cnt_on) moves_window_init<NDIM>(A.cs, c0, span, s_cs, s_cnt);
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      // Every lane runs the common path; a lane past the end, with a bad
-      // cell or of another pass computes on finite stand-in values and has no
-      // effect.  Rare cases (outside the windows, far or non-finite moves,
-      // flags) take wavefront-uniform branches.
-      const int a = ca[q];
-      const float x = px[q], y = py[q], z = NDIM == 3 ? pz[q] : 0.f;
-      const float vx = ux[q], vy = uy[q], vz = uz[q];
-      const bool inrange = b4 + q < end;
-      const bool badcell = inrange && (unsigned)a >= (unsigned)g.ncell;
-      bool live = inrange && !badcell;
-      if (__ballot(badcell) != 0) {
-        if (badcell && pass == 0) raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
-      }
-      const int rel = a - c0;
-      const bool inwin = wok && rel >= 0 && rel <= span;
-      int i = 0, j = 0, k = 0;
-      float Ep[3] = {0.f, 0.f, 0.f}, Bp[3] = {0.f, 0.f, 0.f};
-      if (wok) gather_rec<NDIM, SHAPE>(gw, inwin ? rel : 0, x, y, z, Ep, Bp, i, j, k);
-      // outside the windows: the cell index for the global tables, rebuilt
-      // from its indices (a value of its own, so that the 64-bit address
-      // arithmetic of this rare path does not move the loaded cells into
-      // aligned register pairs on the common path)
-      int ag = 0;
-      bool outwin = live && !inwin;
-      if (__ballot(outwin) != 0) {
-        if (SPLIT && outwin && (pass > 0 || (a >= S.first && a <= S.last))) {
-          // another pass takes it (the first also takes what lies outside
-          // the chunk's cells altogether)
-          live = outwin = false;
-          keep &= ~(1u << q);
-        }
-        if (outwin) {
-          decompose(a, g, i, j, k);
-          ag = i + g.nx * (j + g.ny * k);
-          gather_eb<NDIM, SHAPE>(A.E, A.B, ag, i, j, k, x, y, z, g, Ep, Bp);
-        }
-      }
-      const float wgt = wq && live ? pw[q] : 0.f;
-      // Boris: half kick, rotation, half kick.
-      const float hh = A.a;
-      const float vmx = fmaf(hh, Ep[0], vx), vmy = fmaf(hh, Ep[1], vy), vmz = fmaf(hh, Ep[2], vz);
-      const float tx = hh * Bp[0], ty = hh * Bp[1], tz = hh * Bp[2];
-      // 2 / (1 + |t|^2) through the hardware reciprocal (within 1 ulp; the
-      // operand lies in [1, inf), so no denormals)
-      const float f = 2.0f * __builtin_amdgcn_rcpf(1.0f + (tx * tx + ty * ty + tz * tz));
-      const float sx = f * tx, sy = f * ty, sz = f * tz;
-      const float qx = vmx + (vmy * tz - vmz * ty);
-      const float qy = vmy + (vmz * tx - vmx * tz);
-      const float qz = vmz + (vmx * ty - vmy * tx);
-      const float nvx = fmaf(hh, Ep[0], vmx + (qy * sz - qz * sy));
-      const float nvy = fmaf(hh, Ep[1], vmy + (qz * sx - qx * sz));
-      const float nvz = fmaf(hh, Ep[2], vmz + (qx * sy - qy * sx));
-      if (want_diag) {
-        dK = fmaf(wgt, vx * nvx + vy * nvy + vz * nvz, dK);
-        dP0 = fmaf(wgt, vx + nvx, dP0);
-        dP1 = fmaf(wgt, vy + nvy, dP1);
-        dP2 = fmaf(wgt, vz + nvz, dP2);
-      }
-      // Move: x^{n+1} = x^n + v^{n+1/2} dt, and for the deposit the mid-point
-      // x^{n+1/2} = x^n + (dt/2) v^{n+1/2}, with renormalised offsets.
-      float nx_ = fmaf(nvx, A.kx, x), ny_ = fmaf(nvy, A.ky, y);
-      float nz_ = NDIM == 3 ? fmaf(nvz, A.kz, z) : z;
-      float xm = 0.f, ym = 0.f, zm = 0.f;
-      if (DEP) {
-        xm = fmaf(nvx, 0.5f * A.kx, x);
-        ym = fmaf(nvy, 0.5f * A.ky, y);
-        zm = NDIM == 3 ? fmaf(nvz, 0.5f * A.kz, z) : 0.0f;
-      }
-      bool near = fabsf(nx_) < 3.0f && fabsf(ny_) < 3.0f && (NDIM == 2 || fabsf(nz_) < 3.0f);
-      if (DEP)
-        near = near && fabsf(xm) < 3.0f && fabsf(ym) < 3.0f && (NDIM == 2 || fabsf(zm) < 3.0f);
-      int si = near_shift(nx_), sj = near_shift(ny_), sk = NDIM == 3 ? near_shift(nz_) : 0;
-      nx_ = fmaf(-2.0f, (float)si, nx_);
-      ny_ = fmaf(-2.0f, (float)sj, ny_);
-      if (NDIM == 3) nz_ = fmaf(-2.0f, (float)sk, nz_);
-      int mx = 0, my = 0, mz = 0;
-      if (DEP) {
-        mx = near_shift(xm);
-        my = near_shift(ym);
-        xm = fmaf(-2.0f, (float)mx, xm);
-        ym = fmaf(-2.0f, (float)my, ym);
-        if (NDIM == 3) {
-          mz = near_shift(zm);
-          zm = fmaf(-2.0f, (float)mz, zm);
-        }
-      }
-      int ni = wrap_near(i + si, g.nx), nj = wrap_near(j + sj, g.ny);
-      int nk = NDIM == 3 ? wrap_near(k + sk, g.nz) : 0;
-      const bool general = live && !near;
-      if (__ballot(general) != 0) {
-        if (general)
-          move_general<NDIM, DEP>(A, x, y, z, nvx, nvy, nvz, i, j, k, nx_, ny_, nz_, si, sj, sk,
-                                  ni, nj, nk, xm, ym, zm, mx, my, mz);
-      }
-      // a lane that is not live keeps its values
-      ca[q] = live ? ni + g.nx * (nj + g.ny * nk) : a;
-      px[q] = live ? nx_ : x;
-      py[q] = live ? ny_ : y;
-      if (NDIM == 3) pz[q] = live ? nz_ : z;
-      ux[q] = live ? nvx : vx;
-      uy[q] = live ? nvy : vy;
-      uz[q] = live ? nvz : vz;
-      if (cnt_on) {
-        const int d = move_direction<NDIM>(A, b4 + q, ag, rel, live, inwin, s_cs, i, j, k, ni, nj,
-                                           nk, si, sj, sk);
-        count_move<NDIM>(d, inwin, rel, ag, chome, nstay, s_cnt, A.cnt);
-      }
-      if (DEP)
-        deposit_particle<NDIM, SHAPE>(H, Q, wl, live, inwin, rel, i, j, k, mx, my, mz, xm, ym,
-                                      zm, A.qV * wgt, nvx, nvy, nvz, g, A.acc);
+    if (pass == 0) {  // behind the loads of the first step
+      count_path(A.st, wok);
+      if (cnt_on && check) check_cell_start(A.cs, g.ncell, A.n, A.st, slot, nb);
     }
-    store4(A.cell, b4, end, full, keep, ca);
-    store4(A.ox, b4, end, full, keep, px);
-    store4(A.oy, b4, end, full, keep, py);
-    if (NDIM == 3) store4(A.oz, b4, end, full, keep, pz);
-    store4(A.ux, b4, end, full, keep, ux);
-    store4(A.uy, b4, end, full, keep, uy);
-    store4(A.uz, b4, end, full, keep, uz);
-    if (PM != 0) store4(A.wo, b4, end, full, keep, pw);
-    if (SPLIT && PM == 0) done |= keep << h;
-    // the next step's particles arrive during the flushes below
-    if (h + 4 < PPT) load_step(h + 4);
-    if (DEP) home_flush(H, wl);
-    if (cnt_on) count_flush<NDIM>(chome, nstay, s_cnt);
-  }
-  if (DEP) queue_drain<NDIM, SHAPE>(Q, wl);
-  if (wok && (DEP || cnt_on)) {
     __syncthreads();
-    if (DEP) dwin_flush<NDIM, WM>(win, W, c0, g, A.acc);
-    if (cnt_on) moves_window_flush<NDIM>(s_cnt, c0, span, A.cnt);
-  }
-  // the next pass fills the windows again and reads what this one stored
-  if (SPLIT) __syncthreads();
+#pragma unroll 1
+    for (int h = 0; h < ppt; h += 4) {
+      const int64_t b4 = lb + h * 64;
+      const bool full = step_full(h) && !(SPLIT && S.passes > 1);
+      int* ca = cur.ca;
+      float *px = cur.px, *py = cur.py, *pz = cur.pz, *ux = cur.ux, *uy = cur.uy, *uz = cur.uz;
+      const float* pw = cur.pw;
+      uint32_t keep = 0xFu;  // the lane's particles that this pass takes
+      if (SPLIT && PM == 0 && pass > 0) {
+        // in place, those that an earlier pass pushed hold their new cells: the
+        // chunk's first cell stands for "not in this pass" instead
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if ((done >> (h + q)) & 1u) ca[q] = S.first;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        // Every lane runs the common path; a lane past the end, with a bad
+        // cell or of another pass computes on finite stand-in values and has no
+        // effect.  Rare cases (outside the windows, far or non-finite moves,
+        // flags) take wavefront-uniform branches.
+        const int a = ca[q];
+        const float x = px[q], y = py[q], z = NDIM == 3 ? pz[q] : 0.f;
+        const float vx = ux[q], vy = uy[q], vz = uz[q];
+        const bool inrange = b4 + q < end;
+        const bool badcell = inrange && (unsigned)a >= (unsigned)g.ncell;
+        bool live = inrange && !badcell;
+        if (__ballot(badcell) != 0) {
+          if (badcell && pass == 0) raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
+        }
+        const int rel = a - c0;
+        const bool inwin = wok && rel >= 0 && rel <= span;
+        int i = 0, j = 0, k = 0;
+        float Ep[3] = {0.f, 0.f, 0.f}, Bp[3] = {0.f, 0.f, 0.f};
+        if (wok) gather_rec<NDIM, SHAPE>(gw, inwin ? rel : 0, x, y, z, Ep, Bp, i, j, k);
+        // outside the windows: the cell index for the global tables, rebuilt
+        // from its indices (a value of its own, so that the 64-bit address
+        // arithmetic of this rare path does not move the loaded cells into
+        // aligned register pairs on the common path)
+        int ag = 0;
+        bool outwin = live && !inwin;
+        if (__ballot(outwin) != 0) {
+          if (SPLIT && S.passes > 1 && outwin && (pass > 0 || (a >= S.first && a <= S.last))) {
+            // another pass takes it (the first also takes what lies outside
+            // the chunk's cells altogether)
+            live = outwin = false;
+            keep &= ~(1u << q);
+          }
+          if (outwin) {
+            decompose(a, g, i, j, k);
+            ag = i + g.nx * (j + g.ny * k);
+            gather_eb<NDIM, SHAPE>(A.E, A.B, ag, i, j, k, x, y, z, g, Ep, Bp);
+          }
+        }
+        const float wgt = wq && live ? pw[q] : 0.f;
+        // Boris: half kick, rotation, half kick.
+        const float hh = A.a;
+        const float vmx = fmaf(hh, Ep[0], vx), vmy = fmaf(hh, Ep[1], vy), vmz = fmaf(hh, Ep[2], vz);
+        const float tx = hh * Bp[0], ty = hh * Bp[1], tz = hh * Bp[2];
+        // 2 / (1 + |t|^2) through the hardware reciprocal (within 1 ulp; the
+        // operand lies in [1, inf), so no denormals)
+        const float f = 2.0f * __builtin_amdgcn_rcpf(1.0f + (tx * tx + ty * ty + tz * tz));
+        const float sx = f * tx, sy = f * ty, sz = f * tz;
+        const float qx = vmx + (vmy * tz - vmz * ty);
+        const float qy = vmy + (vmz * tx - vmx * tz);
+        const float qz = vmz + (vmx * ty - vmy * tx);
+        const float nvx = fmaf(hh, Ep[0], vmx + (qy * sz - qz * sy));
+        const float nvy = fmaf(hh, Ep[1], vmy + (qz * sx - qx * sz));
+        const float nvz = fmaf(hh, Ep[2], vmz + (qx * sy - qy * sx));
+        if (want_diag) {
+          dK = fmaf(wgt, vx * nvx + vy * nvy + vz * nvz, dK);
+          dP0 = fmaf(wgt, vx + nvx, dP0);
+          dP1 = fmaf(wgt, vy + nvy, dP1);
+          dP2 = fmaf(wgt, vz + nvz, dP2);
+        }
+        // Move: x^{n+1} = x^n + v^{n+1/2} dt, and for the deposit the mid-point
+        // x^{n+1/2} = x^n + (dt/2) v^{n+1/2}, with renormalised offsets.
+        float nx_ = fmaf(nvx, A.kx, x), ny_ = fmaf(nvy, A.ky, y);
+        float nz_ = NDIM == 3 ? fmaf(nvz, A.kz, z) : z;
+        float xm = 0.f, ym = 0.f, zm = 0.f;
+        if (DEP) {
+          xm = fmaf(nvx, 0.5f * A.kx, x);
+          ym = fmaf(nvy, 0.5f * A.ky, y);
+          zm = NDIM == 3 ? fmaf(nvz, 0.5f * A.kz, z) : 0.0f;
+        }
+        bool near = fabsf(nx_) < 3.0f && fabsf(ny_) < 3.0f && (NDIM == 2 || fabsf(nz_) < 3.0f);
+        if (DEP)
+          near = near && fabsf(xm) < 3.0f && fabsf(ym) < 3.0f && (NDIM == 2 || fabsf(zm) < 3.0f);
+        int si = near_shift(nx_), sj = near_shift(ny_), sk = NDIM == 3 ? near_shift(nz_) : 0;
+        nx_ = fmaf(-2.0f, (float)si, nx_);
+        ny_ = fmaf(-2.0f, (float)sj, ny_);
+        if (NDIM == 3) nz_ = fmaf(-2.0f, (float)sk, nz_);
+        int mx = 0, my = 0, mz = 0;
+        if (DEP) {
+          mx = near_shift(xm);
+          my = near_shift(ym);
+          xm = fmaf(-2.0f, (float)mx, xm);
+          ym = fmaf(-2.0f, (float)my, ym);
+          if (NDIM == 3) {
+            mz = near_shift(zm);
+            zm = fmaf(-2.0f, (float)mz, zm);
+          }
+        }
+        int ni = wrap_near(i + si, g.nx), nj = wrap_near(j + sj, g.ny);
+        int nk = NDIM == 3 ? wrap_near(k + sk, g.nz) : 0;
+        const bool general = live && !near;
+        if (__ballot(general) != 0) {
+          if (general)
+            move_general<NDIM, DEP>(A, x, y, z, nvx, nvy, nvz, i, j, k, nx_, ny_, nz_, si, sj, sk,
+                                    ni, nj, nk, xm, ym, zm, mx, my, mz);
+        }
+        // a lane that is not live keeps its values
+        ca[q] = live ? ni + g.nx * (nj + g.ny * nk) : a;
+        px[q] = live ? nx_ : x;
+        py[q] = live ? ny_ : y;
+        if (NDIM == 3) pz[q] = live ? nz_ : z;
+        ux[q] = live ? nvx : vx;
+        uy[q] = live ? nvy : vy;
+        uz[q] = live ? nvz : vz;
+        if (cnt_on) {
+          const int d = move_direction<NDIM>(A, b4 + q, ag, rel, live, inwin, s_cs, i, j, k, ni, nj,
+                                             nk, si, sj, sk);
+          count_move<NDIM>(d, inwin, rel, ag, chome, nstay, s_cnt, A.cnt);
+        }
+        if (DEP)
+          deposit_particle<NDIM, SHAPE>(H, Q, wl, live, inwin, rel, i, j, k, mx, my, mz, xm, ym,
+                                        zm, A.qV * wgt, nvx, nvy, nvz, g, A.acc);
+      }
+      store4(A.cell, b4, end, full, keep, ca);
+      store4(A.ox, b4, end, full, keep, px);
+      store4(A.oy, b4, end, full, keep, py);
+      if (NDIM == 3) store4(A.oz, b4, end, full, keep, pz);
+      store4(A.ux, b4, end, full, keep, ux);
+      store4(A.uy, b4, end, full, keep, uy);
+      store4(A.uz, b4, end, full, keep, uz);
+      if (PM != 0) store4(A.wo, b4, end, full, keep, pw);
+      if (SPLIT && PM == 0) done |= keep << h;
+      // the next step's particles arrive during the flushes below
+      if (h + 4 < ppt) load_step(h + 4);
+      if (DEP) home_flush(H, wl);
+      if (cnt_on) count_flush<NDIM>(chome, nstay, s_cnt);
+    }
+    if (DEP) queue_drain<NDIM, SHAPE>(Q, wl);
+    if (wok && (DEP || cnt_on)) {
+      __syncthreads();
+      if (DEP) dwin_flush<NDIM, WM>(win, W, c0, g, A.acc);
+      if (cnt_on) moves_window_flush<NDIM>(s_cnt, c0, span, A.cnt);
+    }
+    // the next pass fills the windows again and reads what this one stored
+    if (SPLIT) __syncthreads();
   } while (SPLIT && ++pass < S.passes);
   if (want_diag) {
     const double hm = 0.5 * A.ms;
@@ -1429,18 +1449,12 @@ __device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int
   }
 }
 
-// The push of chunk `chunk` of the nb chunks of PPT*kBlock consecutive
-// particles of the store.  slot, a bijection of the launch's blocks onto
-// [0, nb) that does not depend on the data, picks the block's share of the
-// cell_start check and its diagnostic slot, so that the check covers every
-// entry even where a chunk order built from a bad cell_start repeats a chunk.
-template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM, Split MODE>
-__device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slot, int nb) {
-  constexpr int CN = kBlock * PPT;  // particles per chunk
-  __shared__ __attribute__((aligned(16))) PushLds<NDIM, SHAPE, DEP, WM> lds;
+// Lines up the chunk [base, end) of the store: the span of its cells, from the
+// first and the last particle's.  Every thread calls it, before the block's
+// other use of its LDS.
+template <int NDIM, int PM, int WM>
+__device__ __forceinline__ Span chunk_of(const PushArgs& A, int64_t base, int64_t end) {
   __shared__ int s_c[2];
-  const int64_t base = (int64_t)chunk * CN;
-  const int64_t end = min(base + (int64_t)CN, A.n);
   if (threadIdx.x == 0) {
     if (PM != 0) {
       // (entries outside [0, n) are flagged where the particles are loaded)
@@ -1453,9 +1467,57 @@ __device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slo
     }
   }
   __syncthreads();
-  push_passes<NDIM, SHAPE, DEP, PM, PPT, WM, MODE>(
-      A, base, end, __builtin_amdgcn_readfirstlane(s_c[0]),
-      __builtin_amdgcn_readfirstlane(s_c[1]), slot, nb, lds);
+  return chunk_span<NDIM, WM>(__builtin_amdgcn_readfirstlane(s_c[0]),
+                              __builtin_amdgcn_readfirstlane(s_c[1]), A.g);
+}
+
+// The push of chunk `chunk` of the nb chunks of PPT*kBlock consecutive
+// particles of the store, unless it needs several windows: it is then left,
+// with `tag`, in the list of the split push.  slot, a bijection of the launch's
+// blocks onto [0, nb) that does not depend on the data, picks the block's share
+// of the cell_start check and its diagnostic slot, so that the check covers
+// every entry even where a chunk order built from a bad cell_start repeats a
+// chunk.
+// The split push is a kernel of its own: the few values that it carries along
+// cost the common path registers when it is inlined (2D QS 18 spilled; Harris
+// step 337 to 341 us, full 3D push and sort 6555 to 6677 us), and a call from
+// the kernel costs more (345 and 6717 us).
+template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM, class R>
+__device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slot, int tag,
+                                           int nb) {
+  constexpr int CN = kBlock * PPT;  // particles per chunk
+  __shared__ __attribute__((aligned(16))) PushLds<NDIM, SHAPE, DEP, WM> lds;
+  const int64_t base = (int64_t)chunk * CN;
+  const int64_t end = min(base + (int64_t)CN, A.n);
+  const Span S = chunk_of<NDIM, PM, WM>(A, base, end);
+  if (S.passes > 1) {
+    if (threadIdx.x == 0) {
+      const uint32_t at = atomicAdd(A.split_count, 1u);
+      if (at < A.split_cap) A.split_list[at] = make_int2(chunk, tag);
+    }
+    if (A.cs != nullptr) check_cell_start(A.cs, A.g.ncell, A.n, A.st, slot, nb);
+    return;
+  }
+  push_passes<NDIM, SHAPE, DEP, PM, WM, false, R>(A, base, end, std::integral_constant<int, PPT>{},
+                                                  S, slot, nb, true, lds);
+}
+
+// The same of any chunk, of A.ppt particles per lane, in as many passes as it
+// needs; DENSE: the plan's home sums are float, and so are those of a chunk
+// that fits its window.
+template <int NDIM, int SHAPE, bool DEP, int PM, int WM, bool DENSE>
+__device__ __forceinline__ void push_split_chunk(const PushArgs& A, int chunk, int slot, int nb,
+                                                 bool check) {
+  __shared__ __attribute__((aligned(16))) PushLds<NDIM, SHAPE, DEP, WM> lds;
+  const int64_t base = (int64_t)chunk * (kBlock * A.ppt);
+  const int64_t end = min(base + (int64_t)(kBlock * A.ppt), A.n);
+  const Span S = chunk_of<NDIM, PM, WM>(A, base, end);
+  if (DENSE && S.passes <= 1)
+    push_passes<NDIM, SHAPE, DEP, PM, WM, false, float>(A, base, end, A.ppt, S, slot, nb, check,
+                                                        lds);
+  else
+    push_passes<NDIM, SHAPE, DEP, PM, WM, true, SparseSum>(A, base, end, A.ppt, S, slot, nb, check,
+                                                        lds);
 }
 
 // Wavefronts per SIMD of the push: four unless a wider 3D window's LDS (53 KB
@@ -1465,28 +1527,30 @@ constexpr int push_waves() {
   return NDIM == 2 || WM <= 24 ? 4 : (WM <= 40 ? 3 : 2);
 }
 
-template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM>
+// The chunk of the store that the block of slot `slot` of nb takes.
+__device__ __forceinline__ int ordered_chunk(const PushArgs& A, int slot, int nb) {
+  if (!A.order) return slot;
+  const int o = A.order[slot];
+  return (unsigned)o < (unsigned)nb ? o : slot;
+}
+
+template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM, class R>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(push_waves<NDIM, WM>())))
 void k_gather_push(PushArgs A) {
   const int slot = xcd_chunk(blockIdx.x, gridDim.x);
-  int chunk = slot;
-  if (A.order) {
-    const int o = A.order[slot];
-    if ((unsigned)o < gridDim.x) chunk = o;
-  }
-  push_chunk<NDIM, SHAPE, DEP, PM, PPT, WM, Split::kDefer>(A, chunk, slot, gridDim.x);
+  push_chunk<NDIM, SHAPE, DEP, PM, PPT, WM, R>(A, ordered_chunk(A, slot, gridDim.x), slot, slot,
+                                               gridDim.x);
 }
 
-// The chunks that k_gather_push left in the list (nb chunks in all), a
-// persistent launch.  The last block to end empties the list for the next
-// push.
-template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM>
-__global__ __launch_bounds__(kBlock) void k_push_split(PushArgs A, int nb) {
-  const uint32_t m = min(*A.split_count, (uint32_t)nb);
+// The chunks that k_gather_push left in the list, a persistent launch.  The last
+// block to end empties the list for the next push.
+template <int NDIM, int SHAPE, bool DEP, int PM, int WM, bool DENSE>
+__global__ __launch_bounds__(kBlock) void k_push_split(PushArgs A) {
+  const uint32_t m = min(*A.split_count, A.split_cap);
   if (m == 0) return;  // the same for every block: the list is empty and stays so
   for (uint32_t i = blockIdx.x; i < m; i += gridDim.x) {
     const int2 e = A.split_list[i];
-    push_chunk<NDIM, SHAPE, DEP, PM, PPT, WM, Split::kPasses>(A, e.x, e.y, nb);
+    push_split_chunk<NDIM, SHAPE, DEP, PM, WM, DENSE>(A, e.x, e.y, 0, false);
     __syncthreads();  // the next chunk reuses the LDS
   }
   __syncthreads();
@@ -1597,28 +1661,26 @@ __global__ void k_order_write(int R, int nchunks, OrderWs W) {
     if (p + m < nchunks) W.order[p + m] = f + m;
 }
 
-// Stand-alone deposit at x - half_dt_back v (no push); same lane runs.
-template <int NDIM, int SHAPE, int PPT, int WM>
-__global__ __launch_bounds__(kBlock) void k_deposit(DepArgs A) {
-  constexpr int CN = kBlock * PPT;  // particles per chunk
-  __shared__ __attribute__((aligned(16))) double win[DWin<NDIM, WM>::LEN];
-  __shared__ uint8_t s_wrap[DWin<NDIM, WM>::NB * WM];
-  __shared__ float s_q[kBlock / 64 * Queue<NDIM>::QCAP * Queue<NDIM>::QW];
-  __shared__ int s_c[2];
+// LDS of a block of the deposit.
+template <int NDIM, int WM>
+struct DepLds {
+  double win[DWin<NDIM, WM>::LEN];
+  uint8_t wrap[DWin<NDIM, WM>::NB * WM];
+  float q[kBlock / 64 * Queue<NDIM>::QCAP * Queue<NDIM>::QW];
+};
+
+// The deposit of the chunk [base, end) whose cells S describes.
+template <int NDIM, int SHAPE, int PPT, int WM, class R>
+__device__ __forceinline__ void deposit_passes(const DepArgs& A, int64_t base, int64_t end,
+                                               const Span& S, DepLds<NDIM, WM>& L) {
+  double* win = L.win;
+  uint8_t* s_wrap = L.wrap;
+  float* s_q = L.q;
   const Geo& g = A.g;
-  const int64_t base = (int64_t)xcd_chunk(blockIdx.x, gridDim.x) * CN;
-  const int64_t end = min(base + (int64_t)CN, A.n);
-  if (threadIdx.x == 0) {
-    s_c[0] = A.cell[base];
-    s_c[1] = A.cell[end - 1];
-  }
-  __syncthreads();
-  const Span S = chunk_span<NDIM, WM>(__builtin_amdgcn_readfirstlane(s_c[0]),
-                                      __builtin_amdgcn_readfirstlane(s_c[1]), g);
   const bool wok = S.passes > 0;
   count_path(A.st, wok);
   const WinLds<WM> wl{win, s_wrap};
-  Home<NDIM, SHAPE> H;
+  Home<NDIM, SHAPE, R> H;
   home_clear(H);
   Queue<NDIM> Q;
   Q.base = s_q + (threadIdx.x >> 6) * Queue<NDIM>::QCAP * Queue<NDIM>::QW;
@@ -1628,58 +1690,80 @@ __global__ __launch_bounds__(kBlock) void k_deposit(DepArgs A) {
   int pass = 0;
 #pragma unroll 1
   do {
-  const int c0 = S.begin(pass), span = S.end(pass) - c0, W = span + 5;
-  if (wok) dwin_init<NDIM, WM>(win, s_wrap, W, c0, g);
-  __syncthreads();
-#pragma unroll 1
-  for (int h = 0; h < PPT; h += 4) {
-    const int64_t b4 = lb + h * 64;
-    // the same on all lanes of the wavefront (see load_group)
-    const bool full = A.vec && wb + h * 64 + 256 <= end;
-    Group<NDIM> G;
-    load_group<NDIM>(A, b4, end, full, true, G);
-    const int* ca = G.ca;
-    const float *px = G.px, *py = G.py, *pz = G.pz, *ux = G.ux, *uy = G.uy, *uz = G.uz;
-    const float* pw = G.pw;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      int a = ca[q];
-      bool live = b4 + q < end;
-      if (live && (unsigned)a >= (unsigned)g.ncell) {
-        if (pass == 0) raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
-        live = false;
-      }
-      if (!live) a = 0;
-      const int rel = a - c0;
-      const bool inwin = wok && rel >= 0 && rel <= span;
-      // another pass takes it (see push_chunk)
-      if (S.passes > 1 && !inwin && (pass > 0 || (a >= S.first && a <= S.last))) live = false;
-      int i = 0, j = 0, k = 0, mx = 0, my = 0, mz = 0;
-      float x = px[q], y = py[q], z = NDIM == 3 ? pz[q] : 0.f;
-      if (live) {
-        decompose(a, g, i, j, k);
-        float xm = fmaf(ux[q], A.bx, x), ym = fmaf(uy[q], A.by, y);
-        float zm = NDIM == 3 ? fmaf(uz[q], A.bz, z) : 0.f;
-        if (renorm_fast(xm, mx) && renorm_fast(ym, my) && (NDIM == 2 || renorm_fast(zm, mz))) {
-          x = xm;
-          y = ym;
-          z = zm;
-        } else {
-          mx = my = mz = 0;
-        }
-      }
-      deposit_particle<NDIM, SHAPE>(H, Q, wl, live, inwin, rel, i, j, k, mx, my, mz, x, y, z,
-                                    A.qV * pw[q], ux[q], uy[q], uz[q], g, A.acc);
-    }
-    home_flush(H, wl);
-  }
-  queue_drain<NDIM, SHAPE>(Q, wl);
-  if (wok) {
+    const int c0 = S.begin(pass), span = S.end(pass) - c0, W = span + 5;
+    if (wok) dwin_init<NDIM, WM>(win, s_wrap, W, c0, g);
     __syncthreads();
-    dwin_flush<NDIM, WM>(win, W, c0, g, A.acc);
-    if (pass + 1 < S.passes) __syncthreads();  // the next pass fills the window again
-  }
+#pragma unroll 1
+    for (int h = 0; h < PPT; h += 4) {
+      const int64_t b4 = lb + h * 64;
+      // the same on all lanes of the wavefront (see load_group)
+      const bool full = A.vec && wb + h * 64 + 256 <= end;
+      Group<NDIM> G;
+      load_group<NDIM>(A, b4, end, full, true, G);
+      const int* ca = G.ca;
+      const float *px = G.px, *py = G.py, *pz = G.pz, *ux = G.ux, *uy = G.uy, *uz = G.uz;
+      const float* pw = G.pw;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        int a = ca[q];
+        bool live = b4 + q < end;
+        if (live && (unsigned)a >= (unsigned)g.ncell) {
+          if (pass == 0) raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
+          live = false;
+        }
+        if (!live) a = 0;
+        const int rel = a - c0;
+        const bool inwin = wok && rel >= 0 && rel <= span;
+        // another pass takes it (see push_chunk)
+        if (S.passes > 1 && !inwin && (pass > 0 || (a >= S.first && a <= S.last))) live = false;
+        int i = 0, j = 0, k = 0, mx = 0, my = 0, mz = 0;
+        float x = px[q], y = py[q], z = NDIM == 3 ? pz[q] : 0.f;
+        if (live) {
+          decompose(a, g, i, j, k);
+          float xm = fmaf(ux[q], A.bx, x), ym = fmaf(uy[q], A.by, y);
+          float zm = NDIM == 3 ? fmaf(uz[q], A.bz, z) : 0.f;
+          if (renorm_fast(xm, mx) && renorm_fast(ym, my) && (NDIM == 2 || renorm_fast(zm, mz))) {
+            x = xm;
+            y = ym;
+            z = zm;
+          } else {
+            mx = my = mz = 0;
+          }
+        }
+        deposit_particle<NDIM, SHAPE>(H, Q, wl, live, inwin, rel, i, j, k, mx, my, mz, x, y, z,
+                                      A.qV * pw[q], ux[q], uy[q], uz[q], g, A.acc);
+      }
+      home_flush(H, wl);
+    }
+    queue_drain<NDIM, SHAPE>(Q, wl);
+    if (wok) {
+      __syncthreads();
+      dwin_flush<NDIM, WM>(win, W, c0, g, A.acc);
+      if (pass + 1 < S.passes) __syncthreads();  // the next pass fills the window again
+    }
   } while (++pass < S.passes);
+}
+
+// Stand-alone deposit at x - half_dt_back v (no push); same lane runs.  DENSE as
+// for the push.
+template <int NDIM, int SHAPE, int PPT, int WM, bool DENSE>
+__global__ __launch_bounds__(kBlock) void k_deposit(DepArgs A) {
+  constexpr int CN = kBlock * PPT;  // particles per chunk
+  __shared__ __attribute__((aligned(16))) DepLds<NDIM, WM> lds;
+  __shared__ int s_c[2];
+  const int64_t base = (int64_t)xcd_chunk(blockIdx.x, gridDim.x) * CN;
+  const int64_t end = min(base + (int64_t)CN, A.n);
+  if (threadIdx.x == 0) {
+    s_c[0] = A.cell[base];
+    s_c[1] = A.cell[end - 1];
+  }
+  __syncthreads();
+  const Span S = chunk_span<NDIM, WM>(__builtin_amdgcn_readfirstlane(s_c[0]),
+                                      __builtin_amdgcn_readfirstlane(s_c[1]), A.g);
+  if (DENSE && S.passes <= 1)
+    deposit_passes<NDIM, SHAPE, PPT, WM, float>(A, base, end, S, lds);
+  else
+    deposit_passes<NDIM, SHAPE, PPT, WM, SparseSum>(A, base, end, S, lds);
 }
 
 __global__ void k_zero(float* __restrict__ a, int64_t na, float* __restrict__ b, int64_t nb) {
@@ -1805,13 +1889,22 @@ void with_plan(const Plan& P, F f) {
   }
 }
 
+// Whether a plan is that of a dense store, whose chunks took one window at any
+// time: their home sums are float.
+template <int NDIM, int PPT, int WM>
+constexpr bool plan_dense() {
+  return NDIM == 2 ? PPT == 12 : WM == 24;
+}
+
 template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM>
 void launch_push_kernels(hipStream_t s, const PushArgs& A) {
+  constexpr bool DENSE = plan_dense<NDIM, PPT, WM>();
+  using R = typename std::conditional<DENSE, float, SparseSum>::type;
   const int nb = (int)ceil_div(A.n, kBlock * PPT);
-  hipLaunchKernelGGL((k_gather_push<NDIM, SHAPE, DEP, PM, PPT, WM>), dim3(nb), dim3(kBlock), 0, s,
-                     A);
-  hipLaunchKernelGGL((k_push_split<NDIM, SHAPE, DEP, PM, PPT, WM>), dim3(std::min(nb, 256)),
-                     dim3(kBlock), 0, s, A, nb);
+  hipLaunchKernelGGL((k_gather_push<NDIM, SHAPE, DEP, PM, PPT, WM, R>), dim3(nb), dim3(kBlock), 0,
+                     s, A);
+  hipLaunchKernelGGL((k_push_split<NDIM, SHAPE, DEP, PM, WM, DENSE>), dim3(std::min(nb, 256)),
+                     dim3(kBlock), 0, s, A);
 }
 
 template <int NDIM, int SHAPE, bool DEP>
@@ -1914,8 +2007,10 @@ PushArgs push_args(hvpic_ctx* c, const hvpic_particles* in, const int32_t* perm,
   A.iw = in->w;
   A.wo = p->w;
   A.order = nullptr;
+  A.ppt = 0;  // (set with the plan)
   A.split_list = reinterpret_cast<int2*>(c->split_list);
   A.split_count = c->status->split_count;
+  A.split_cap = 0;
   return A;
 }
 
@@ -1936,6 +2031,8 @@ int launch_push(hvpic_ctx* c, const hvpic_particles* in, const int32_t* perm,
   const Plan plan = c->p.ndim == 2 ? particle_plan<2>(p->n, c->ncell)
                                    : particle_plan<3>(p->n, c->ncell);
   const int nblocks = (int)ceil_div(p->n, plan.chunk());
+  A.ppt = plan.ppt;
+  A.split_cap = (uint32_t)nblocks;
   if (c->p.ndim == 3 && cell_start != nullptr && c->chunk_order &&
       (int64_t)c->p.ny * c->p.nz <= 65536) {
     // the chunk order (kernels of their own, outside the push's timing)
@@ -2007,11 +2104,12 @@ void deposit_dispatch(hvpic_ctx* c, const DepArgs& A) {
   const Plan P = particle_plan<NDIM>(A.n, c->ncell);
   const dim3 grid((unsigned)ceil_div(A.n, P.chunk()));
   with_plan<NDIM>(P, [&](auto ppt, auto win) {
+    constexpr bool DENSE = plan_dense<NDIM, ppt.value, win.value>();
     if (c->p.shape == HVPIC_SHAPE_QS)
-      hipLaunchKernelGGL((k_deposit<NDIM, HVPIC_SHAPE_QS, ppt.value, win.value>), grid,
+      hipLaunchKernelGGL((k_deposit<NDIM, HVPIC_SHAPE_QS, ppt.value, win.value, DENSE>), grid,
                          dim3(kBlock), 0, c->stream, A);
     else
-      hipLaunchKernelGGL((k_deposit<NDIM, HVPIC_SHAPE_NGP, ppt.value, win.value>), grid,
+      hipLaunchKernelGGL((k_deposit<NDIM, HVPIC_SHAPE_NGP, ppt.value, win.value, DENSE>), grid,
                          dim3(kBlock), 0, c->stream, A);
   });
 }
@@ -2062,16 +2160,37 @@ int launch_deposit(hvpic_ctx* c, const hvpic_particles* p, const int32_t* cell_s
 
 namespace {
 
-template <int SHAPE, int PPT>
+template <int SHAPE, int PPT, class R>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
 void k_gather_push_batch(const PushArgs* __restrict__ tab, const Item* __restrict__ items,
                          int nitems) {
   for_items(nitems, [&](int it) {
     const Item item = items[it];
     const PushArgs A = tab[item.run];
-    push_chunk<2, SHAPE, true, 1, PPT, kWin2, Split::kNever>(A, item.idx, item.idx, item.nb);
+    push_chunk<2, SHAPE, true, 1, PPT, kWin2, R>(A, item.idx, item.idx, item.run, item.nb);
     __syncthreads();  // the next item reuses the LDS
   });
+}
+
+// The chunks of all runs that the batched push left in its list, as
+// k_push_split.
+template <int SHAPE>
+__global__ __launch_bounds__(kBlock) void k_push_split_batch(const PushArgs* __restrict__ tab,
+                                                             const int2* __restrict__ list,
+                                                             uint32_t* count, uint32_t cap) {
+  const uint32_t m = min(count[0], cap);
+  if (m == 0) return;
+  for (uint32_t i = blockIdx.x; i < m; i += gridDim.x) {
+    const int2 e = list[i];
+    const PushArgs A = tab[e.y];
+    push_split_chunk<2, SHAPE, true, 1, kWin2, false>(A, e.x, e.x, 0, false);
+    __syncthreads();
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && atomicAdd(count + 1, 1u) == gridDim.x - 1) {
+    count[0] = 0;
+    count[1] = 0;
+  }
 }
 
 __global__ __launch_bounds__(kMomBlock) void k_moments_out_batch(const MomArgs* __restrict__ tab,
@@ -2086,26 +2205,34 @@ __global__ __launch_bounds__(kMomBlock) void k_moments_out_batch(const MomArgs* 
 }
 
 template <int SHAPE>
-void push_batch_ppt(hipStream_t s, int ppt, const PushArgs* tab, const Item* items, int nitems,
-                    int grid) {
-  if (ppt == 4)
-    hipLaunchKernelGGL((k_gather_push_batch<SHAPE, 4>), dim3(grid), dim3(kBlock), 0, s, tab, items,
-                       nitems);
-  else if (ppt == 8)
-    hipLaunchKernelGGL((k_gather_push_batch<SHAPE, 8>), dim3(grid), dim3(kBlock), 0, s, tab, items,
-                       nitems);
+void push_batch(hipStream_t s, int kind, const PushArgs* tab, const Item* items, int nitems,
+                int grid) {
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, tab, items, nitems);
+  };
+  if (kind == 0)
+    go(k_gather_push_batch<SHAPE, 4, float>);
+  else if (kind == 1)
+    go(k_gather_push_batch<SHAPE, 8, float>);
+  else if (kind == 2)
+    go(k_gather_push_batch<SHAPE, 12, float>);
+  else if (kind == 3)
+    go(k_gather_push_batch<SHAPE, 4, SparseSum>);
   else
-    hipLaunchKernelGGL((k_gather_push_batch<SHAPE, 12>), dim3(grid), dim3(kBlock), 0, s, tab,
-                       items, nitems);
+    go(k_gather_push_batch<SHAPE, 8, SparseSum>);
 }
 
 }  // namespace
 
 size_t ens_push_record(hvpic_ctx* c, const hvpic_particles* in, const int32_t* perm,
                        hvpic_particles* out, const int32_t* cs, const float* E, const float* B,
-                       bool diag, void* dst) {
+                       bool diag, int kind, const EnsSplit& split, void* dst) {
   if (dst) {
-    const PushArgs A = push_args(c, in, perm, out, cs, E, B, diag ? c->push_part : nullptr);
+    PushArgs A = push_args(c, in, perm, out, cs, E, B, diag ? c->push_part : nullptr);
+    A.ppt = kEnsPpt[kind];
+    A.split_list = reinterpret_cast<int2*>(split.list);
+    A.split_count = split.count;
+    A.split_cap = (uint32_t)split.cap;
     memcpy(dst, &A, sizeof(A));
   }
   return sizeof(PushArgs);
@@ -2122,16 +2249,32 @@ size_t ens_moments_record(hvpic_ctx* c, float* n, float* J, int nparts, double* 
 
 int ens_moment_blocks(const hvpic_ctx* c) { return moment_blocks(c); }
 
-int ens_plain_ppt(int64_t n, int64_t ncell) { return particle_plan<2>(n, ncell).ppt; }
+int ens_push_kind(int64_t n, int64_t ncell, int choice) {
+  const int plan = particle_plan<2>(n, ncell).ppt;
+  return kEnsPpt[choice] <= plan ? choice : (plan == 4 ? 3 : 4);
+}
 
-int ens_launch_push(hipStream_t s, int shape, int ppt, const void* tab, const Item* items,
+int ens_launch_push(hipStream_t s, int shape, int kind, const void* tab, const Item* items,
                     int nitems, int grid) {
   if (nitems == 0) return HVPIC_OK;
   const PushArgs* t = static_cast<const PushArgs*>(tab);
   if (shape == HVPIC_SHAPE_QS)
-    push_batch_ppt<HVPIC_SHAPE_QS>(s, ppt, t, items, nitems, grid);
+    push_batch<HVPIC_SHAPE_QS>(s, kind, t, items, nitems, grid);
   else
-    push_batch_ppt<HVPIC_SHAPE_NGP>(s, ppt, t, items, nitems, grid);
+    push_batch<HVPIC_SHAPE_NGP>(s, kind, t, items, nitems, grid);
+  return hipGetLastError() == hipSuccess ? HVPIC_OK : HVPIC_EHIP;
+}
+
+int ens_launch_push_split(hipStream_t s, int shape, const void* tab, const EnsSplit& split) {
+  const PushArgs* t = static_cast<const PushArgs*>(tab);
+  const int2* list = reinterpret_cast<const int2*>(split.list);
+  const dim3 grid((unsigned)std::min<int64_t>(split.cap, 256));
+  if (shape == HVPIC_SHAPE_QS)
+    hipLaunchKernelGGL(k_push_split_batch<HVPIC_SHAPE_QS>, grid, dim3(kBlock), 0, s, t, list,
+                       split.count, (uint32_t)split.cap);
+  else
+    hipLaunchKernelGGL(k_push_split_batch<HVPIC_SHAPE_NGP>, grid, dim3(kBlock), 0, s, t, list,
+                       split.count, (uint32_t)split.cap);
   return hipGetLastError() == hipSuccess ? HVPIC_OK : HVPIC_EHIP;
 }
 

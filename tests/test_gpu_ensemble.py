@@ -264,3 +264,40 @@ def test_ensemble_full_size(mods):
         assert flags & (H.FLAG_BAD_INPUT | H.FLAG_NONFINITE) == 0, (r, flags)
     print(f"ensemble: {len(specs)} runs, {n_total} ions, equal to the plain runs after "
           f"3 graph-replayed steps", flush=True)
+
+
+def _banded(seed, side, ppc, thin):
+    """A run whose rows come in bands of three dense ones and three with `thin`
+    times their density (ppc ions per cell on average)."""
+    cfg, parts, B = W.ensemble_run(dict(seed=seed, side=side, ppc=int(2.0 * ppc / (1.0 + thin)), amp=0.02, te_ratio=0.5,
+                                        vth=0.5), shape=W.SHAPE_QS)
+    rng = np.random.Generator(np.random.PCG64(seed))
+    row = parts["cell"] // cfg.nx
+    keep = ((row // 3) % 2 == 0) | (rng.uniform(size=row.size) < thin)
+    return cfg, {k: np.ascontiguousarray(v[keep]) for k, v in parts.items()}, B
+
+
+def test_uneven_runs_match_separate_runs(mods):
+    """Runs with chunks that need several windows of cells (sparse bands in a
+    dense run, runs sparse all over, one whose chunks span more than the
+    passes cover) equal the same runs stepped alone, bit for bit, and a graph
+    replays them."""
+    H, S = mods
+    announce("ensemble_uneven")
+    runs = [_banded(31, 70, 90, 0.05), _banded(32, 97, 64, 0.1), _banded(33, 50, 30, 0.2), _banded(34, 120, 6, 0.3)]
+    runs.append(W.ensemble_run(dict(seed=35, side=60, ppc=5, amp=0.02, te_ratio=0.5, vth=0.5)))
+    sparse = W.ensemble_run(dict(seed=36, side=200, ppc=1, amp=0.02, te_ratio=0.5, vth=0.5))
+    runs.append((sparse[0], {k: np.ascontiguousarray(v[::2]) for k, v in sparse[1].items()}, sparse[2]))
+    ens = S.Ensemble(_sims(S, runs))
+    plain = _sims(S, runs)
+    scratch = torch.zeros(1 << 20, device="cuda")
+    for step in range(6):
+        if step == 3:
+            ens.capture(True)
+        ens.step()
+        scratch.add_(1.0)
+        for g in plain:
+            g.step()
+        for r, g in enumerate(plain):
+            _same_state(ens, r, g, exact=True)
+            assert torch.equal(ens.state(r)["push_diag"], g.push_diag), (step, r)

@@ -108,3 +108,52 @@ def test_uneven_density(H, ndim, ppc, thin, shape, mapped):
     torch.cuda.synchronize()
     assert rel_l2(n_mid.cpu().numpy(), rn) < 1e-5
     assert rel_l2(J_mid.cpu().numpy(), rJ) < 1e-5
+
+
+# plans and chunks whose ions went to the FP64 accumulators one by one before the chunks were cut to the windows:
+# 1024 and 2048 ions a block, windows of 40 and 64 cells, several passes, more passes than a block makes
+SPARSE = [(2, 30.0, 1.0), (2, 45.0, 1.0), (2, 90.0, 0.05), (2, 5.0, 1.0), (2, 0.4, 1.0), (3, 45.0, 1.0), (3, 24.0, 1.0),
+          (3, 70.0, 0.05), (3, 4.0, 1.0), (3, 0.4, 1.0)]
+
+
+@pytest.mark.parametrize("ndim,ppc,thin", SPARSE)
+@pytest.mark.parametrize("call", ["deposit", "push", "push_perm"])
+def test_sparse_sums_are_rounded_once(H, ndim, ppc, thin, call):
+    """Weights with all 24 bits in use, velocities +-1 and +-1/2 and no fields:
+    every product is exact in FP32 and every sum in FP64, so the moments of
+    sparse stores are the exact sums rounded to FP32, bit for bit.  (Of a store
+    with thin bands the middle row of each band is looked at.)"""
+    announce("sparse_sums", ndim, ppc, thin, call)
+    dims = dict(nx=61, ny=24, nz=1) if ndim == 2 else dict(nx=19, ny=12, nz=6)
+    if ppc < 1:
+        dims["ny"] *= 4
+    cfg = W.Config(name="sums", ndim=ndim, dx=1.0, dy=1.0, dz=1.0, dt=0.05, nsub=3, shape=W.SHAPE_NGP, te=0.2, eta=1e-3, **dims)
+    rng = np.random.Generator(np.random.PCG64(int(10 * ppc) + ndim))
+    rate = np.full(cfg.ncell, 2.0 * ppc / (1.0 + thin))
+    thinned = (np.arange(cfg.ncell) // cfg.nx // 3) % 2 == 1
+    rate[thinned] *= thin
+    cell = np.repeat(np.arange(cfg.ncell), rng.poisson(rate)).astype(np.int32)
+    n = cell.size
+    parts = {"cell": cell}
+    for k in ["ox", "oy"] + (["oz"] if ndim == 3 else []):
+        parts[k] = rng.uniform(-0.5, 0.5, n).astype(np.float32)
+    for k in ("ux", "uy", "uz"):
+        parts[k] = rng.choice(np.array([-1.0, -0.5, 0.5, 1.0], np.float32), n)
+    parts["w"] = (1.0 + rng.integers(0, 1 << 23, n) * 2.0 ** -23).astype(np.float32)
+    sums = [np.bincount(cell, parts["w"].astype(np.float64) * f, cfg.ncell) for f in (1.0, parts["ux"], parts["uy"], parts["uz"])]
+    ctx = H.Context(cfg, n)
+    cs = dev(np.concatenate([[0], np.cumsum(np.bincount(cell, minlength=cfg.ncell))]), np.int32)
+    nd, Jd = torch.zeros(cfg.ncell, device="cuda"), torch.zeros((3, cfg.ncell), device="cuda")
+    zero = torch.zeros((3, cfg.ncell), device="cuda")
+    p, q = H.Particles.from_numpy(parts, ndim), H.Particles(ndim, n)
+    if call == "deposit":
+        H.hvpic_deposit(ctx.ctx, p, cs, 0.0, nd, Jd)
+    elif call == "push":
+        H.hvpic_gather_push(ctx.ctx, p, cs, zero, zero, nd, Jd)
+    else:
+        H.hvpic_gather_push_perm(ctx.ctx, p, torch.arange(n, dtype=torch.int32, device="cuda"), q, cs, zero, zero, nd, Jd)
+    torch.cuda.synchronize()
+    look = np.arange(cfg.ncell) // cfg.nx % 6 == 4 if thin < 1 else np.ones(cfg.ncell, bool)
+    got = [nd.cpu().numpy()] + list(Jd.cpu().numpy())
+    for g, s in zip(got, sums):
+        assert np.array_equal(g[look], s[look].astype(np.float32))

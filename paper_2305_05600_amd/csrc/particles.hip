@@ -908,9 +908,10 @@ __device__ __forceinline__ void load_group(const Args& A, int64_t b4, int64_t en
 
 // The same through the gather map A.perm (16-byte aligned, like the
 // destination store): four map entries, then element loads of the source.
+// count: bad entries are counted (once, however many passes load them).
 template <int NDIM, int PM>
 __device__ __forceinline__ void load_group_perm(const PushArgs& A, int64_t b4, int64_t end,
-                                                bool full, Group<NDIM>& G) {
+                                                bool full, bool count, Group<NDIM>& G) {
   int src[4];
   if (full)
     load4v(A.perm, b4, src);
@@ -925,7 +926,7 @@ __device__ __forceinline__ void load_group_perm(const PushArgs& A, int64_t b4, i
     src[q] = (uint32_t)src[q] >= (uint32_t)A.nsrc ? 0 : src[q];
   }
   if (__ballot(bad) != 0) {
-    if (bad) raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
+    if (bad && count) raise_flag(A.st, HVPIC_FLAG_BAD_INPUT, &A.st->bad_input);
   }
   if (PM == 1) {
     // one 32-bit byte offset per element shared by all arrays, whose bases
@@ -1257,14 +1258,14 @@ __device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int
   // a step of the wavefront is all in range, or it takes element-wise accesses
   auto step_full = [&](int h) { return A.vec && wb + h * 64 + 256 <= end; };
   Group<NDIM> cur;
-  auto load_step = [&](int h) {
+  auto load_step = [&](int h, bool count) {
     if (PM != 0)
-      load_group_perm<NDIM, PM>(A, lb + h * 64, end, step_full(h), cur);
+      load_group_perm<NDIM, PM>(A, lb + h * 64, end, step_full(h), count, cur);
     else
       load_group<NDIM>(A, lb + h * 64, end, step_full(h), wq, cur);
   };
 
-  load_step(0);
+  load_step(0, true);
   const bool wok = SPLIT ? S.passes > 0 : S.passes == 1;
 
   float dK = 0.f, dP0 = 0.f, dP1 = 0.f, dP2 = 0.f;
@@ -1282,7 +1283,7 @@ __device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int
   do {
     const int c0 = SPLIT ? S.begin(pass) : S.first;
     const int span = (SPLIT ? S.end(pass) : S.last) - c0, W = span + 5;
-    if (SPLIT && pass > 0) load_step(0);
+    if (SPLIT && pass > 0) load_step(0, false);
     if (wok) {
       gwin_fill<NDIM, SHAPE>(reinterpret_cast<float*>(gw), span + 1, c0, g, A.E, A.B);
       if (DEP) dwin_init<NDIM, WM>(win, s_wrap, W, c0, g);
@@ -1431,7 +1432,7 @@ __device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int
       if (PM != 0) store4(A.wo, b4, end, full, keep, pw);
       if (SPLIT && PM == 0) done |= keep << h;
       // the next step's particles arrive during the flushes below
-      if (h + 4 < ppt) load_step(h + 4);
+      if (h + 4 < ppt) load_step(h + 4, !SPLIT || pass == 0);
       if (DEP) home_flush(H, wl);
       if (cnt_on) count_flush<NDIM>(chome, nstay, s_cnt);
     }

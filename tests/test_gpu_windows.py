@@ -157,3 +157,25 @@ def test_sparse_sums_are_rounded_once(H, ndim, ppc, thin, call):
     got = [nd.cpu().numpy()] + list(Jd.cpu().numpy())
     for g, s in zip(got, sums):
         assert np.array_equal(g[look], s[look].astype(np.float32))
+
+
+def test_bad_map_entry_is_counted_once(H):
+    """A map entry outside the store, in a chunk that takes several passes:
+    flagged, and counted once (in the status block at the workspace's start)."""
+    announce("bad_map_entry")
+    cfg = _cfg(2, W.SHAPE_QS)
+    parts, E, B, _ = _uneven(cfg, 950, 90.0, 0.05)
+    n = parts["cell"].size
+    row = parts["cell"] // cfg.nx
+    at = int(np.flatnonzero(row == 4)[0])  # the middle of a thin band
+    perm = np.arange(n, dtype=np.int32)
+    perm[at] = n + 5
+    ctx = H.Context(cfg, n)
+    p, q = H.Particles.from_numpy(parts, 2), H.Particles(2, n)
+    n_mid, J_mid = torch.zeros(cfg.ncell, device="cuda"), torch.zeros((3, cfg.ncell), device="cuda")
+    H.hvpic_gather_push_perm(ctx.ctx, p, dev(perm, np.int32), q, None, dev(E), dev(B), n_mid, J_mid)
+    torch.cuda.synchronize()
+    # flags, unused, moved_gt1, nonfinite, floor_hits, bad_input
+    assert int(ctx.workspace[:40].view(torch.int64)[4]) == 1
+    flags, _ = H.hvpic_sync_status(ctx.ctx)
+    assert flags & H.FLAG_BAD_INPUT

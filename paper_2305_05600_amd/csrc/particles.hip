@@ -1545,18 +1545,25 @@ void k_gather_push(PushArgs A) {
                                                gridDim.x);
 }
 
-// The chunks that k_gather_push left in the list, a persistent launch.  The last
-// block to end empties the list for the next push.
+// nb = 0: the chunks that k_gather_push left in the list, a persistent launch;
+// the last block to end empties the list for the next push.  Otherwise all nb
+// chunks of a small store, a block each, in place of both kernels.
 template <int NDIM, int SHAPE, bool DEP, int PM, int WM, bool DENSE>
-__global__ __launch_bounds__(kBlock) void k_push_split(PushArgs A) {
-  const uint32_t m = min(*A.split_count, A.split_cap);
+__global__ __launch_bounds__(kBlock) void k_push_split(PushArgs A, int nb) {
+  const uint32_t m = nb > 0 ? (uint32_t)nb : min(*A.split_count, A.split_cap);
   if (m == 0) return;  // the same for every block: the list is empty and stays so
   for (uint32_t i = blockIdx.x; i < m; i += gridDim.x) {
-    const int2 e = A.split_list[i];
-    push_split_chunk<NDIM, SHAPE, DEP, PM, WM, DENSE>(A, e.x, e.y, 0, false);
+    int2 e;  // chunk and slot
+    if (nb > 0) {
+      e.y = xcd_chunk((int)i, nb);
+      e.x = ordered_chunk(A, e.y, nb);
+    } else {
+      e = A.split_list[i];
+    }
+    push_split_chunk<NDIM, SHAPE, DEP, PM, WM, DENSE>(A, e.x, e.y, nb, nb > 0);
     __syncthreads();  // the next chunk reuses the LDS
   }
-  __syncthreads();
+  if (nb > 0) return;
   if (threadIdx.x == 0 && atomicAdd(A.split_count + 1, 1u) == gridDim.x - 1) {
     A.split_count[0] = 0;
     A.split_count[1] = 0;
@@ -1899,15 +1906,27 @@ constexpr bool plan_dense() {
   return NDIM == 2 ? PPT == 12 : WM == 24;
 }
 
+// The push of a store: all its chunks, then those that need several windows.  A
+// store of no more chunks than the GPU has CUs takes both in one launch of the
+// second kernel, whose registers cost it nothing with one block per CU; an empty
+// second launch would take 4.5 to 6.5 us, and the host's time for it (32 x 32
+// cells of 64 ions, whole steps: 105 to 108 us with two launches, 91 to 102 with one).
+constexpr int kCUs = 256;
+
 template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM>
 void launch_push_kernels(hipStream_t s, const PushArgs& A) {
   constexpr bool DENSE = plan_dense<NDIM, PPT, WM>();
   using R = typename std::conditional<DENSE, float, SparseSum>::type;
   const int nb = (int)ceil_div(A.n, kBlock * PPT);
+  if (nb <= kCUs) {
+    hipLaunchKernelGGL((k_push_split<NDIM, SHAPE, DEP, PM, WM, DENSE>), dim3(nb), dim3(kBlock), 0,
+                       s, A, nb);
+    return;
+  }
   hipLaunchKernelGGL((k_gather_push<NDIM, SHAPE, DEP, PM, PPT, WM, R>), dim3(nb), dim3(kBlock), 0,
                      s, A);
   hipLaunchKernelGGL((k_push_split<NDIM, SHAPE, DEP, PM, WM, DENSE>), dim3(std::min(nb, 256)),
-                     dim3(kBlock), 0, s, A);
+                     dim3(kBlock), 0, s, A, 0);
 }
 
 template <int NDIM, int SHAPE, bool DEP>

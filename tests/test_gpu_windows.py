@@ -16,7 +16,8 @@ import pytest
 
 import oracle as O
 from paper_2305_05600_amd import workloads as W
-from tests.helpers import announce, compare_particles, drop_push_straddlers, rel_l2
+from tests import graph_nodes
+from tests.helpers import announce, compare_particles, deposit_point_straddlers, drop_push_straddlers, rel_l2
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -179,3 +180,106 @@ def test_bad_map_entry_is_counted_once(H):
     assert int(ctx.workspace[:40].view(torch.int64)[4]) == 1
     flags, _ = H.hvpic_sync_status(ctx.ctx)
     assert flags & H.FLAG_BAD_INPUT
+
+
+def _banded(cfg, seed, ppc, thin):
+    """As _uneven, the straddlers looked for on a copy (the oracle's push moves the cells of the store that it is given)."""
+    _, parts, B = W.random_box(seed, cfg, 2.0 * ppc / (1.0 + thin), vmax_cells=0.9)
+    rng = np.random.Generator(np.random.PCG64(seed + 1))
+    keep = ((parts["cell"] // cfg.nx // 3) % 2 == 0) | (rng.uniform(size=parts["cell"].size) < thin)
+    parts = {k: np.ascontiguousarray(v[keep]) for k, v in parts.items()}
+    E = W.random_field(seed + 2, cfg, 0.3)
+    ref = {k: v.copy() for k, v in O.particles64(parts).items()}
+    O.push(cfg, ref, E, B)
+    near = deposit_point_straddlers(cfg, ref, 0.0) | deposit_point_straddlers(cfg, ref, 0.5 * cfg.dt)
+    parts = {k: v[~near] for k, v in parts.items()}
+    perm, cs = O.sort(cfg, parts["cell"])
+    return {k: np.ascontiguousarray(v[perm]) for k, v in parts.items()}, E, B, cs
+
+
+def _passes(cfg, cell):
+    """Window passes of every chunk of a sorted store, and the number of chunks (the library's plan, in numpy)."""
+    ppc = cell.size / cfg.ncell
+    if cfg.ndim == 2:
+        chunk, win = (3072 if ppc >= 60 else 2048 if ppc >= 40 else 1024), 64
+    else:
+        chunk, win = 1024, (24 if ppc >= 56 else 40 if ppc >= 31 else 64)
+    first = np.arange(0, cell.size, chunk)
+    cells = cell[np.minimum(first + chunk, cell.size) - 1] - cell[first] + 1
+    return -(-cells // (win - 4)), first.size
+
+
+# boxes of more chunks than the GPU has CUs, whose push takes two kernels: per plan one with chunks of one and of several
+# windows, and in 2D and 3D one with chunks of too many
+LARGE = [(2, (183, 60, 1), 90.0, 0.05), (2, (183, 72, 1), 45.0, 0.05), (2, (183, 60, 1), 30.0, 0.05), (2, (640, 640, 1), 0.8, 1.0),
+         (3, (19, 24, 12), 70.0, 0.05), (3, (19, 24, 15), 45.0, 0.05), (3, (19, 30, 24), 24.0, 0.05), (3, (64, 80, 80), 0.8, 1.0)]
+
+
+@pytest.mark.parametrize("ndim,dims,ppc,thin", LARGE)
+@pytest.mark.parametrize("mapped", [False, True])
+def test_two_kernels_of_larger_stores(H, ndim, dims, ppc, thin, mapped):
+    announce("larger_stores", ndim, dims, ppc, thin, mapped)
+    cfg = _cfg(ndim, W.SHAPE_QS).replace(nx=dims[0], ny=dims[1], nz=dims[2])
+    parts, E, B, cs0 = _banded(cfg, 970 + int(ppc), ppc, thin)
+    passes, chunks = _passes(cfg, parts["cell"])
+    assert chunks > 256
+    if ppc < 1:
+        assert (passes > 16).any()  # (more than a block makes: global accesses)
+    else:
+        assert (passes == 1).any() and (passes > 1).any() and passes.max() <= 16
+    n = parts["cell"].size
+    ctx = H.Context(cfg, n)
+    cs_prev, cs = dev(cs0, np.int32), torch.zeros(cfg.ncell + 1, dtype=torch.int32, device="cuda")
+    n_mid, J_mid = torch.full((cfg.ncell,), 7.0, device="cuda"), torch.full((3, cfg.ncell), 7.0, device="cuda")
+    diag = torch.zeros(4, dtype=torch.float64, device="cuda")
+    ref = {k: v.copy() for k, v in O.particles64(parts).items()}
+    rd, st = O.push(cfg, ref, E, B)
+    rn, rJ = O.deposit(cfg, ref, 0.5 * cfg.dt)
+    rperm, rcs = O.sort(cfg, ref["cell"])
+    p, q = H.Particles.from_numpy(parts, ndim), H.Particles(ndim, n)
+    H.hvpic_path_stats(ctx.ctx)
+    for again in range(2):  # (the list of the second kernel is empty again after the first time)
+        if mapped:
+            perm = torch.arange(n, dtype=torch.int32, device="cuda")
+            H.hvpic_gather_push_perm(ctx.ctx, p, perm, q, cs_prev, dev(E), dev(B), n_mid, J_mid, diag)
+            H.hvpic_sort_perm(ctx.ctx, q, cs_prev, perm, cs)
+            torch.cuda.synchronize()
+            assert np.array_equal(perm.cpu().numpy(), rperm)
+            pushed = q.to_numpy()
+        else:
+            p = H.Particles.from_numpy(parts, ndim)
+            H.hvpic_gather_push(ctx.ctx, p, cs_prev, dev(E), dev(B), n_mid, J_mid, diag)
+            H.hvpic_sort(ctx.ctx, p, q, cs_prev, cs)
+            pushed, ordered = p.to_numpy(), q.to_numpy()
+            for k in pushed:
+                assert np.array_equal(ordered[k], pushed[k][rperm]), k
+        flags, counts = H.hvpic_sync_status(ctx.ctx)
+        assert flags == 0 and counts[0] == st.moved_gt1 == 0
+        win, glob = H.hvpic_path_stats(ctx.ctx)
+        assert win + glob == chunks and (glob > 0) == (ppc < 1)
+        compare_particles(cfg, pushed, ref, band=0.0)
+        assert np.array_equal(cs.cpu().numpy(), rcs)
+        assert rel_l2(n_mid.cpu().numpy(), rn) < 1e-5
+        assert rel_l2(J_mid.cpu().numpy(), rJ) < 1e-5
+        assert np.allclose(diag.cpu().numpy(), rd, rtol=1e-5, atol=1e-6 * abs(rd[0]))
+    H.hvpic_deposit(ctx.ctx, H.Particles.from_numpy(pushed, ndim), None, 0.5 * cfg.dt, n_mid, J_mid)
+    torch.cuda.synchronize()
+    assert rel_l2(n_mid.cpu().numpy(), rn) < 1e-5
+    assert rel_l2(J_mid.cpu().numpy(), rJ) < 1e-5
+
+
+@pytest.mark.parametrize("ndim,ppc", [(2, 90.0), (2, 30.0), (3, 70.0), (3, 24.0)])
+def test_small_stores_take_one_kernel(H, ndim, ppc):
+    """A push of no more chunks than the GPU has CUs enqueues one kernel, and one more with its moments."""
+    announce("one_kernel", ndim, ppc)
+    cfg = _cfg(ndim, W.SHAPE_QS)
+    _, parts, B = W.random_box(77, cfg, ppc)
+    n = parts["cell"].size
+    order = np.argsort(parts["cell"], kind="stable")
+    p = H.Particles.from_numpy({k: np.ascontiguousarray(v[order]) for k, v in parts.items()}, ndim)
+    ctx = H.Context(cfg, n)
+    E, Bd = torch.zeros((3, cfg.ncell), device="cuda"), dev(B)
+    n_mid, J_mid = torch.zeros(cfg.ncell, device="cuda"), torch.zeros((3, cfg.ncell), device="cuda")
+    stream = lambda s: H.hvpic_set_stream(ctx.ctx, s)  # noqa: E731
+    assert graph_nodes.count(lambda: H.hvpic_gather_push(ctx.ctx, p, None, E, Bd), stream) == 1
+    assert graph_nodes.count(lambda: H.hvpic_gather_push(ctx.ctx, p, None, E, Bd, n_mid, J_mid), stream) == 2

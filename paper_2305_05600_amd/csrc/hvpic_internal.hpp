@@ -344,8 +344,8 @@ int ens_launch_field_diag(hipStream_t s, const void* tab, int nruns);
 // The batched push's chunks: three lengths (particles per lane) that a tuning
 // can choose, and the plain push's for the sparse stores in which the chosen
 // one would not fit the LDS windows (their sums are the plain push's too).
-constexpr int kEnsKinds = 5;
-constexpr int kEnsPpt[kEnsKinds] = {4, 8, 12, 4, 8};
+constexpr int kEnsKinds = 4;
+constexpr int kEnsPpt[kEnsKinds] = {4, 8, 12, 4};
 int ens_push_kind(int64_t n, int64_t ncell, int choice);
 // particles per chunk for ppt particles per lane
 constexpr int ens_chunk(int ppt) { return 256 * ppt; }

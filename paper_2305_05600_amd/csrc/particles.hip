@@ -220,16 +220,25 @@ struct Stencil {
 // in `passes` equal parts of at most WM - 4 cells each (a window has two more
 // columns at either end): one where the chunk fits, more where the density
 // is below what its length was chosen for; none (0) for an unsorted chunk, a
-// grid smaller than a stencil, or one so sparse that kMaxPasses windows do
+// grid smaller than a stencil, or one so sparse that max_passes windows do
 // not cover it.  A pass handles the particles whose cell lies in its part.
-constexpr int kMaxPasses = 16;
+// Each pass loads the chunk again and has its window to clear and to add up, in
+// one block after the other passes: a store of which a few chunks take many has
+// to wait for them.  The limits lie where that costs no more than global
+// accesses, whose atomics are 20 or 28 an ion with QS and 4 with NGP (push and sort
+// of 512 x 512 cells: 1 ion per cell, 17 passes of which some chunks take 16, 284 us,
+// without them 190; 1.5, 12 passes, 260 and 279; NGP 3, 6 passes, 203, without them 134).
+template <int SHAPE>
+constexpr int max_passes() {
+  return SHAPE == HVPIC_SHAPE_QS ? 12 : 4;
+}
 struct Span {
   int first, last, passes, part;
   // cells [c0, c1] of pass t
   __device__ __forceinline__ int begin(int t) const { return first + t * part; }
   __device__ __forceinline__ int end(int t) const { return min(first + (t + 1) * part - 1, last); }
 };
-template <int NDIM, int WM>
+template <int NDIM, int SHAPE, int WM>
 __device__ __forceinline__ Span chunk_span(int first, int last, const Geo& g) {
   Span S{first, last, 0, 0};
   if (first < 0 || last >= g.ncell || last < first || g.nx < 4 || (NDIM == 3 && g.ny < 4)) return S;
@@ -237,7 +246,7 @@ __device__ __forceinline__ Span chunk_span(int first, int last, const Geo& g) {
   if (cells <= WM - 4) {
     S.passes = 1;
     S.part = cells;
-  } else if (cells <= kMaxPasses * (WM - 4)) {
+  } else if (cells <= max_passes<SHAPE>() * (WM - 4)) {
     const int t = (cells + WM - 5) / (WM - 4);
     S.part = (int)((uint32_t)(cells + t - 1) / (uint32_t)t);
     S.passes = (int)((uint32_t)(cells + S.part - 1) / (uint32_t)S.part);
@@ -1455,7 +1464,7 @@ __device__ __forceinline__ void push_passes(const PushArgs& A, int64_t base, int
 // Lines up the chunk [base, end) of the store: the span of its cells, from the
 // first and the last particle's.  Every thread calls it, before the block's
 // other use of its LDS.
-template <int NDIM, int PM, int WM>
+template <int NDIM, int SHAPE, int PM, int WM>
 __device__ __forceinline__ Span chunk_of(const PushArgs& A, int64_t base, int64_t end) {
   __shared__ int s_c[2];
   if (threadIdx.x == 0) {
@@ -1470,8 +1479,8 @@ __device__ __forceinline__ Span chunk_of(const PushArgs& A, int64_t base, int64_
     }
   }
   __syncthreads();
-  return chunk_span<NDIM, WM>(__builtin_amdgcn_readfirstlane(s_c[0]),
-                              __builtin_amdgcn_readfirstlane(s_c[1]), A.g);
+  return chunk_span<NDIM, SHAPE, WM>(__builtin_amdgcn_readfirstlane(s_c[0]),
+                                     __builtin_amdgcn_readfirstlane(s_c[1]), A.g);
 }
 
 // The push of chunk `chunk` of the nb chunks of PPT*kBlock consecutive
@@ -1492,7 +1501,7 @@ __device__ __forceinline__ void push_chunk(const PushArgs& A, int chunk, int slo
   __shared__ __attribute__((aligned(16))) PushLds<NDIM, SHAPE, DEP, WM> lds;
   const int64_t base = (int64_t)chunk * CN;
   const int64_t end = min(base + (int64_t)CN, A.n);
-  const Span S = chunk_of<NDIM, PM, WM>(A, base, end);
+  const Span S = chunk_of<NDIM, SHAPE, PM, WM>(A, base, end);
   if (S.passes > 1) {
     if (threadIdx.x == 0) {
       const uint32_t at = atomicAdd(A.split_count, 1u);
@@ -1514,7 +1523,7 @@ __device__ __forceinline__ void push_split_chunk(const PushArgs& A, int chunk, i
   __shared__ __attribute__((aligned(16))) PushLds<NDIM, SHAPE, DEP, WM> lds;
   const int64_t base = (int64_t)chunk * (kBlock * A.ppt);
   const int64_t end = min(base + (int64_t)(kBlock * A.ppt), A.n);
-  const Span S = chunk_of<NDIM, PM, WM>(A, base, end);
+  const Span S = chunk_of<NDIM, SHAPE, PM, WM>(A, base, end);
   if (DENSE && S.passes <= 1)
     push_passes<NDIM, SHAPE, DEP, PM, WM, false, float>(A, base, end, A.ppt, S, slot, nb, check,
                                                         lds);
@@ -1768,8 +1777,8 @@ __global__ __launch_bounds__(kBlock) void k_deposit(DepArgs A) {
     s_c[1] = A.cell[end - 1];
   }
   __syncthreads();
-  const Span S = chunk_span<NDIM, WM>(__builtin_amdgcn_readfirstlane(s_c[0]),
-                                      __builtin_amdgcn_readfirstlane(s_c[1]), A.g);
+  const Span S = chunk_span<NDIM, SHAPE, WM>(__builtin_amdgcn_readfirstlane(s_c[0]),
+                                             __builtin_amdgcn_readfirstlane(s_c[1]), A.g);
   if (DENSE && S.passes <= 1)
     deposit_passes<NDIM, SHAPE, PPT, WM, float>(A, base, end, S, lds);
   else
@@ -1860,11 +1869,15 @@ Geo make_geo(const hvpic_ctx* c) {
 // windows only if the cells of its chunk fit them; otherwise every particle
 // takes global gathers and up to 28 FP64 global atomics, which took 30 times
 // as long (413 x 257 cells of 36 ions: 3295 us in chunks of 3072, 75 us in
-// chunks of 1024).  So the chunk (2D: 3072, 2048 or 1024 ions) or the window
-// (3D: 24, 40 or 64 cells wide for 1024 ions) follows the ions per cell; the
-// limits lie where the chunk of a uniform store fills its window (2D 3072 /
-// 60 and 2048 / 60 cells, 3D 1024 / 20 and 1024 / 36), with a tenth to spare.
+// chunks of 1024).  So the chunk (2D: 3072 or 1024 ions) or the window (3D: 24,
+// 40 or 64 cells wide for 1024 ions) follows the ions per cell; the limits lie
+// where the chunk of a uniform store fills its window (2D 3072 / 60 cells, 3D
+// 1024 / 20 and 1024 / 36), with a tenth to spare in 3D and in 2D three times the
+// scatter of a chunk's cells.  (2D chunks of 2048 for 40 to 54 ions per cell do
+// not fit 128 registers with FP64 sums: push and sort of 512 x 512 cells of 45
+// ions 407 us, 347 with a quarter fewer wavefronts, 345 in chunks of 1024.)
 // What is locally sparser goes to k_push_split.
+constexpr double kDensePpc2 = 54.0;
 struct Plan {
   int ppt, win;
   int64_t chunk() const { return (int64_t)kBlock * ppt; }
@@ -1873,7 +1886,7 @@ template <int NDIM>
 Plan particle_plan(int64_t n, int64_t ncell) {
   const double ppc = (double)n / (double)ncell;
   if (NDIM == 3) return Plan{kPpt3, ppc >= 56.0 ? 24 : (ppc >= 31.0 ? 40 : 64)};
-  return Plan{ppc >= 60.0 ? 12 : (ppc >= 40.0 ? 8 : 4), kWin2};
+  return Plan{ppc >= kDensePpc2 ? 12 : 4, kWin2};
 }
 
 // Calls f(ppt, win) with the plan's values as compile-time constants.
@@ -1884,8 +1897,6 @@ void with_plan(const Plan& P, F f) {
     const integral_constant<int, kWin2> w;
     if (P.ppt == 4)
       f(integral_constant<int, 4>{}, w);
-    else if (P.ppt == 8)
-      f(integral_constant<int, 8>{}, w);
     else
       f(integral_constant<int, 12>{}, w);
   } else {
@@ -1912,6 +1923,10 @@ constexpr bool plan_dense() {
 // second launch would take 4.5 to 6.5 us, and the host's time for it (32 x 32
 // cells of 64 ions, whole steps: 105 to 108 us with two launches, 91 to 102 with one).
 constexpr int kCUs = 256;
+// Its registers and LDS let two blocks share a CU (with all chunks in the list,
+// 512 x 512 cells of 4 ions, push and sort: 328 us with one, 229 with two, and no
+// better with the registers cut for three).
+constexpr int kSplitBlocks = 2 * kCUs;
 
 template <int NDIM, int SHAPE, bool DEP, int PM, int PPT, int WM>
 void launch_push_kernels(hipStream_t s, const PushArgs& A) {
@@ -1925,8 +1940,8 @@ void launch_push_kernels(hipStream_t s, const PushArgs& A) {
   }
   hipLaunchKernelGGL((k_gather_push<NDIM, SHAPE, DEP, PM, PPT, WM, R>), dim3(nb), dim3(kBlock), 0,
                      s, A);
-  hipLaunchKernelGGL((k_push_split<NDIM, SHAPE, DEP, PM, WM, DENSE>), dim3(std::min(nb, 256)),
-                     dim3(kBlock), 0, s, A, 0);
+  hipLaunchKernelGGL((k_push_split<NDIM, SHAPE, DEP, PM, WM, DENSE>),
+                     dim3(std::min(nb, kSplitBlocks)), dim3(kBlock), 0, s, A, 0);
 }
 
 template <int NDIM, int SHAPE, bool DEP>
@@ -2238,10 +2253,8 @@ void push_batch(hipStream_t s, int kind, const PushArgs* tab, const Item* items,
     go(k_gather_push_batch<SHAPE, 8, float>);
   else if (kind == 2)
     go(k_gather_push_batch<SHAPE, 12, float>);
-  else if (kind == 3)
-    go(k_gather_push_batch<SHAPE, 4, SparseSum>);
   else
-    go(k_gather_push_batch<SHAPE, 8, SparseSum>);
+    go(k_gather_push_batch<SHAPE, 4, SparseSum>);
 }
 
 }  // namespace
@@ -2272,8 +2285,9 @@ size_t ens_moments_record(hvpic_ctx* c, float* n, float* J, int nparts, double* 
 int ens_moment_blocks(const hvpic_ctx* c) { return moment_blocks(c); }
 
 int ens_push_kind(int64_t n, int64_t ncell, int choice) {
-  const int plan = particle_plan<2>(n, ncell).ppt;
-  return kEnsPpt[choice] <= plan ? choice : (plan == 4 ? 3 : 4);
+  // ions per cell from which the chunk fits a window (as for the plain push)
+  constexpr double least[3] = {0.0, 40.0, kDensePpc2};
+  return (double)n >= least[choice] * (double)ncell ? choice : 3;
 }
 
 int ens_launch_push(hipStream_t s, int shape, int kind, const void* tab, const Item* items,
@@ -2290,7 +2304,7 @@ int ens_launch_push(hipStream_t s, int shape, int kind, const void* tab, const I
 int ens_launch_push_split(hipStream_t s, int shape, const void* tab, const EnsSplit& split) {
   const PushArgs* t = static_cast<const PushArgs*>(tab);
   const int2* list = reinterpret_cast<const int2*>(split.list);
-  const dim3 grid((unsigned)std::min<int64_t>(split.cap, 256));
+  const dim3 grid((unsigned)std::min<int64_t>(split.cap, kSplitBlocks));
   if (shape == HVPIC_SHAPE_QS)
     hipLaunchKernelGGL(k_push_split_batch<HVPIC_SHAPE_QS>, grid, dim3(kBlock), 0, s, t, list,
                        split.count, (uint32_t)split.cap);

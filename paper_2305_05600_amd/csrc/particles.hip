@@ -1873,30 +1873,37 @@ Geo make_geo(const hvpic_ctx* c) {
 // 40 or 64 cells wide for 1024 ions) follows the ions per cell; the limits lie
 // where the chunk of a uniform store fills its window (2D 3072 / 60 cells, 3D
 // 1024 / 20 and 1024 / 36), with a tenth to spare in 3D and in 2D three times the
-// scatter of a chunk's cells.  (2D chunks of 2048 for 40 to 54 ions per cell do
+// scatter of a chunk's cells (512 x 512 cells of 55 ions, push and sort: 344 us, 405
+// in chunks of 1024; of 54 ions 407 and 406).  (2D chunks of 2048 for 40 to 55 ions per cell do
 // not fit 128 registers with FP64 sums: push and sort of 512 x 512 cells of 45
 // ions 407 us, 347 with a quarter fewer wavefronts, 345 in chunks of 1024.)
 // What is locally sparser goes to k_push_split.
-constexpr double kDensePpc2 = 54.0;
+constexpr double kDensePpc2 = 55.0;
 struct Plan {
   int ppt, win;
   int64_t chunk() const { return (int64_t)kBlock * ppt; }
 };
+// long2: the stand-alone deposit, which has the registers, takes 2D chunks of 2048
+// where they fit with some to spare (400 x 300 cells of 50 ions: 72 us, 98 in
+// chunks of 1024; a Harris box of 40 on average, whose lobes hold 31, 355 us at its
+// start, 338 in chunks of 1024).
 template <int NDIM>
-Plan particle_plan(int64_t n, int64_t ncell) {
+Plan particle_plan(int64_t n, int64_t ncell, bool long2 = false) {
   const double ppc = (double)n / (double)ncell;
   if (NDIM == 3) return Plan{kPpt3, ppc >= 56.0 ? 24 : (ppc >= 31.0 ? 40 : 64)};
-  return Plan{ppc >= kDensePpc2 ? 12 : 4, kWin2};
+  return Plan{ppc >= kDensePpc2 ? 12 : (long2 && ppc >= 48.0 ? 8 : 4), kWin2};
 }
 
 // Calls f(ppt, win) with the plan's values as compile-time constants.
-template <int NDIM, class F>
+template <int NDIM, bool LONG2, class F>
 void with_plan(const Plan& P, F f) {
   using std::integral_constant;
   if constexpr (NDIM == 2) {
     const integral_constant<int, kWin2> w;
     if (P.ppt == 4)
       f(integral_constant<int, 4>{}, w);
+    else if (LONG2 && P.ppt == 8)
+      f(integral_constant<int, 8>{}, w);
     else
       f(integral_constant<int, 12>{}, w);
   } else {
@@ -1946,7 +1953,7 @@ void launch_push_kernels(hipStream_t s, const PushArgs& A) {
 
 template <int NDIM, int SHAPE, bool DEP>
 void push_dispatch(const Plan& P, hipStream_t s, const PushArgs& A) {
-  with_plan<NDIM>(P, [&](auto ppt, auto win) {
+  with_plan<NDIM, false>(P, [&](auto ppt, auto win) {
     if (!A.perm)
       launch_push_kernels<NDIM, SHAPE, DEP, 0, ppt.value, win.value>(s, A);
     else if (A.off32)
@@ -2138,9 +2145,9 @@ namespace {
 
 template <int NDIM>
 void deposit_dispatch(hvpic_ctx* c, const DepArgs& A) {
-  const Plan P = particle_plan<NDIM>(A.n, c->ncell);
+  const Plan P = particle_plan<NDIM>(A.n, c->ncell, true);
   const dim3 grid((unsigned)ceil_div(A.n, P.chunk()));
-  with_plan<NDIM>(P, [&](auto ppt, auto win) {
+  with_plan<NDIM, true>(P, [&](auto ppt, auto win) {
     constexpr bool DENSE = plan_dense<NDIM, ppt.value, win.value>();
     if (c->p.shape == HVPIC_SHAPE_QS)
       hipLaunchKernelGGL((k_deposit<NDIM, HVPIC_SHAPE_QS, ppt.value, win.value, DENSE>), grid,

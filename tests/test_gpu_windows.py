@@ -201,7 +201,7 @@ def _passes(cfg, cell):
     """Window passes of every chunk of a sorted store, and the number of chunks (the library's plan, in numpy)."""
     ppc = cell.size / cfg.ncell
     if cfg.ndim == 2:
-        chunk, win = (3072 if ppc >= 54 else 1024), 64
+        chunk, win = (3072 if ppc >= 55 else 1024), 64
     else:
         chunk, win = 1024, (24 if ppc >= 56 else 40 if ppc >= 31 else 64)
     first = np.arange(0, cell.size, chunk)

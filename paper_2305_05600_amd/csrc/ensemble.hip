@@ -178,11 +178,13 @@ bool tuning_ok(const hvpic_tuning* t) {
   return true;
 }
 
-// Run r's push: the tuned chunk, but no longer than the plain push takes (one
-// that fits the LDS windows at the run's particles per cell).
+// Run r's push for a tuned chunk: that one, but no longer than the plain push
+// takes (one that fits the LDS windows at the run's particles per cell).
+int push_kind_of(const hvpic_ensemble* e, int r, int choice) {
+  return ens_push_kind(e->runs[r].store[0].n, e->runs[r].ctx->ncell, choice);
+}
 int push_kind(const hvpic_ensemble* e, int r) {
-  return ens_push_kind(e->runs[r].store[0].n, e->runs[r].ctx->ncell,
-                       e->tune.push_chunk[e->pclass[r]]);
+  return push_kind_of(e, r, e->tune.push_chunk[e->pclass[r]]);
 }
 
 // The item lists and both parities' tables for the current tuning, uploaded
@@ -527,6 +529,11 @@ int hvpic_ensemble_autotune(hvpic_ensemble* e, int reps, hvpic_tuning* best_out,
     double best = 1e30;
     int arg = cur.push_chunk[cls];
     for (int g = 0; g < 3 && rc == HVPIC_OK; ++g) {
+      // (a chunk that none of the class's runs takes otherwise than the last)
+      bool same = g > 0;
+      for (int r = 0; r < e->nruns; ++r)
+        if (e->pclass[r] == cls) same &= push_kind_of(e, r, g) == push_kind_of(e, r, g - 1);
+      if (same) continue;
       hvpic_tuning t = cur;
       t.push_chunk[cls] = g;
       double ms = 0.0;

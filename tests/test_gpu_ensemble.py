@@ -301,3 +301,17 @@ def test_uneven_runs_match_separate_runs(mods):
         for r, g in enumerate(plain):
             _same_state(ens, r, g, exact=True)
             assert torch.equal(ens.state(r)["push_diag"], g.push_diag), (step, r)
+
+
+def test_autotune_times_each_chunk_once(mods):
+    """Runs so sparse that the chunks of 2048 and 3072 are the same: two push
+    candidates are timed instead of three (then three grids for each of the
+    three phases, and three tiles), one real step each."""
+    H, S = mods
+    announce("ensemble_autotune_sparse")
+    runs = _runs([dict(seed=41, side=40, ppc=20, amp=0.02, te_ratio=0.5, vth=0.5),
+                  dict(seed=42, side=31, ppc=33, amp=0.02, te_ratio=0.5, vth=0.5)])
+    ens = S.Ensemble(_sims(S, runs))
+    choices, _ = ens.autotune(reps=1)
+    assert ens.steps == 2 + 9 + 3
+    assert choices["push_chunk"][0] in (0, 1)

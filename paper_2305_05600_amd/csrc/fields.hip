@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kBlock) void k_field_ohm_cells(const float* __restr
   if (c >= g.ncell) return;
   const int nc = g.ncell;
   float e[3];
-  if (PREP) prep_at<3>(n, nullptr, Ji, nullptr, 1.0f, 0.0f, c, g, eos, aux);
+  if (PREP) prep_at<3>(n, Ji, c, g, eos, aux);
   ohm_at<3>(BSum<false>{Bsrc, nullptr}, aux, eta, c, g, e);
   E[c] = e[0];
   E[nc + c] = e[1];
@@ -871,8 +871,7 @@ int launch_field_advance_no(hvpic_ctx* c, float* B, const float* n_half, const f
   const unsigned g3 = (unsigned)ceil_div(n3, kBlock);
   // residual test of the proposal
   hipLaunchKernelGGL(k_mid, dim3(g3), blk, 0, s, (const float*)B, Bno, Bmid, n3);
-  hipLaunchKernelGGL((k_field_prep<2>), grid, blk, 0, s, n_half, (const float*)nullptr, J_half,
-                     (const float*)nullptr, 1.0f, 0.0f, g, eos, aux);
+  hipLaunchKernelGGL((k_field_prep<2>), grid, blk, 0, s, n_half, J_half, g, eos, aux);
   hipLaunchKernelGGL((k_field_stage<2>), grid, blk, 0, s, (const float*)Bmid, (const float*)B, T,
                      (float*)nullptr, (float)c->p.dt, eta, g, aux);
   hipLaunchKernelGGL(k_no_resid, grid, blk, 0, s, Bno, (const float*)T, (const float*)B, nc,

@@ -103,39 +103,32 @@ Eos make_eos(const hvpic_ctx* c) {
   return eos;
 }
 
-// Frozen terms of cell c from n_eff = ca*na + cb*nb, J_eff = ca*Ja + cb*Jb.
+// Frozen terms of cell c from the moments n, Ji.
 template <int NDIM>
-__device__ __forceinline__ void prep_at(const float* na, const float* nb, const float* Ja,
-                                        const float* Jb, float ca, float cb, int c, const FGeo& g,
+__device__ __forceinline__ void prep_at(const float* n, const float* Ji, int c, const FGeo& g,
                                         const Eos& eos, const Aux& aux) {
   const int nc = g.ncell;
   int i, j, k;
   fijk(c, g, i, j, k);
   const Nbr nn = neighbours(c, i, j, k, g);
-  auto dens = [&](int q) { return nb ? ca * na[q] + cb * nb[q] : na[q]; };
   auto pres = [&](int q) {
-    return pressure(dens(q), eos.nfloor, eos.te_n0, eos.n0, eos.gam, eos.iso);
+    return pressure(n[q], eos.nfloor, eos.te_n0, eos.n0, eos.gam, eos.iso);
   };
-  const float nf = fmaxf(dens(c), eos.nfloor);
+  const float nf = fmaxf(n[c], eos.nfloor);
   const float inv = (float)(1.0 / (double)nf);
   aux.inv[c] = inv;
-  for (int a = 0; a < 3; ++a) {
-    const float J = Jb ? ca * Ja[a * nc + c] + cb * Jb[a * nc + c] : Ja[a * nc + c];
-    aux.u[a * nc + c] = J * inv;
-  }
+  for (int a = 0; a < 3; ++a) aux.u[a * nc + c] = Ji[a * nc + c] * inv;
   aux.gp[c] = -(pres(nn.xp) - pres(nn.xm)) * g.idx2 * inv;
   aux.gp[nc + c] = -(pres(nn.yp) - pres(nn.ym)) * g.idy2 * inv;
   aux.gp[2 * nc + c] = NDIM == 3 ? -(pres(nn.zp) - pres(nn.zm)) * g.idz2 * inv : 0.f;
 }
 
 template <int NDIM>
-__global__ __launch_bounds__(kBlock) void k_field_prep(const float* __restrict__ na,
-                                                       const float* __restrict__ nb,
-                                                       const float* __restrict__ Ja,
-                                                       const float* __restrict__ Jb, float ca,
-                                                       float cb, FGeo g, Eos eos, Aux aux) {
+__global__ __launch_bounds__(kBlock) void k_field_prep(const float* __restrict__ n,
+                                                       const float* __restrict__ Ji, FGeo g,
+                                                       Eos eos, Aux aux) {
   const int c = blockIdx.x * kBlock + threadIdx.x;
-  if (c < g.ncell) prep_at<NDIM>(na, nb, Ja, Jb, ca, cb, c, g, eos, aux);
+  if (c < g.ncell) prep_at<NDIM>(n, Ji, c, g, eos, aux);
 }
 
 // Electron internal energy per unit volume of density n (floored), divided by

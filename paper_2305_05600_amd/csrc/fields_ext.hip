@@ -342,8 +342,7 @@ int ext_impl(hvpic_ctx* c, float* B, float* pe, const float* n_half, const float
     fpl = A.PLin;
   } else if (mode == 0 && c->p.nsub > 0) {
     const float h = (float)(c->p.dt / c->p.nsub);
-    hipLaunchKernelGGL((k_field_prep<NDIM>), grid, blk, 0, s, n_half, (const float*)nullptr,
-                       J_half, (const float*)nullptr, 1.0f, 0.0f, g, eos, aux);
+    hipLaunchKernelGGL((k_field_prep<NDIM>), grid, blk, 0, s, n_half, J_half, g, eos, aux);
     const int cblocks = (int)std::min<int64_t>(ceil_div(3ll * nc, kBlock), 1024);
     hipLaunchKernelGGL(k_copy, dim3(cblocks), blk, 0, s, (const float*)B, Xh, 3ll * nc);
     hipLaunchKernelGGL(k_fill, dim3(cblocks), blk, 0, s, Xl, 3ll * nc, 0.0f);

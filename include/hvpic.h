@@ -375,9 +375,10 @@ typedef struct {
 /* The choices the autotuner makes.  push_chunk[c]: particles per push block
    for runs of class c of particles per cell (c = 0: below 64, 1: below 128,
    2: more), 0/1/2 = 1024/2048/3072; a chunk must span few enough cells for
-   the block's LDS windows, so a run whose plain push takes a shorter one keeps
-   that.  field_tile[c]: subcycle tile for runs of grid class c (0: below
-   128^2 cells, 1: larger), 0 = 32x8, 1 = 16x16, 2 = 64x4.
+   the block's LDS windows, so a run of fewer than 40 (2048) or 55 (3072)
+   particles per cell takes the plain push's 1024 instead.  field_tile[c]:
+   subcycle tile for runs of grid class c (0: below 128^2 cells, 1: larger),
+   0 = 32x8, 1 = 16x16, 2 = 64x4.
    blocks_per_cu[k]: persistent workgroups per CU of the push, the moment
    output, the sort passes and the tile launches (1..64). */
 typedef struct {
@@ -396,7 +397,8 @@ typedef struct hvpic_ensemble hvpic_ensemble;
    pointers set (the diagnostics may be NULL). */
 int hvpic_ensemble_workspace_bytes(const hvpic_run* runs, int nruns, size_t* bytes);
 
-/* The plain path's choices (3072-particle push blocks, 32x8 tiles). */
+/* The plain path's choices (3072-particle push blocks, 1024 for runs of few
+   particles per cell; 32x8 tiles). */
 int hvpic_tuning_default(hvpic_tuning* t);
 
 /* Creates an ensemble of nruns runs (the array is copied; the buffers and

@@ -1868,7 +1868,7 @@ Geo make_geo(const hvpic_ctx* c) {
 // Chunk and window of a store of n particles.  A block works through its LDS
 // windows only if the cells of its chunk fit them; otherwise every particle
 // takes global gathers and up to 28 FP64 global atomics, which took 30 times
-// as long (413 x 257 cells of 36 ions: 3295 us in chunks of 3072, 75 us in
+// as long (413 x 257 cells of 36 ions: 3295 us in chunks of 3072, 86 us in
 // chunks of 1024).  So the chunk (2D: 3072 or 1024 ions) or the window (3D: 24,
 // 40 or 64 cells wide for 1024 ions) follows the ions per cell; the limits lie
 // where the chunk of a uniform store fills its window (2D 3072 / 60 cells, 3D

@@ -104,7 +104,7 @@ __device__ __forceinline__ float tanh_f32(float x) {
 // of them at 32 x 32 channels) over all tiles of the wavefront: read from LDS
 // for every tile they took one LDS access per matrix instruction.  The next
 // tile's nine loads go out before the current tile's products.
-// 32 -> 32 at 1,048,576 pixels: 125 to 49 us (2.7 TB/s of HBM); at 131,072 29 to
+// 32 -> 32 at 1,048,576 pixels: 125 to 53 us (2.5 TB/s of HBM); at 131,072 29 to
 // 12 us.
 template <int CINP, int COUTP, int MODE>
 __global__ __launch_bounds__(256, 2) void k_conv3x3(const uint16_t* __restrict__ X,
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(const uint16_t* __restrict__
 // eight wavefronts' are added in order at the end.  The pixel stride (80 or 48
 // bytes) spreads the 16 pixels of an access over all banks.  The next tile's
 // loads go out before the current tile's products.
-// 32 x 32 channels, 1,048,576 pixels: 763 to 72 us (134 MB, 19.3 GFLOP).
+// 32 x 32 channels, 1,048,576 pixels: 763 to 43 us (134 MB, 19.3 GFLOP).
 constexpr int kSegX = 32, kSegY = 8, kWgThreads = 64 * kSegY;
 template <int CINP, int COUTP>
 __global__ __launch_bounds__(kWgThreads, 2) void k_conv3x3_wgrad(const uint16_t* __restrict__ X,

@@ -18,7 +18,7 @@
 // wavefront ballots.  Kernels: count (one wavefront per old cell; skipped when
 // the push already counted), tile totals of the new counts, per-cell prefix +
 // group bases (each block adds up the tile totals before its own), scatter
-// (one wavefront per four old cells).  A particle that moved further (or an
+// (one wavefront per four old cells, or fewer).  A particle that moved further (or an
 // inconsistent cell_start) is flagged by the count pass; the flag is handed
 // to the scatter kernel, in which one block then runs the general sort on its
 // own (slow, but it costs no extra launch in the common case and needs no host
@@ -165,7 +165,8 @@ __device__ __forceinline__ uint64_t match_code(int code, uint64_t valid, const u
 constexpr int kCellsPerWave = 2;
 constexpr int kCellBits = 1;
 constexpr int kCountBatches = 4;    // 64-particle batches whose keys are loaded together
-// The scatter takes kScatterCells cells per wavefront.
+// The scatter takes kScatterCells cells per wavefront, fewer in dense stores
+// (see enqueue_neighbour).
 constexpr int kScatterCells = 4;
 
 // Boundaries of the wavefront's cells: b(m) = cs_prev[a0 + m], m = 0..na,
@@ -930,12 +931,12 @@ __device__ void block_sort(int64_t n, int ncell, Fields in, Fields out, int32_t*
 
 // PERM: write the gather map out.perm[dst] = p instead of moving the fields.
 // Bound by instructions and by the two dependent trips to memory of a wavefront
-// (its bounds and bases, then its keys), so a wavefront takes four cells and
+// (its bounds and bases, then its keys), so a wavefront takes up to four cells and
 // loads ahead, and a batch costs some 60 instructions without a branch.  Map of
 // the 3D beam store (134M ions in 128^3 cells): 525 us, 2.9 TB/s (two cells
 // without the loads ahead 690, and 886 with the votes taken from a code's bits);
 // of 13M ions in 512 x 256, beside the field advance: 51 us (58, 76).
-template <int NDIM, bool PERM, bool OPEN = false>
+template <int NDIM, bool PERM, int CELLS, bool OPEN = false>
 __device__ __forceinline__ void nb_scatter_body(const int32_t* __restrict__ cs_prev, int64_t n,
                                                 const SortGeo& g, uint32_t* __restrict__ bases,
                                                 const Fields& in, const Fields& out, int32_t* cs,
@@ -943,13 +944,13 @@ __device__ __forceinline__ void nb_scatter_body(const int32_t* __restrict__ cs_p
                                                 uint32_t* rv0, uint32_t* rv1, int bid) {
   constexpr int ND = Dirs<NDIM>::N;
   constexpr int NF = PERM ? 0 : 7;        // fields carried through registers
-  constexpr int NG = kScatterCells * ND;  // groups of the wavefront
+  constexpr int NG = CELLS * ND;          // groups of the wavefront
   constexpr int GPL = (NG + 63) / 64;     // groups per lane
   __shared__ uint32_t s_next[kWaves][NG];  // next free slot of each group
   // the wavefront's number in scalar registers, and so what follows from it
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int a0 = (bid * kWaves + wid) * kScatterCells;
-  const int na = a0 < g.ncell ? min(kScatterCells, g.ncell - a0) : 0;
+  const int a0 = (bid * kWaves + wid) * CELLS;
+  const int na = a0 < g.ncell ? min(CELLS, g.ncell - a0) : 0;
   // The far decision, the group bases and the cell bounds are independent:
   // their loads go out together.
   const uint32_t far = __hip_atomic_load(&st->far_decision, __ATOMIC_RELAXED,
@@ -1104,14 +1105,14 @@ __device__ __forceinline__ void nb_scatter_body(const int32_t* __restrict__ cs_p
     run(std::false_type{});
 }
 
-template <int NDIM, bool PERM>
+template <int NDIM, bool PERM, int CELLS>
 __global__ __launch_bounds__(kBlock) void k_nb_scatter(const int32_t* __restrict__ cs_prev, int64_t n,
                                                        SortGeo g, uint32_t* __restrict__ bases,
                                                        Fields in, Fields out, int32_t* cs,
                                                        const Status* st, uint32_t* rk0, uint32_t* rk1,
                                                        uint32_t* rv0, uint32_t* rv1) {
-  nb_scatter_body<NDIM, PERM>(cs_prev, n, g, bases, in, out, cs, st, rk0, rk1, rv0, rv1,
-                              blockIdx.x);
+  nb_scatter_body<NDIM, PERM, CELLS>(cs_prev, n, g, bases, in, out, cs, st, rk0, rk1, rv0, rv1,
+                                     blockIdx.x);
 }
 
 // The open-boundary form (gather map): absorbed ions left out, injected
@@ -1138,8 +1139,8 @@ __global__ __launch_bounds__(kBlock) void k_nb_scatter_open(const int32_t* __res
                                                             uint32_t* __restrict__ bases,
                                                             Fields in, Fields out, int32_t* cs,
                                                             const Status* st) {
-  nb_scatter_body<NDIM, true, true>(cs_prev, n, g, bases, in, out, cs, st, nullptr, nullptr,
-                                    nullptr, nullptr, blockIdx.x);
+  nb_scatter_body<NDIM, true, kScatterCells, true>(cs_prev, n, g, bases, in, out, cs, st, nullptr,
+                                                   nullptr, nullptr, nullptr, blockIdx.x);
 }
 
 // The gather-map entries of the injected ions (slot r's ions, r over the
@@ -1205,8 +1206,8 @@ __global__ __launch_bounds__(kBlock) void k_nb_scatter_batch(const NbArgs* __res
   for_items(nitems, [&](int it) {
     const Item item = items[it];
     const NbArgs A = tab[item.run];
-    nb_scatter_body<2, true>(A.cs_prev, A.n, A.g, A.cnt, A.in, A.out, A.cs, A.st, A.rk0, A.rk1,
-                             A.rv0, A.rv1, item.idx);
+    nb_scatter_body<2, true, kScatterCells>(A.cs_prev, A.n, A.g, A.cnt, A.in, A.out, A.cs, A.st,
+                                            A.rk0, A.rk1, A.rv0, A.rv1, item.idx);
     __syncthreads();
   });
 }
@@ -1356,15 +1357,30 @@ void enqueue_neighbour(hvpic_ctx* c, const hvpic_particles* in, const Fields& ou
                        c->sort_cnt, g, cs, (const uint32_t*)blk);
   }
   timing_begin(c, HVPIC_KERNEL_SORT_SCATTER);
-  const int sblocks = (int)ceil_div(c->ncell, kWaves * kScatterCells);
-  if (out.perm)
-    hipLaunchKernelGGL((k_nb_scatter<NDIM, true>), dim3(sblocks), dim3(kBlock), 0, s, cs_prev, in->n,
-                       g, c->sort_cnt, fields_of(in), out, cs, (const Status*)c->status,
-                       c->rkey[0], c->rkey[1], c->rval[0], c->rval[1]);
-  else
-    hipLaunchKernelGGL((k_nb_scatter<NDIM, false>), dim3(sblocks), dim3(kBlock), 0, s, cs_prev,
-                       in->n, g, c->sort_cnt, fields_of(in), out, cs, (const Status*)c->status,
-                       c->rkey[0], c->rkey[1], c->rval[0], c->rval[1]);
+  auto scatter = [&](auto kern, int cells) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(c->ncell, kWaves * cells)), dim3(kBlock), 0, s,
+                       cs_prev, in->n, g, c->sort_cnt, fields_of(in), out, cs,
+                       (const Status*)c->status, c->rkey[0], c->rkey[1], c->rval[0], c->rval[1]);
+  };
+  // Cells per wavefront: the fewer ions a cell has, the more the two trips to
+  // memory at a wavefront's start weigh; many ions of many cells make it long,
+  // and leave a small grid with few wavefronts.  Moved stores, 4 / 2 / 1 cells: 512 x
+  // 512 cells of 16 ions 153 / 176 / 235 us, of 36 278 / 301 / 356, of 64 438 / 407 /
+  // 471, 256 x 256 of 200 344 / 331 / 295; maps, 4 / 2: 512 x 512 of 64 ions 164 / 174,
+  // 64 x 64 of 200 24.1 / 21.8, 16 x 16 of 1000 50 / 40.
+  const double ppc = (double)in->n / (double)c->ncell;
+  if (out.perm) {
+    if (ppc < 150.0)
+      scatter(k_nb_scatter<NDIM, true, kScatterCells>, kScatterCells);
+    else
+      scatter(k_nb_scatter<NDIM, true, 2>, 2);
+  } else if (ppc < 50.0) {
+    scatter(k_nb_scatter<NDIM, false, kScatterCells>, kScatterCells);
+  } else if (ppc < 150.0) {
+    scatter(k_nb_scatter<NDIM, false, 2>, 2);
+  } else {
+    scatter(k_nb_scatter<NDIM, false, 1>, 1);
+  }
   timing_end(c, HVPIC_KERNEL_SORT_SCATTER);
 }
 

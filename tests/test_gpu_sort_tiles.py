@@ -94,3 +94,10 @@ def test_neighbour(H, shape, ppc):
     assert np.array_equal(perm.cpu().numpy(), order)
     flags, _ = H.hvpic_sync_status(ctx.ctx)
     assert not flags & H.FLAG_MOVE_GT1
+
+
+@pytest.mark.parametrize("shape", [(3, 3, 1), (7, 9, 1), (66, 17, 1), (3, 3, 3), (9, 8, 5)])
+@pytest.mark.parametrize("ppc", [30.0, 110.0, 230.0])
+def test_neighbour_by_density(H, shape, ppc):
+    """The same at the densities that select four, two and one cells per wavefront."""
+    test_neighbour(H, shape, ppc)
